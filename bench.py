@@ -34,7 +34,7 @@ HBM_PEAK = 8000.0                        # GB/s
 CLASSES = ["gemm", "jacobi", "qr", "krp", "ls", "eigvals"]
 KERNEL_NAME = {
     "gemm": "gemm_kernel: grouped MFMA GEMM (TTMs, factor products, Grams)",
-    "jacobi": "jacobi_blk_kernel: symmetric eigendecomposition with vectors (ST-HOSVD, two-pass Jacobi on 2x2 blocks)",
+    "jacobi": "jacobi_osj_kernel: symmetric eigendecomposition with vectors (ST-HOSVD, Cholesky and one-sided Jacobi)",
     "qr": "chol_kernel: Cholesky of the range-sketch Gram (Cholesky-QR3)",
     "krp": "krp_kernel: Khatri-Rao / MTTKRP core reductions",
     "ls": "ls_add_kernel: sketched least-squares column update",
@@ -49,8 +49,8 @@ UNIT = {"gemm": "2*M*N*K flops per product", "jacobi": "9*N^3 flops per eigendec
 NOTE = {
     "gemm": "GEMMs run in FP32 inside cycles and FP64 in the restart steps; peak is the FP32 matrix-core peak",
     "jacobi": "one workgroup per matrix (ST-HOSVD modes are sequential), so the kernel can use at most 1/256 of "
-              "the chip's 78.6 TFLOP/s vector peak (packed FP32 disabled); latency bound (one barrier per rotation "
-              "round, two when the round rotates)",
+              "the chip's 78.6 TFLOP/s vector peak (packed FP32 disabled); latency bound (one dependent chain and "
+              "one barrier per rotation step)",
     "qr": "latency bound single-workgroup factorization",
     "krp": "core reductions, L2 resident",
     "ls": "FP64 single-workgroup update",

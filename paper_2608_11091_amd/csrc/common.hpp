@@ -116,13 +116,13 @@ __device__ __forceinline__ double rdlane(double v, int lane) {
 // quad_perm[2,3,0,1], 0x141 row_half_mirror, 0x140 row_mirror.
 template <int CTRL>
 __device__ __forceinline__ float dpp_mov(float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xF, 0xF, true));
 }
 template <int CTRL>
 __device__ __forceinline__ double dpp_mov(double v) {
   const long long b = __double_as_longlong(v);
-  const unsigned lo = unsigned(__builtin_amdgcn_update_dpp(0, int(b), CTRL, 0xF, 0xF, false));
-  const unsigned hi = unsigned(__builtin_amdgcn_update_dpp(0, int(b >> 32), CTRL, 0xF, 0xF, false));
+  const unsigned lo = unsigned(__builtin_amdgcn_mov_dpp(int(b), CTRL, 0xF, 0xF, true));
+  const unsigned hi = unsigned(__builtin_amdgcn_mov_dpp(int(b >> 32), CTRL, 0xF, 0xF, true));
   return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
 

@@ -8,12 +8,10 @@
 //    global memory (it stays in the L2 of the workgroup's XCD), reduced in
 //    place; each step streams the trailing block once, applying the previous
 //    step's rank-2 update and forming the next product A v in the same pass.
-//  * Eigenvalues and vectors (N <= 64): cyclic Jacobi with the round-robin
-//    parallel ordering on 2 x 2 blocks, full matrix and eigenvector block in
-//    LDS.  A rotation is taken only when |a_pq| > eps * sqrt(|a_pp a_qq|),
-//    the relative criterion under which Jacobi resolves the small eigenvalues
-//    of graded positive semidefinite matrices to high relative accuracy; a
-//    sweep without rotations ends it.
+//  * Eigenvalues and vectors of positive semidefinite matrices (N <= 64):
+//    Cholesky factor and one-sided cyclic Jacobi on its columns, which stay in
+//    registers.  The relative rotation criterion resolves the small
+//    eigenvalues of graded matrices to high relative accuracy.
 // Results are sorted in descending order; an optional rank rule (RoundSum
 // effective rank / ST-HOSVD truncation) runs on the sorted spectrum.
 #include <cfloat>
@@ -35,13 +33,15 @@ template <> struct Vec4<double> { using type = double __attribute__((ext_vector_
 template <typename T> struct Lim;
 template <> struct Lim<double> {
   static __device__ constexpr double eps() { return DBL_EPSILON; }
-  static __device__ constexpr double sqrt_eps() { return 1.4901161193847656e-08; }  // 2^-26
+  static __device__ constexpr double stop() { return 1e-9; }  // 2^-21 of it is about eps
   static __device__ constexpr double tiny() { return 1e-300; }
+  static __device__ constexpr double pivot_tiny() { return 1e-300; }  // stands for a zero pivot
 };
 template <> struct Lim<float> {
   static __device__ constexpr float eps() { return FLT_EPSILON; }
-  static __device__ constexpr float sqrt_eps() { return 3.4526698e-04f; }  // 2^-11.5
+  static __device__ constexpr float stop() { return 3.4526698e-04f; }  // sqrt(eps)
   static __device__ constexpr float tiny() { return 1e-37f; }
+  static __device__ constexpr float pivot_tiny() { return 1e-36f; }
 };
 
 // A task does nothing when its pair flag or any rank certificate is set.
@@ -53,16 +53,17 @@ __device__ __forceinline__ bool task_skipped(const EigTask<T>& t) {
   return c;
 }
 
-// Rank rules on a descending spectrum; returns the rank (run by one thread).
-template <typename T>
-__device__ int apply_rule(const EigRule& ru, const T* lam_desc, int N) {
+// Rank rules on a descending spectrum lam_desc(0) >= lam_desc(1) >= ..; returns
+// the rank.
+template <typename T, typename Lam>
+__device__ int apply_rule(const EigRule& ru, Lam lam_desc, int N) {
   int r = 0;
   if (ru.kind == 1) {
-    const double l0 = N > 0 ? double(lam_desc[0]) : 0.0;
+    const double l0 = N > 0 ? double(lam_desc(0)) : 0.0;
     if (N > 0 && l0 > 0.0) {
       double total = 0.0;
       for (int i = 0; i < N; ++i) {
-        const double li = double(lam_desc[i]);
+        const double li = double(lam_desc(i));
         total += li > ru.delta * l0 ? li : 0.0;
       }
       const double tau = *ru.tau;
@@ -70,7 +71,7 @@ __device__ int apply_rule(const EigRule& ru, const T* lam_desc, int N) {
       double tail = 0.0;
       r = N;
       for (int i = N - 1; i >= 0; --i) {
-        const double li = double(lam_desc[i]);
+        const double li = double(lam_desc(i));
         tail += li > ru.delta * l0 ? li : 0.0;
         if (tail <= thr) r = i;
         else break;
@@ -88,7 +89,7 @@ __device__ int apply_rule(const EigRule& ru, const T* lam_desc, int N) {
       double tail = 0.0;
       r = N;
       for (int i = N - 1; i >= 0; --i) {
-        const double li = double(lam_desc[i]);
+        const double li = double(lam_desc(i));
         tail += li > 0.0 ? li : 0.0;
         if (tail <= thr) r = i;
         else break;
@@ -200,7 +201,7 @@ __device__ void tridiag_spectrum(const EigTask<T>& tk_, T* dd, T* ee, T* lam, T*
   __syncthreads();
   if (tk_.lam)
     for (int i = tid; i < N; i += nthreads) tk_.lam[i] = lam[i];
-  if (tid == 0 && tk_.rule.kind != 0) *tk_.rule.rank_out = apply_rule<T>(tk_.rule, lam, N);
+  if (tid == 0 && tk_.rule.kind != 0) *tk_.rule.rank_out = apply_rule<T>(tk_.rule, [&](int i) { return lam[i]; }, N);
 }
 
 // Householder tridiagonalisation with the matrix in registers: lane l of
@@ -590,72 +591,122 @@ __global__ __launch_bounds__(1024) void tridiag_gm_kernel(const EigTask<T>* __re
 // ------------------------------------------------------------ eigenvalues + vectors
 
 
-// Jacobi rotation annihilating a_pq: t = tan(phi), c = cos(phi).  FP32 uses
-// the hardware reciprocal / square-root approximations (about 1 ulp, below
-// the rounding of applying the rotation); FP64 uses IEEE operations.
-__device__ __forceinline__ float jac_sqrt(float x) { return __builtin_amdgcn_sqrtf(x); }
-__device__ __forceinline__ double jac_sqrt(double x) { return sqrt(x); }
-__device__ __forceinline__ void jac_rot(float app, float aqq, float apq, float& tt, float& c) {
-  const float theta = (aqq - app) * __builtin_amdgcn_rcpf(2.0f * apq);
-  const float at = fabsf(theta);
-  const float tmag = at > 1e15f ? 0.5f * __builtin_amdgcn_rcpf(at)
-                                : __builtin_amdgcn_rcpf(at + __builtin_amdgcn_sqrtf(fmaf(theta, theta, 1.0f)));
-  tt = theta >= 0.0f ? tmag : -tmag;
-  c = __builtin_amdgcn_rsqf(fmaf(tt, tt, 1.0f));
-}
-__device__ __forceinline__ void jac_rot(double app, double aqq, double apq, double& tt, double& c) {
-  const double theta = (aqq - app) / (2.0 * apq);
-  if (fabs(theta) > 1e15) tt = 0.5 / theta;
-  else tt = (theta >= 0.0 ? 1.0 : -1.0) / (fabs(theta) + sqrt(theta * theta + 1.0));
-  c = 1.0 / sqrt(tt * tt + 1.0);
+// 1 / sqrt(x) to working accuracy (about 1 ulp): the hardware approximation,
+// in FP64 (about 23 bits) followed by one third-order step.
+__device__ __forceinline__ float rsq_full(float x) { return __builtin_amdgcn_rsqf(x); }
+__device__ __forceinline__ double rsq_full(double x) {
+  const double y = __builtin_amdgcn_rsq(x);
+  const double e = fma(-x * y, y, 1.0);
+  return fma(y * e, fma(0.375, e, 0.5), y);
 }
 
+// t = tan of the rotation that makes columns with dot product d and squared
+// norms nx, ny orthogonal: sign(z) / (|z| + sqrt(1 + z^2)), z = (ny - nx) / 2d.
+// FP64 forms z with the hardware reciprocal and the rest in FP32: an angle
+// with a relative error of 2^-21 leaves that share of the product it
+// annihilates, which the stopping rule allows for; the cosine belongs to the
+// t that is used and has working accuracy, so the rotation is orthogonal.
+// The root is taken of a z bounded against overflow: it is |z| itself long
+// before the bound.
+__device__ __forceinline__ float jac_tan_of(float z) {
+  const float az = fabsf(z);
+  const float q = fminf(az, 1e18f);
+  const float w = fmaf(q, q, 1.0f);
+  return copysignf(__builtin_amdgcn_rcpf(az + fmaxf(w * __builtin_amdgcn_rsqf(w), az)), z);
+}
+__device__ __forceinline__ float jac_tan(float d, float nx, float ny) {
+  return jac_tan_of((ny - nx) * __builtin_amdgcn_rcpf(d + d));
+}
+__device__ __forceinline__ double jac_tan(double d, double nx, double ny) {
+  return double(jac_tan_of(float((ny - nx) * __builtin_amdgcn_rcp(d + d))));
+}
 
-// Two-sided cyclic Jacobi on 2 x 2 blocks.  With the round-robin ordering a
-// round applies N/2 disjoint rotations J, A <- J^T A J; every entry of A
-// belongs to exactly one block (rows of pair I) x (columns of pair J), and the
-// block's new value depends on that block and the two rotations only.  One
-// thread per block with I <= J updates it in place and writes the mirrored
-// block (J, I) too, so A stays exactly symmetric (full storage, column-major,
-// leading dimension 65 = 1 mod 32: both a column and a row of the lanes'
-// entries fall in distinct banks).  The kernel is bound by instruction issue
-// (16 waves share 4 SIMDs), so every index that does not change between
-// rounds is computed once, and V is rotated four rows per lane with 16-byte
-// LDS accesses.  Per round:
-//   phase 1: wave 0 computes the round's rotations from A (one lane per pair)
-//            and decides whether any pair rotates -- if none does, the round
-//            is skipped; meanwhile other waves apply the previous executed
-//            round's rotations to the eigenvector block (V <- V J, one round
-//            behind);
-//   phase 2: every block thread rotates its block (the 2 x 2 pivot blocks are
-//            set to their exact diagonal form).
-// A rotation is taken only when |a_pq| > eps sqrt(|a_pp a_qq|) (relative
-// criterion: small eigenvalues of graded matrices keep their digits); a sweep
-// without rotations ends the iteration.  Every decision is taken once, by
-// wave 0, and read by all threads after a barrier; decisions are
-// double-buffered by round parity because wave 0 may enter the next round's
-// first phase while slower waves still read the current one.
+// Sum over the 8 lanes of a column group; every lane gets the same value.
 template <typename T>
-__global__ __launch_bounds__(1024) void jacobi_blk_kernel(const EigTask<T>* __restrict__ tasks, int N) {
+__device__ __forceinline__ T group8_sum(T v) {
+  v += dpp_mov<0xB1>(v);
+  v += dpp_mov<0x4E>(v);
+  v += dpp_mov<0x141>(v);
+  return v;
+}
+
+// Whether the columns with dot product d and squared norms nx, ny are to be
+// rotated against each other (|d| > tol ||x|| ||y||).
+__device__ __forceinline__ bool above_tol(double d, double nx, double ny, double tol) {
+  return d * d > tol * tol * nx * ny;
+}
+__device__ __forceinline__ bool above_tol(float d, float nx, float ny, float tol) {
+  // norms one by one: their product underflows on strongly graded spectra
+  const float ad = fabsf(d);
+  return ad > Lim<float>::tiny() && ad > tol * (__builtin_amdgcn_sqrtf(nx) * __builtin_amdgcn_sqrtf(ny));
+}
+
+// Largest of a value over the wave, the same in every lane.
+__device__ __forceinline__ unsigned wave_umax(unsigned v) {
+  v = max(v, unsigned(__builtin_amdgcn_mov_dpp(int(v), 0xB1, 0xF, 0xF, true)));
+  v = max(v, unsigned(__builtin_amdgcn_mov_dpp(int(v), 0x4E, 0xF, 0xF, true)));
+  v = max(v, unsigned(__builtin_amdgcn_mov_dpp(int(v), 0x141, 0xF, 0xF, true)));
+  v = max(v, unsigned(__builtin_amdgcn_mov_dpp(int(v), 0x140, 0xF, 0xF, true)));
+  const unsigned a = __builtin_amdgcn_readlane(int(v), 0), b = __builtin_amdgcn_readlane(int(v), 16);
+  const unsigned c = __builtin_amdgcn_readlane(int(v), 32), d = __builtin_amdgcn_readlane(int(v), 48);
+  const unsigned ab = a > b ? a : b, cd = c > d ? c : d;
+  return __builtin_amdgcn_readfirstlane(int(ab > cd ? ab : cd));
+}
+
+// Symmetric positive semidefinite eigensolver with vectors, one workgroup per
+// matrix of order N <= 64: pivoted Cholesky factor A = L L^T (rows in place),
+// then one-sided Jacobi on the columns of L.  Rotations from the right make the columns orthogonal,
+// L W = X with X^T X diagonal, so A = X X^T: the eigenvalues are the squared
+// column norms and the eigenvectors the normalised columns; no eigenvector
+// block is carried along.  Both steps keep the small eigenvalues of a graded
+// matrix D H D to the relative accuracy that the conditioning of H allows, as
+// the Cholesky factor is formed entry by entry relative to its diagonal and a
+// rotation is taken whenever |x_p . x_q| > eps ||x_p|| ||x_q||.  A pivot at
+// or below its rounding level N eps a_kk is raised to it and its column of L
+// cut below the diagonal (what stands there is rounding noise that a division
+// by such a pivot would amplify), which leaves L regular and the eigenvectors
+// a full orthonormal set whatever the rank of A.
+//
+// Why this shape: the solver is one dependent chain of rounds on one CU, so
+// the time of a round is what counts.  The two-sided form it replaces kept A
+// and V in LDS and moved about 4 matrices' worth of LDS traffic a round over
+// two barriers of 16 waves (1.5 us a round in FP64, 0.8 us in FP32).  Here
+// lane l of group g (8 lanes) holds rows l, l + 8, .. of the two columns of
+// pair g in registers, one wave per SIMD; the dot product is RPL FMAs and
+// three DPP steps, and only one column of every pair moves between rounds.
+// The rounds follow the odd-even transposition ordering: columns sit at
+// positions 0 .. NP - 1, odd steps rotate (2g, 2g + 1), even steps
+// (2g + 1, 2g + 2), and both swap the two columns, so every pair meets once in
+// NP steps.  Group g owns position 2g + 1; before an even step every group
+// publishes the column at position 2g (buffer 1) and takes its right
+// neighbour's, after it hands the one at 2g + 2 on (buffer 2).  Position 0
+// waits in buffer 1 during even steps.  Each buffer is written again only
+// after a barrier that follows its readers, so a step needs one barrier.
+// The squared norms travel with the columns, updated by the rotation
+// (n_p - t d, n_q + t d) and computed afresh at the start of every sweep.
+//
+// Bound: the dependent chain of one wave per SIMD (about 6 cycles an
+// instruction): a rotation step (dot and DPP reduction, the angle's
+// reciprocals and square roots, the rotation, LDS hand-over and barrier) takes
+// 920 cycles in FP64 and 730 in FP32, a Cholesky step 990 and 730.  Measured at
+// order 53 (two-sided form in brackets): three Grams of 32 partials each 158 us
+// (419) in FP64, 105 us (270) in FP32; a nearly diagonal Gram, the second pass,
+// 47 us (66) and 37 us (48); three Grams of order 15 30 us (71) and 22 us (43).
+template <typename T, int RPL>
+__global__ __launch_bounds__(1024) void jacobi_osj_kernel(const EigTask<T>* __restrict__ tasks, int N) {
   constexpr int NT = 1024;
-  constexpr int NPM = VEC_NMAX;
-  constexpr int HM = NPM / 2;
-  constexpr int LD = NPM + 1;            // A leading dimension (65 = 1 mod 32)
-  constexpr int LDV = NPM + 4;           // V leading dimension: 16-byte aligned columns
-  constexpr int RQ = NPM / 4;            // row quads of V
-  using T4 = typename Vec4<T>::type;
-  __shared__ T A[NPM * LD];              // A[c * LD + r]
-  __shared__ __align__(16) T V[NPM * LDV];
-  __shared__ T csb[2][HM][2];            // rotations (c, s) of a round, by buffer
-  __shared__ T tnb[2][HM];               // tan of the round's rotations, by buffer
-  __shared__ unsigned short sch[NPM][HM];  // round-robin schedule: pair k of round t = p | q << 8, p < q
-  __shared__ unsigned int rmask[2];      // pairs that rotate (bit k), by round parity
-  __shared__ int skip_s[2];
-  __shared__ int rotflag[3];
-  __shared__ int bigflag[3];             // a rotation of the sweep had a scaled off-diagonal above sqrt(eps)
-  __shared__ int rank_s;
-  __shared__ int posv[NPM];
-  __shared__ T lam_s[NPM];
+  constexpr int JW = 4;                               // waves of the factorisation and the rotations
+  constexpr int NM = 8 * RPL;                         // row capacity (N <= NM)
+  constexpr int LDX = (RPL & 1) ? NM : NM + 8;        // an odd multiple of 8: groups in distinct LDS banks
+  constexpr int LDG = VEC_NMAX + 1;
+  constexpr int NB = 2 * RPL;                         // Cholesky columns per wave
+  __shared__ T G[VEC_NMAX * LDG];                     // the matrix: G[c * LDG + r], lower triangle
+  __shared__ T X0[VEC_NMAX * LDX];                    // columns of L
+  __shared__ T buf[2][VEC_NMAX / 2][LDX];             // columns on the move
+  __shared__ T nbuf[2][VEC_NMAX / 2];                 // their squared norms
+  __shared__ __align__(16) T colk[2][kWave];          // pivot column, by step parity
+  __shared__ T lam_s[VEC_NMAX], lam_d[VEC_NMAX];
+  __shared__ int bigflag[3];
   const EigTask<T> tk_ = tasks[blockIdx.x];
   if (task_skipped(tk_)) return;
   const int tid = threadIdx.x;
@@ -663,212 +714,259 @@ __global__ __launch_bounds__(1024) void jacobi_blk_kernel(const EigTask<T>* __re
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
   const int NP = N + (N & 1);
   const int H = NP / 2;
-  const int M = NP - 1;  // rounds per sweep
-  for (int e = tid; e < M * H; e += NT) {
-    const int t = e / H, k = e % H;
-    const int a = k == 0 ? 0 : ((k - 1 + t) % M) + 1;
-    const int b = ((NP - 2 - k + t) % M) + 1;
-    const int p = a < b ? a : b, q = a < b ? b : a;
-    sch[t][k] = (unsigned short)(p | (q << 8));
-  }
-  // the lower triangle, column by column (contiguous reads of whole cache
-  // lines), mirrored into the upper one in LDS; the padding row and column
-  // of an odd order are zero
-  for (int e = tid; e < NP * NP; e += NT) {
-    const int c = e / NP, r = e % NP;
-    if (r < c) continue;
+  // ---- load: the lower triangle, contiguous along its columns (column c
+  // starts at entry c N - c (c - 1) / 2 of the packed triangle)
+  for (int e = tid; e < N * (N + 1) / 2; e += NT) {
+    const float h = float(N) + 0.5f;
+    int c = int(h - __builtin_amdgcn_sqrtf(h * h - 2.0f * float(e)));
+    while (c > 0 && c * N - c * (c - 1) / 2 > e) --c;
+    while ((c + 1) * N - (c + 1) * c / 2 <= e) ++c;
+    const int r = c + e - (c * N - c * (c - 1) / 2);
+    const size_t at = r + (size_t)c * tk_.lda;
     T a = T(0);
-    if (r < N) {
-      const size_t at = r + (size_t)c * tk_.lda;
-      if (tk_.part) {  // the matrix's split-K partials, summed in split order
-        // (eight loads in flight at a time; the additions keep their order)
-        const T* pp = tk_.part + at;
-        int sp = 0;
-        for (; sp + 8 <= tk_.splits; sp += 8) {
-          T v[8];
+    if (tk_.part) {  // the matrix's split-K partials, summed in split order
+      // (sixteen loads in flight at a time; the additions keep their order)
+      const GPtr<T> pp = (GPtr<T>)(tk_.part + at);
+      for (int sp = 0; sp < tk_.splits; sp += 16) {
+        T v[16];
 #pragma unroll
-          for (int u = 0; u < 8; ++u) v[u] = pp[(sp + u) * tk_.pstride];
+        for (int u = 0; u < 16; ++u) v[u] = pp[min(sp + u, tk_.splits - 1) * tk_.pstride];
 #pragma unroll
-          for (int u = 0; u < 8; ++u) a += v[u];
-        }
-        for (; sp < tk_.splits; ++sp) a += pp[sp * tk_.pstride];
-      } else {
-        a = tk_.A[at];
+        for (int u = 0; u < 16; ++u) a += sp + u < tk_.splits ? v[u] : T(0);
       }
+    } else {
+      a = ((GPtr<T>)tk_.A)[at];
     }
-    A[c * LD + r] = a;
-    A[r * LD + c] = a;
+    G[c * LDG + r] = a;
   }
-  for (int e = tid; e < NP * LDV; e += NT) {
-    const int c = e / LDV, r = e % LDV;
-    V[e] = (r == c) ? T(1) : T(0);
-  }
-  if (tid < 3) {
-    rotflag[tid] = 0;
-    bigflag[tid] = 0;
-  }
-  // block task of this thread (pair I <= pair J), fixed for the whole kernel
-  const int nblk = H * (H + 1) / 2;
-  int bI = 0, bJ = 0;
-  const bool blk = tid < nblk;
-  if (blk) {
-    int J = 0, rem = tid;
-    while (rem >= J + 1) {
-      rem -= J + 1;
-      ++J;
-    }
-    bI = rem;
-    bJ = J;
-  }
-  // V task: rows 4 vi .. 4 vi + 3 of the columns of pair vJ (threads of waves 1..)
-  const int vt = tid - kWave;
-  const int nq = (NP + 3) / 4;
-  const bool vtask = vt >= 0 && vt < nq * H;
-  const int vi = vtask ? vt % nq : 0, vJ = vtask ? vt / nq : 0;
-  const bool vtask2 = vt >= 0 && vt + (NT - kWave) < nq * H;  // a second task for large N
-  const int vi2 = vtask2 ? (vt + NT - kWave) % nq : 0, vJ2 = vtask2 ? (vt + NT - kWave) / nq : 0;
-  static_assert(RQ * HM <= 2 * (NT - kWave), "two V tasks per thread cover every row quad and pair");
+  for (int e = tid; e < NP * LDX; e += NT) X0[e] = T(0);
+  if (tid < 3) bigflag[tid] = 0;
   __syncthreads();
-  int g = 0;            // rounds executed or skipped so far (buffer parity)
-  int prev_t = -1;      // round whose rotations V still has to take (-1: none)
-  int prev_buf = 0;
-  auto v_rot = [&](int t, int buf, int i4, int J) {
-    const unsigned pq = sch[t][J];
-    const int p = int(pq & 0xffu), q = int(pq >> 8);
-    const T c = csb[buf][J][0], sn = csb[buf][J][1];
-    T4* vp = reinterpret_cast<T4*>(&V[p * LDV + 4 * i4]);
-    T4* vq = reinterpret_cast<T4*>(&V[q * LDV + 4 * i4]);
-    const T4 a = *vp, b = *vq;
-    *vp = c * a - sn * b;
-    *vq = sn * a + c * b;
+  if (wave >= JW) return;  // a barrier waits for the waves that are left
+
+  // ---- scale by a power of two so that the trace is in [1, 2)
+  T tr = T(0);
+  {
+    const T dg = lane < N ? G[lane * LDG + lane] : T(0);
+    tr = wave_sum(dg);
+  }
+  int ex = 0;
+  if (tr > T(0) && tr < T(INFINITY)) (void)frexp(tr, &ex);
+  const T down = ldexp(T(1), -ex), up = ldexp(T(1), ex);
+
+  // ---- Cholesky: lane = row, wave w holds the columns w NB .. w NB + NB - 1 of
+  // the remaining symmetric matrix in registers and every wave the remaining
+  // diagonal.  The pivot column goes through LDS, one barrier a step; its
+  // entries for a wave's columns are read across lanes (as LDS broadcasts
+  // they took longer than the whole update).  The first pass of ST-HOSVD meets
+  // matrices of any rank in any order and takes the largest remaining diagonal
+  // (to 17 bits, ties to the lowest row; all waves derive the same p), without
+  // which a rank-deficient matrix amplifies rounding; the second pass (the one
+  // with the truncation rule) has its rows sorted by the first and keeps
+  // their order, which saves the search.
+  {
+    typedef T Cols __attribute__((ext_vector_type(16)));
+    static_assert(NB <= 16, "a wave's columns fit the vector");
+    const bool piv = tk_.rule.kind != 2;
+    Cols a;
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      const int j = wave * NB + b;
+      const bool in = lane < N && j < N;
+      const int hi = in ? (j > lane ? j : lane) : 0, lo = in ? (j > lane ? lane : j) : 0;
+      const T v = G[lo * LDG + hi];
+      a[b] = in ? v * down : T(0);
+    }
+    T dg = lane < N ? G[lane * LDG + lane] * down : T(0);
+    const T floor_l = dg * (T(N) * Lim<T>::eps());
+    bool alive = lane < N;
+    // every lane prepares its own row as the next pivot: l_pp in dl, 1 / l_pp in
+    // ri (zero where the rest of the column is cut)
+    T dl = T(0), ri = T(0);
+    auto prepare = [&]() {
+      const bool dead = dg <= floor_l;  // false for NaN, which stays
+      const T pv = dead ? (floor_l > T(0) ? floor_l : Lim<T>::pivot_tiny()) : dg;
+      const T r = rsq_full(pv);
+      dl = pv * r;
+      ri = dead ? T(0) : r;
+    };
+    int p = 0;
+    auto choose = [&](int k) {  // the pivot of step k, its column published to the step's buffer
+      p = k;
+      if (piv) {
+        const unsigned bits = __float_as_uint(fmaxf(float(dg), 0.0f));
+        p = 63 - int(wave_umax(alive ? 0x80000000u | (bits & ~63u) | unsigned(63 - lane) : 0u) & 63u);
+      }
+      const int b = p - wave * NB;
+      if (b >= 0 && b < NB) colk[k & 1][lane] = a[b];
+    };
+    prepare();
+    choose(0);
+    for (int k = 0; k < N; ++k) {
+      const T rp = rdlane(ri, p);
+      const bool own = lane == p;
+      alive = alive && !own;
+      const T rc = alive ? rp : T(0);  // row of L below the pivot: c rc
+      __syncthreads();
+      const T c = colk[k & 1][lane];
+      T cj[NB];
+#pragma unroll
+      for (int b = 0; b < NB; ++b) cj[b] = rdlane(c, wave * NB + b);
+      // all reads before the first update: a read right before its use stalls
+      __builtin_amdgcn_sched_barrier(0);
+      const T x = c * rc;
+      const T f = x * rp;
+      const T lk = own ? dl : x;
+      dg = fma(-x, x, dg);
+#pragma unroll
+      for (int b = 0; b < NB; ++b) a[b] = fma(-f, cj[b], a[b]);
+      prepare();
+      if (k + 1 < N) choose(k + 1);
+      if (wave == (k & (JW - 1)) && lane < NM) X0[k * LDX + lane] = lk;
+    }
+  }
+  __syncthreads();
+
+  // ---- one-sided Jacobi
+  const int g = tid >> 3, l = tid & 7;
+  const bool act = g < H;
+  const bool last = g == H - 1;
+  const bool pair = g < H - 1;
+  // the last group idles in even steps: its column A becomes the one at its
+  // position (the exchange that B needs comes with the rotation)
+  const T c_off = last ? T(0) : T(1), s_off = last ? T(1) : T(0);
+  const int gn = pair ? g + 1 : 0, gs = act ? g : 0, g0 = g == 0 ? 0 : 1;
+  T A[RPL], B[RPL];
+  T nA = T(0), nB = T(0);
+#pragma unroll
+  for (int i = 0; i < RPL; ++i) {
+    A[i] = act ? X0[(2 * g) * LDX + l + 8 * i] : T(0);
+    B[i] = act ? X0[(2 * g + 1) * LDX + l + 8 * i] : T(0);
+  }
+  bool big = false;
+  // rotates (x, y) to orthogonal columns; where nothing is to be done applies
+  // (co, so): the identity, or the exchange (x, y) <- (-y, x)
+  auto rotate = [&](T (&x)[RPL], T (&y)[RPL], T& nx, T& ny, bool on, T co, T so) {
+    T d0 = x[0] * y[0], d1 = T(0);
+#pragma unroll
+    for (int i = 2; i < RPL; i += 2) d0 = fma(x[i], y[i], d0);
+#pragma unroll
+    for (int i = 1; i < RPL; i += 2) d1 = i == 1 ? x[i] * y[i] : fma(x[i], y[i], d1);
+    const T d = group8_sum(d0 + d1);
+    const bool flag = on && above_tol(d, nx, ny, Lim<T>::eps());
+    big |= flag && above_tol(d, nx, ny, Lim<T>::stop());
+    const T t = flag ? jac_tan(d, nx, ny) : T(0);
+    const T cr = rsq_full(fma(t, t, T(1)));
+    const T c = flag ? cr : co;
+    const T s = flag ? t * cr : so;
+    nx = fma(-t, d, nx);
+    ny = fma(t, d, ny);
+#pragma unroll
+    for (int i = 0; i < RPL; ++i) {
+      const T xi = x[i], yi = y[i];
+      x[i] = fma(-s, yi, c * xi);
+      y[i] = fma(s, xi, c * yi);
+    }
+  };
+  auto norm2 = [&](const T (&x)[RPL]) {
+    T d0 = T(0), d1 = T(0);
+#pragma unroll
+    for (int i = 0; i < RPL; i += 2) d0 = fma(x[i], x[i], d0);
+#pragma unroll
+    for (int i = 1; i < RPL; i += 2) d1 = fma(x[i], x[i], d1);
+    return group8_sum(d0 + d1);
   };
   for (int sweep = 0; sweep < 40; ++sweep) {
-    for (int t = 0; t < M; ++t) {
-      const int cur = g & 1;
-      // ---- phase 1
-      if (wave == 0) {
-        T c = T(1), sn = T(0), tt = T(0);
-        int flag = 0, big = 0;
-        if (lane < H) {
-          const unsigned pq = sch[t][lane];
-          const int p = int(pq & 0xffu), q = int(pq >> 8);
-          const T app = A[p * LD + p], aqq = A[q * LD + q], apq = A[q * LD + p];
-          const T aa = fabs(apq);
-          const T sc = jac_sqrt(fabs(app * aqq));
-          flag = (q < N) && aa > Lim<T>::tiny() && aa > Lim<T>::eps() * sc;
-          big = flag && aa > Lim<T>::sqrt_eps() * sc;
-          T tr, cr;
-          jac_rot(app, aqq, flag ? apq : T(1), tr, cr);
-          if (flag) {
-            c = cr;
-            sn = tr * cr;
-            tt = tr;
-          }
-          csb[cur][lane][0] = c;
-          csb[cur][lane][1] = sn;
-          tnb[cur][lane] = tt;
-        }
-        const unsigned long long fm = __ballot(flag);
-        const unsigned long long bm = __ballot(big);
-        if (lane == 0) {
-          skip_s[cur] = fm == 0;
-          rmask[cur] = (unsigned int)fm;
-          if (fm != 0) rotflag[sweep % 3] = 1;
-          if (bm != 0) bigflag[sweep % 3] = 1;
-          if (t == 0) {
-            rotflag[(sweep + 1) % 3] = 0;
-            bigflag[(sweep + 1) % 3] = 0;
-          }
-        }
-      } else if (prev_t >= 0) {
-        if (vtask) v_rot(prev_t, prev_buf, vi, vJ);
-        if (vtask2) v_rot(prev_t, prev_buf, vi2, vJ2);
+    big = false;
+    if (tid == 0) bigflag[(sweep + 1) % 3] = 0;
+    nA = norm2(A);
+    nB = norm2(B);
+    for (int ds = 0; ds < H; ++ds) {
+      rotate(A, B, nA, nB, act, T(1), T(0));
+      // swapped: B sits at position 2g, A at 2g + 1
+      if (act) {
+#pragma unroll
+        for (int i = 0; i < RPL; ++i) buf[0][g][l + 8 * i] = B[i];
+        if (l == 0) nbuf[0][g] = nB;
       }
       __syncthreads();
-      ++g;
-      if (skip_s[cur]) {
-        prev_t = -1;
-        continue;  // uniform: every thread read the same flag after the barrier
+      // (a group without a right neighbour reads some column and leaves it alone)
+#pragma unroll
+      for (int i = 0; i < RPL; ++i) B[i] = buf[0][gn][l + 8 * i];
+      nB = nbuf[0][gn];
+      rotate(A, B, nA, nB, pair, c_off, s_off);
+      // swapped: B sits at position 2g + 1, A at 2g + 2 (the last group keeps A)
+      if (pair) {
+#pragma unroll
+        for (int i = 0; i < RPL; ++i) buf[1][g + 1][l + 8 * i] = A[i];
+        if (l == 0) nbuf[1][g + 1] = nA;
       }
-      // ---- phase 2
-      if (blk) {
-        const unsigned pqI = sch[t][bI], pqJ = sch[t][bJ];
-        const int pI = int(pqI & 0xffu), qI = int(pqI >> 8);
-        const int pJ = int(pqJ & 0xffu), qJ = int(pqJ >> 8);
-        const T cI = csb[cur][bI][0], sI = csb[cur][bI][1];
-        const T cJ = csb[cur][bJ][0], sJ = csb[cur][bJ][1];
-        const T x00 = A[pJ * LD + pI], x01 = A[qJ * LD + pI];
-        const T x10 = A[pJ * LD + qI], x11 = A[qJ * LD + qI];
-        // columns (X J_J), then rows (J_I^T Y)
-        const T y00 = cJ * x00 - sJ * x01, y01 = sJ * x00 + cJ * x01;
-        const T y10 = cJ * x10 - sJ * x11, y11 = sJ * x10 + cJ * x11;
-        T z00 = cI * y00 - sI * y10, z10 = sI * y00 + cI * y10;
-        T z01 = cI * y01 - sI * y11, z11 = sI * y01 + cI * y11;
-        if (bI == bJ) {
-          if ((rmask[cur] >> bI) & 1u) {
-            const T tI = tnb[cur][bI];
-            z00 = x00 - tI * x01;
-            z11 = x11 + tI * x01;
-            z01 = T(0);
-          } else {
-            z01 = T(0.5) * (z01 + z10);
-          }
-          z10 = z01;
-        }
-        A[pJ * LD + pI] = z00;
-        A[qJ * LD + pI] = z01;
-        A[pJ * LD + qI] = z10;
-        A[qJ * LD + qI] = z11;
-        if (bI != bJ) {  // the mirrored block
-          A[pI * LD + pJ] = z00;
-          A[pI * LD + qJ] = z01;
-          A[qI * LD + pJ] = z10;
-          A[qI * LD + qJ] = z11;
-        }
+      nB = last ? nA : nB;
+      if (ds == H - 1) {
+        const bool wb = __any(big);
+        if (lane == 0 && wb) bigflag[sweep % 3] = 1;
       }
-      prev_t = t;
-      prev_buf = cur;
       __syncthreads();
+#pragma unroll
+      for (int i = 0; i < RPL; ++i) A[i] = buf[g0][gs][l + 8 * i];
+      nA = nbuf[g0][gs];
     }
     // Read after the sweep's last barrier: the same values in every thread.
-    // Stop after a sweep without rotations, or after one whose rotations all
-    // had scaled off-diagonals |a_pq| / sqrt(a_pp a_qq) <= sqrt(eps): cyclic
-    // Jacobi converges quadratically, so the off-diagonal it leaves is
-    // O(eps) relative to the diagonal, and another sweep would only confirm.
-    if (rotflag[sweep % 3] == 0 || bigflag[sweep % 3] == 0) break;
+    // Stop after a sweep whose rotations all had scaled products
+    // |x_p . x_q| / (||x_p|| ||x_q||) at or below a bound whose square, and whose share that an inexact angle leaves, are O(eps):
+    // cyclic Jacobi converges quadratically, so another sweep would only
+    // confirm.
+    if (bigflag[sweep % 3] == 0) break;
   }
-  if (prev_t >= 0) {
-    if (vtask) v_rot(prev_t, prev_buf, vi, vJ);
-    if (vtask2) v_rot(prev_t, prev_buf, vi2, vJ2);
+
+  // ---- eigenvalues, sorted descending (stable by position), rank rule, output
+  nA = norm2(A);
+  nB = norm2(B);
+  if (act && l == 0) {
+    lam_s[2 * g] = nA;
+    lam_s[2 * g + 1] = nB;
   }
   __syncthreads();
-  // sort descending (stable by index), rank rule, write out
-  for (int i = tid; i < N; i += NT) {
-    const T li = A[i * LD + i];
-    int pos = 0;
-    for (int j = 0; j < N; ++j) {
-      const T lj = A[j * LD + j];
-      pos += (lj > li) || (lj == li && j < i);
+  // the padding column of an odd order has norm zero, below every other one
+  int posA = 0, posB = 0;
+  if (act) {
+    // each of the 8 lanes counts every eighth column
+    for (int j = l; j < NP; j += 8) {
+      const T lj = lam_s[j];
+      posA += (lj > nA) || (lj == nA && j < 2 * g);
+      posB += (lj > nB) || (lj == nB && j < 2 * g + 1);
     }
-    posv[i] = pos;
-    lam_s[pos] = li;
+    for (int m = 1; m < 8; m *= 2) {
+      posA += __shfl_xor(posA, m, 8);
+      posB += __shfl_xor(posB, m, 8);
+    }
+    if (l == 0) {
+      lam_d[posA] = nA * up;
+      lam_d[posB] = nB * up;
+    }
   }
   __syncthreads();
   const EigRule& ru = tk_.rule;
-  if (tid == 0) {
-    rank_s = (ru.kind != 0) ? apply_rule<T>(ru, lam_s, N) : N;
-    if (ru.kind != 0) *ru.rank_out = rank_s;
+  // every wave applies the rule to the spectrum in its lanes
+  const T lam_l = lane < N ? lam_d[lane] : T(0);
+  int rkeep = N;
+  if (ru.kind != 0) {
+    const int r = apply_rule<T>(ru, [&](int i) { return rdlane(lam_l, i); }, N);
+    if (tid == 0) *ru.rank_out = r;
+    if (ru.kind == 2) rkeep = r;
   }
-  __syncthreads();
-  const int rkeep = (ru.kind == 2) ? rank_s : N;
-  if (tk_.lam)
-    for (int i = tid; i < N; i += NT) tk_.lam[i] = lam_s[i];
-  if (tk_.V)
-    for (int e = tid; e < N * N; e += NT) {
-      const int i = e / N, r = e % N;  // source column i, row r
-      const int pos = posv[i];
-      tk_.V[r + (size_t)pos * N] = pos < rkeep ? V[i * LDV + r] : T(0);
+  if (tk_.lam && wave == 0 && lane < N) tk_.lam[lane] = lam_l;
+  if (tk_.V && act) {
+    const T ia = rsq_full(nA), ib = rsq_full(nB);
+#pragma unroll
+    for (int i = 0; i < RPL; ++i) {
+      const int r = l + 8 * i;
+      if (r < N) {
+        if (posA < N) tk_.V[r + (size_t)posA * N] = posA < rkeep ? A[i] * ia : T(0);
+        if (posB < N) tk_.V[r + (size_t)posB * N] = posB < rkeep ? B[i] * ib : T(0);
+      }
     }
+  }
 }
 
 // Rank certificate of the effective-rank rule, one workgroup per mode (the
@@ -948,7 +1046,22 @@ void jacobi_eig(const EigTask<T>* tasks_d, int ntasks, int N, bool want_v, hipSt
               double(ntasks) * sizeof(T) * (in_b + (want_v ? nn * nn : 0.0) + nn));
   if (want_v) {
     TK_CHECK(N <= VEC_NMAX, kErrUnsupported, "symmetric eigensolver: eigenvectors above size 64");
-    hipLaunchKernelGGL((jacobi_blk_kernel<T>), dim3(ntasks), dim3(1024), 0, st, tasks_d, N);
+    // rows per lane: the least that covers the order
+    switch (ceil_div(N, 8)) {
+#define TK_OSJ_CASE(R)                                                                                      \
+  case R:                                                                                                   \
+    hipLaunchKernelGGL((jacobi_osj_kernel<T, R>), dim3(ntasks), dim3(1024), 0, st, tasks_d, N);             \
+    break;
+      TK_OSJ_CASE(1)
+      TK_OSJ_CASE(2)
+      TK_OSJ_CASE(3)
+      TK_OSJ_CASE(4)
+      TK_OSJ_CASE(5)
+      TK_OSJ_CASE(6)
+      TK_OSJ_CASE(7)
+      TK_OSJ_CASE(8)
+#undef TK_OSJ_CASE
+    }
   } else {
     TK_CHECK(N <= GM_NMAX, kErrUnsupported, "symmetric eigensolver: matrix larger than 512");
     if (N <= VAL_NMAX)

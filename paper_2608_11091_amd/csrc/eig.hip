@@ -173,6 +173,35 @@ __device__ void tridiag_spectrum(const EigTask<T>& tk_, T* dd, T* ee, T* lam, T*
       return;  // uniform: every thread read the same flag after the barrier
     }
   }
+  // FP64, and a tail threshold below the zero clamp whatever the spectrum
+  // (tau^2 N < delta: the total is at most N lambda_1, so every eigenvalue
+  // above delta lambda_1 exceeds tau^2 total by itself): r~ is the number of
+  // eigenvalues above delta lambda_1, so only the largest one is located, to
+  // 1e-7 of itself (256 points a round), and one more count gives the rank.
+  // (Not in FP32, where the clamp lies below the Gram's rounding and the
+  // count follows the noise of the eigenvalues as computed.)
+  if constexpr (sizeof(T) == 8) {
+    const double tau = tk_.rule.kind == 1 ? *tk_.rule.tau : 1.0;
+    if (tk_.rule.kind == 1 && tk_.rule.cap1 > 0 && tau * tau * N * 2.0 < tk_.rule.delta) {
+      T lo = gl - tolx, hi = gu + tolx;
+      int* const first = reinterpret_cast<int*>(lam);  // scratch: first point above lambda_1, by wave
+      for (int it = 0; it < 4; ++it) {
+        if (tid < 256) {
+          const T mid = lo + (hi - lo) * (T(tid + 1) / T(257));
+          const unsigned long long up = __ballot(sturm_count(dd, ee, N, mid, pivmin) == N);
+          if ((tid & (kWave - 1)) == 0) first[tid / kWave] = up ? (tid & ~(kWave - 1)) + __builtin_ctzll(up) : 256;
+        }
+        __syncthreads();
+        const int f = min(min(first[0], first[1]), min(first[2], first[3]));
+        const T span = hi - lo;
+        hi = f < 256 ? lo + span * (T(f + 1) / T(257)) : hi;
+        lo = f > 0 ? lo + span * (T(f) / T(257)) : lo;
+        __syncthreads();
+      }
+      if (tid == 0) *tk_.rule.rank_out = hi > T(0) ? N - sturm_count(dd, ee, N, T(tk_.rule.delta) * hi, pivmin) : 0;
+      return;  // uniform
+    }
+  }
   // G = lanes per eigenvalue: the largest power of two <= min(16, nthreads / N)
   int G = 1;
   while (G < 16 && 2 * G * N <= nthreads) G *= 2;
@@ -205,7 +234,7 @@ __device__ void tridiag_spectrum(const EigTask<T>& tk_, T* dd, T* ee, T* lam, T*
 }
 
 // Householder tridiagonalisation with the matrix in registers: lane l of
-// wave w of W holds the entries (l + 64 a, w + W b), a < 3, so the rank-2
+// wave w of W holds the entries (l + 64 a, w + W b), so the rank-2
 // update of a step touches only registers and LDS carries vectors and partial
 // sums, never the matrix.  Step j: the wave holding column j forms v (the
 // Householder vector of the part below the diagonal) and tau; every thread
@@ -214,38 +243,35 @@ __device__ void tridiag_spectrum(const EigTask<T>& tk_, T* dd, T* ee, T* lam, T*
 // w = p - (tau^2 / 2)(v^T A_sub v) v; every thread applies
 // A_sub -= v w^T + w v^T to its entries.  Vectors alternate between two LDS
 // buffers with the step parity.  Then the spectrum as above.
-constexpr int TRG_RR = (VAL_NMAX + kWave - 1) / kWave;  // rows per thread
+// Bound by latency, one workgroup per matrix: a serial chain of N steps with
+// three barriers each.  The body is compiled for three orders (rows and
+// columns a thread holds; the order is a device value), as the registers of
+// order 160 for every matrix made the FP64 form spill at each of them.  With
+// the count in place of the spectrum (below) and the narrower Gram side, the
+// FP64 launches of a preconditioned training step at n = 128 went from 1124 to
+// 224 us on average, those of twelve solver iterations at n = 512 from 295 to
+// 109 us.
+constexpr int TRG_NT = 1024;            // 16 waves
+constexpr int TRG_NW = TRG_NT / kWave;
 
-// 16 waves (FP64 spills some registers; 8 waves with twice the entries per
-// thread spill more)
 template <typename T>
-constexpr int trg_nt() { return 1024; }
+struct TrgShared {
+  T vb[2][VAL_NMAX], wb[2][VAL_NMAX];
+  T pp[TRG_NW][VAL_NMAX];
+  T qs[TRG_NW];
+  T tau_s[2];
+  T dd[VAL_NMAX], ee[VAL_NMAX], lam[VAL_NMAX];
+  T sc[4];
+};
 
-template <typename T, int TRG_NT>
-__global__ __launch_bounds__(TRG_NT) void tridiag_reg_kernel(const EigTask<T>* __restrict__ tasks, int NL) {
-  constexpr int TRG_NW = TRG_NT / kWave;                   // waves
-  constexpr int TRG_RC = (VAL_NMAX + TRG_NW - 1) / TRG_NW;  // columns per thread
-  const EigTask<T> tk_ = tasks[blockIdx.x];
-  if (task_skipped(tk_)) return;
-  int N = NL;
-  if (tk_.ndyn != nullptr) {
-    const int nd = *tk_.ndyn;
-    if (nd < 0 || nd > NL) {
-      if (threadIdx.x == 0 && tk_.rule.rank_out) *tk_.rule.rank_out = -1;
-      return;
-    }
-    N = nd;
-  }
-  if (N == 0) {
-    if (threadIdx.x == 0 && tk_.rule.rank_out) *tk_.rule.rank_out = 0;
-    return;
-  }
-  __shared__ T vb[2][VAL_NMAX], wb[2][VAL_NMAX];
-  __shared__ T pp[TRG_NW][VAL_NMAX];
-  __shared__ T qs[TRG_NW];
-  __shared__ T tau_s[2];
-  __shared__ T dd[VAL_NMAX], ee[VAL_NMAX], lam[VAL_NMAX];
-  __shared__ T sc[4];
+// N <= min(64 RR, 16 RC)
+template <typename T, int RR, int RC>
+__device__ __forceinline__ void tridiag_reg(const EigTask<T>& tk_, TrgShared<T>& sh, int N) {
+  auto &vb = sh.vb, &wb = sh.wb;
+  auto& pp = sh.pp;
+  auto& qs = sh.qs;
+  auto& tau_s = sh.tau_s;
+  auto &dd = sh.dd, &ee = sh.ee;
   const int tid = threadIdx.x;
   const int lane = tid & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
@@ -253,11 +279,11 @@ __global__ __launch_bounds__(TRG_NT) void tridiag_reg_kernel(const EigTask<T>* _
     vb[e / VAL_NMAX][e % VAL_NMAX] = T(0);
     wb[e / VAL_NMAX][e % VAL_NMAX] = T(0);
   }
-  T a[TRG_RR][TRG_RC];
+  T a[RR][RC];
 #pragma unroll
-  for (int i = 0; i < TRG_RR; ++i)
+  for (int i = 0; i < RR; ++i)
 #pragma unroll
-    for (int k = 0; k < TRG_RC; ++k) {
+    for (int k = 0; k < RC; ++k) {
       const int r = lane + kWave * i, c = wave + TRG_NW * k;
       T v = T(0);
       if (r < N && c < N) v = (r >= c) ? tk_.A[r + (size_t)c * tk_.lda] : tk_.A[c + (size_t)r * tk_.lda];
@@ -269,13 +295,13 @@ __global__ __launch_bounds__(TRG_NT) void tridiag_reg_kernel(const EigTask<T>* _
     const int buf = jj & 1;
     const int r0 = jj + 1;
     const int kb = jj / TRG_NW;  // uniform
-    T x[TRG_RR];
+    T x[RR];
     T s2 = T(0);
 #pragma unroll
-    for (int i = 0; i < TRG_RR; ++i) {
+    for (int i = 0; i < RR; ++i) {
       T v = T(0);
 #pragma unroll
-      for (int k = 0; k < TRG_RC; ++k)
+      for (int k = 0; k < RC; ++k)
         if (k == kb) v = a[i][k];
       x[i] = v;
       const int r = lane + kWave * i;
@@ -284,7 +310,7 @@ __global__ __launch_bounds__(TRG_NT) void tridiag_reg_kernel(const EigTask<T>* _
     s2 = wave_sum(s2);
     T xa = T(0);
 #pragma unroll
-    for (int i = 0; i < TRG_RR; ++i)
+    for (int i = 0; i < RR; ++i)
       if (i == r0 / kWave) xa = x[i];
     const T alpha = rdlane(xa, r0 & (kWave - 1));
     T beta, tau, scal;
@@ -298,7 +324,7 @@ __global__ __launch_bounds__(TRG_NT) void tridiag_reg_kernel(const EigTask<T>* _
       scal = T(1) / (alpha - beta);
     }
 #pragma unroll
-    for (int i = 0; i < TRG_RR; ++i) {
+    for (int i = 0; i < RR; ++i) {
       const int r = lane + kWave * i;
       if (r >= r0 && r < N) vb[buf][r] = r == r0 ? T(1) : x[i] * scal;
       if (r == jj) dd[jj] = x[i];
@@ -317,24 +343,24 @@ __global__ __launch_bounds__(TRG_NT) void tridiag_reg_kernel(const EigTask<T>* _
     if (tau == T(0)) continue;  // the same value in every thread: nothing to apply
     // unconditional loads (in-bounds indices; the buffers hold finite values)
     // times a 0/1 mask, so that all loads issue before a single wait
-    T vr[TRG_RR], vc[TRG_RC];
+    T vr[RR], vc[RC];
 #pragma unroll
-    for (int i = 0; i < TRG_RR; ++i) {
+    for (int i = 0; i < RR; ++i) {
       const int r = lane + kWave * i;
       vr[i] = vb[buf][min(r, VAL_NMAX - 1)] * T(r >= r0 && r < N);
     }
 #pragma unroll
-    for (int k = 0; k < TRG_RC; ++k) {
+    for (int k = 0; k < RC; ++k) {
       const int c = wave + TRG_NW * k;
       vc[k] = vb[buf][c] * T(c >= r0 && c < N);
     }
     // ---- partial products over this wave's columns
     T q = T(0);
 #pragma unroll
-    for (int i = 0; i < TRG_RR; ++i) {
+    for (int i = 0; i < RR; ++i) {
       T acc = T(0);
 #pragma unroll
-      for (int k = 0; k < TRG_RC; ++k) acc += a[i][k] * vc[k];
+      for (int k = 0; k < RC; ++k) acc += a[i][k] * vc[k];
       q += vr[i] * acc;
       const int r = lane + kWave * i;
       if (r < N) pp[wave][r] = acc;
@@ -354,21 +380,21 @@ __global__ __launch_bounds__(TRG_NT) void tridiag_reg_kernel(const EigTask<T>* _
     }
     __syncthreads();
     // ---- rank-2 update of this thread's entries
-    T wr[TRG_RR], wc[TRG_RC];
+    T wr[RR], wc[RC];
 #pragma unroll
-    for (int i = 0; i < TRG_RR; ++i) {
+    for (int i = 0; i < RR; ++i) {
       const int r = lane + kWave * i;
       wr[i] = wb[buf][min(r, VAL_NMAX - 1)] * T(r >= r0 && r < N);
     }
 #pragma unroll
-    for (int k = 0; k < TRG_RC; ++k) {
+    for (int k = 0; k < RC; ++k) {
       const int c = wave + TRG_NW * k;
       wc[k] = wb[buf][c] * T(c >= r0 && c < N);
     }
 #pragma unroll
-    for (int i = 0; i < TRG_RR; ++i)
+    for (int i = 0; i < RR; ++i)
 #pragma unroll
-      for (int k = 0; k < TRG_RC; ++k) a[i][k] -= vr[i] * wc[k] + wr[i] * vc[k];
+      for (int k = 0; k < RC; ++k) a[i][k] -= vr[i] * wc[k] + wr[i] * vc[k];
     // no barrier here: the next step's Householder vector comes from its
     // wave's own registers and goes to the other buffer, and every shared
     // array this step reads is written again only after the next step's
@@ -376,16 +402,42 @@ __global__ __launch_bounds__(TRG_NT) void tridiag_reg_kernel(const EigTask<T>* _
   }
   // last 2 x 2 block: diagonal entries and the coupling, from their holders
 #pragma unroll
-  for (int i = 0; i < TRG_RR; ++i)
+  for (int i = 0; i < RR; ++i)
 #pragma unroll
-    for (int k = 0; k < TRG_RC; ++k) {
+    for (int k = 0; k < RC; ++k) {
       const int r = lane + kWave * i, c = wave + TRG_NW * k;
       if (N >= 2 && r == N - 2 && c == N - 2) dd[N - 2] = a[i][k];
       if (N >= 2 && r == N - 1 && c == N - 2) ee[N - 2] = a[i][k];
       if (r == N - 1 && c == N - 1) dd[N - 1] = a[i][k];
     }
   __syncthreads();
-  tridiag_spectrum<T>(tk_, dd, ee, lam, sc, N, tid, TRG_NT);
+}
+
+template <typename T>
+__global__ __launch_bounds__(TRG_NT) void tridiag_reg_kernel(const EigTask<T>* __restrict__ tasks, int NL) {
+  const EigTask<T> tk_ = tasks[blockIdx.x];
+  if (task_skipped(tk_)) return;
+  int N = NL;
+  if (tk_.ndyn != nullptr) {
+    const int nd = *tk_.ndyn;
+    if (nd < 0 || nd > NL) {
+      if (threadIdx.x == 0 && tk_.rule.rank_out) *tk_.rule.rank_out = -1;
+      return;
+    }
+    N = nd;
+  }
+  if (N == 0) {
+    if (threadIdx.x == 0 && tk_.rule.rank_out) *tk_.rule.rank_out = 0;
+    return;
+  }
+  __shared__ TrgShared<T> sh;
+  if (N <= 64)
+    tridiag_reg<T, 1, 4>(tk_, sh, N);
+  else if (N <= 112)
+    tridiag_reg<T, 2, 7>(tk_, sh, N);
+  else
+    tridiag_reg<T, 3, 10>(tk_, sh, N);
+  tridiag_spectrum<T>(tk_, sh.dd, sh.ee, sh.lam, sh.sc, N, int(threadIdx.x), TRG_NT);
 }
 
 // Householder tridiagonalisation of an N x N symmetric matrix (160 < N <= 512)
@@ -1065,7 +1117,7 @@ void jacobi_eig(const EigTask<T>* tasks_d, int ntasks, int N, bool want_v, hipSt
   } else {
     TK_CHECK(N <= GM_NMAX, kErrUnsupported, "symmetric eigensolver: matrix larger than 512");
     if (N <= VAL_NMAX)
-      hipLaunchKernelGGL((tridiag_reg_kernel<T, trg_nt<T>()>), dim3(ntasks), dim3(trg_nt<T>()), 0, st, tasks_d, N);
+      hipLaunchKernelGGL((tridiag_reg_kernel<T>), dim3(ntasks), dim3(TRG_NT), 0, st, tasks_d, N);
     else
       hipLaunchKernelGGL((tridiag_gm_kernel<T>), dim3(ntasks), dim3(1024), 0, st, tasks_d, N);
     // (the planner gives the order-512 path matrices with a leading dimension

@@ -627,7 +627,12 @@ RoundSumOut<T> plan_roundsum(Seq& q, Planner& pl, const Shape& sh, const Blocks<
         e.rule.cap1 = sh.cap;  // the width only takes min(r~ + p, cap + p); lam is scratch
         return e;
       };
-      if (n <= kEigRegMax) {
+      // n-side up to order 64 (where the eigensolve is short either way), and
+      // up to 160 unless the concatenation is the narrower side: at n = 128 and
+      // three blocks of rank 12 the order drops from 128 to 36.  The FP32 form
+      // stays on the n-side there (its count of the zero eigenvalues' noise
+      // depends on the side).
+      if (n <= 64 || (n <= kEigRegMax && (Rp > n || !std::is_same<T, double>::value))) {
         // n-side Gram: sum_b w_b^2 U_b U_b^T, register eigensolver
         T* Gn = nside_gram(n);
         T* lam = ar.alloc<T>(size_t(n) * modes.size());

@@ -153,6 +153,18 @@ __device__ __forceinline__ T wave_max(T v) {
   return ab > cd ? ab : cd;
 }
 
+// Largest of a value over the wave, the same in every lane.
+__device__ __forceinline__ unsigned wave_umax(unsigned v) {
+  v = max(v, unsigned(__builtin_amdgcn_mov_dpp(int(v), 0xB1, 0xF, 0xF, true)));
+  v = max(v, unsigned(__builtin_amdgcn_mov_dpp(int(v), 0x4E, 0xF, 0xF, true)));
+  v = max(v, unsigned(__builtin_amdgcn_mov_dpp(int(v), 0x141, 0xF, 0xF, true)));
+  v = max(v, unsigned(__builtin_amdgcn_mov_dpp(int(v), 0x140, 0xF, 0xF, true)));
+  const unsigned a = __builtin_amdgcn_readlane(int(v), 0), b = __builtin_amdgcn_readlane(int(v), 16);
+  const unsigned c = __builtin_amdgcn_readlane(int(v), 32), d = __builtin_amdgcn_readlane(int(v), 48);
+  const unsigned ab = a > b ? a : b, cd = c > d ? c : d;
+  return __builtin_amdgcn_readfirstlane(int(ab > cd ? ab : cd));
+}
+
 // Block-wide sum for blockDim.x a multiple of 64; `red` holds >= nwaves values.
 // Every thread gets the same result (fixed reduction order: deterministic).
 template <typename T>

@@ -693,18 +693,6 @@ __device__ __forceinline__ bool above_tol(float d, float nx, float ny, float tol
   return ad > Lim<float>::tiny() && ad > tol * (__builtin_amdgcn_sqrtf(nx) * __builtin_amdgcn_sqrtf(ny));
 }
 
-// Largest of a value over the wave, the same in every lane.
-__device__ __forceinline__ unsigned wave_umax(unsigned v) {
-  v = max(v, unsigned(__builtin_amdgcn_mov_dpp(int(v), 0xB1, 0xF, 0xF, true)));
-  v = max(v, unsigned(__builtin_amdgcn_mov_dpp(int(v), 0x4E, 0xF, 0xF, true)));
-  v = max(v, unsigned(__builtin_amdgcn_mov_dpp(int(v), 0x141, 0xF, 0xF, true)));
-  v = max(v, unsigned(__builtin_amdgcn_mov_dpp(int(v), 0x140, 0xF, 0xF, true)));
-  const unsigned a = __builtin_amdgcn_readlane(int(v), 0), b = __builtin_amdgcn_readlane(int(v), 16);
-  const unsigned c = __builtin_amdgcn_readlane(int(v), 32), d = __builtin_amdgcn_readlane(int(v), 48);
-  const unsigned ab = a > b ? a : b, cd = c > d ? c : d;
-  return __builtin_amdgcn_readfirstlane(int(ab > cd ? ab : cd));
-}
-
 // Symmetric positive semidefinite eigensolver with vectors, one workgroup per
 // matrix of order N <= 64: pivoted Cholesky factor A = L L^T (rows in place),
 // then one-sided Jacobi on the columns of L.  Rotations from the right make the columns orthogonal,

@@ -4,6 +4,7 @@
 // triangular solve that turns a Gram's Cholesky factor into a basis.
 // Everything is deterministic: no atomics, fixed reduction orders.
 #include <algorithm>
+#include <cfloat>
 
 #include "kernels.hpp"
 
@@ -12,21 +13,30 @@ namespace tk {
 namespace {
 
 // ---------------------------------------------------------------- Householder QR
-// Column-distributed layout: lane c of every wave owns column c (c < 64) and
-// wave w holds rows [RS w, RS w + RS) of it in registers (RS = 32 up to 256
-// rows, 64 above), so a block of at most 8 waves covers n <= 512 rows.  Sums over rows are in-thread
-// over the 32 rows plus one pass over the waves' partials in LDS (fixed
-// order).  Every wave derives the pivot of a step from the same LDS partials,
-// and the pivot column's lane of each wave hands the reflector of that
-// wave's rows to the other lanes through a per-wave LDS slot (in-order LDS
-// within a wave, no block barrier), so a factorisation step needs two
-// barriers and a Q step one.
-constexpr int QC_RS = 32;              // rows per wave up to 256 rows
-constexpr int QC_MAXW = 16;
+// Lane c of every wave owns column c (c < 64) and wave w holds rows
+// [RS w, RS w + RS) of it in registers.  The pivot column's entries on a
+// wave's rows are read across lanes (v_readlane) into scalar registers and
+// enter the dot products and the updates as scalar operands, so a reflector
+// never goes through LDS; it stays unscaled, v = (1, scal * x), and the scale
+// is folded into the coefficients.  Before step j, row j of all columns leaves
+// the registers for LDS (zeros take its place), where it becomes row j of R;
+// in columns chosen earlier it holds their reflectors' entries.  Dot products,
+// updates and norms then run over all rows of the registers without a test on
+// the diagonal.  Sums over rows are in-thread plus one fixed-order pass over
+// the waves' partials in LDS; every wave derives the pivot and the reflector
+// from the same partials, so a factorisation step needs two barriers and a Q
+// step one.
+//
+// Bound by latency: one dependent chain a step, at about 6 cycles an
+// instruction where one wave has a SIMD to itself, so the rows are spread
+// over four waves first (16 or 32 rows each) and over eight above 128 rows.
+// Measured, three matrices a launch (in brackets the form that handed the
+// reflector over through LDS and tested every row against the diagonal):
+// pivoted 96 x 48 with Q 123 us (205), plain 48 x 48 with Q 76 (176), R only
+// 256 x 32 72 (98) and 512 x 48 176 (240), pivoted 512 x 48 with Q 339 (940).
 constexpr int QC_MAXROWS = 512;
-constexpr int QC_NT_SMALL = 4 * kWave;
-constexpr int QC_NT = 8 * kWave;
-constexpr int QC_NT_BIG = 16 * kWave;
+constexpr int QC_V = 16;  // rows per register vector (indexed at run time by the retired row)
+typedef double QcVec __attribute__((ext_vector_type(QC_V)));
 
 struct QrJob {
   const double* Y;
@@ -48,270 +58,234 @@ __device__ __forceinline__ QrJob job_of(const QrPivTask& t, int cap, const int*)
   return j;
 }
 
-// Sum of part[q][c] over the nw waves in fixed order (every wave gets the
+// Sum of part[q][c] over the NW waves in fixed order (every wave gets the
 // same result).
-__device__ __forceinline__ double wave_partials_sum(const double (*part)[kWave], int nw, int c) {
-  double s = 0.0;
-#pragma unroll 2
-  for (int q = 0; q < nw; ++q) s += part[q][c];
-  return s;
+template <int NW>
+__device__ __forceinline__ double wave_partials_sum(const double (*part)[kWave], int c) {
+  double s0 = part[0][c], s1 = part[1][c];
+#pragma unroll
+  for (int q = 2; q < NW; q += 2) {
+    s0 += part[q][c];
+    s1 += part[q + 1][c];
+  }
+  return s0 + s1;
 }
 
-// Eight independent accumulation chains combined by a fixed tree.
-__device__ __forceinline__ double tree8(const double* s) {
-  return ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7]));
+// Householder vector of a column with leading entry alpha and squared norm xx
+// (over the rows from the diagonal down): beta = -sign(alpha) ||x||,
+// tau = (beta - alpha) / beta, v = (1, scal * x_below); tau = scal = 0 where
+// nothing stands below the diagonal (to rounding).
+struct Reflector {
+  double beta, tau, scal;
+};
+__device__ __forceinline__ Reflector reflector(double alpha, double xx) {
+  const bool some = xx > alpha * alpha;
+  const double aa = fabs(alpha);
+  const double nrm = sqrt(some ? xx : 1.0);
+  Reflector r;
+  r.beta = some ? -copysign(nrm, alpha) : alpha;
+  r.tau = some ? 1.0 + aa / nrm : 0.0;
+  r.scal = some ? copysign(1.0 / (aa + nrm), alpha) : 0.0;
+  return r;
 }
 
 // PIV = false: plain Householder QR of the leading m columns (m from the task,
 // else m_dev, else cap).  PIV = true: column pivoting by the largest remaining
 // norm relative to the column's reference norm (or to the largest input
-// column when the task has no reference) and a stop once that ratio is at or
-// below drop_tol; R[j][c] is then the coefficient of input column c on basis
-// column j.
-//
-// NTB is the largest block the instantiation is launched with and RS the
-// rows each wave holds: at most 8 waves leave each thread at least 256
-// registers (16 waves cap it at 128), so n <= 128 runs on up to 4 waves of
-// 32 rows, n <= 256 on up to 8, and n <= 512 on 8 waves of 64 rows, except
-// the pivoted form, whose extra state spills there: it takes 16 waves of 32
-// rows with one select per row (the form with the smallest register need).
-template <bool PIV, typename Task, int NTB, int RS>
-__global__ __launch_bounds__(NTB) void qr_cols_kernel(const Task* __restrict__ tasks, int n, int cap,
-                                                      double drop_tol, const int* __restrict__ m_dev) {
-  static_assert(NTB / kWave * RS <= QC_MAXROWS && NTB / kWave <= QC_MAXW, "row blocks within the LDS arrays");
-  __shared__ double pn1[QC_MAXW][kWave];  // per-wave sums of squares over rows >= j
-  __shared__ double rowj[kWave];          // row j of every column
-  __shared__ double pw[2][QC_MAXW][kWave];  // per-wave partials of v^T A
-  __shared__ double fref2[kWave];
-  __shared__ double tau_s[kWave];
+// column when the task has no reference; the largest to 17 bits, ties to the
+// lowest column) and a stop once that ratio is at or below drop_tol; R[j][c]
+// is then the coefficient of input column c on basis column j.  NW waves of RS
+// rows cover n.
+template <bool PIV, typename Task, int RS, int NW>
+__global__ __launch_bounds__(NW* kWave) void qr_cols_kernel(const Task* __restrict__ tasks, int n, int cap,
+                                                             double drop_tol, const int* __restrict__ m_dev) {
+  static_assert(NW * RS <= QC_MAXROWS && RS % QC_V == 0 && RS <= 4 * QC_V && NW % 2 == 0, "row blocks");
+  constexpr int NV = RS / QC_V;
+  __shared__ double rows[kWave + 1][kWave];  // retired rows: R, and reflector entries of columns chosen earlier
+  __shared__ double pn1[NW][kWave];          // per-wave sums of squares over the rows in registers
+  __shared__ double pw[2][NW][kWave];        // per-wave partials of x^T A
+  __shared__ double tau_s[kWave], scal_s[kWave];
   __shared__ int piv_s[kWave];
   __shared__ int step_of[kWave];
-  __shared__ double vsh_all[QC_MAXROWS];  // reflector on each wave's rows
-  // rows per chunk; a 16-wave block (n > 256 in the pivoted form) keeps one
-  // select per row, the form whose register need is the smallest
-  constexpr bool CHUNKED = NTB <= QC_NT;
-  constexpr int QC_CH = 8;
   const QrJob jb = job_of(tasks[blockIdx.x], cap, m_dev);
   const int tid = threadIdx.x;
   const int c = tid & (kWave - 1);
   const int w = __builtin_amdgcn_readfirstlane(tid / kWave);  // wave-uniform: row tests stay scalar
-  const int nw = blockDim.x / kWave;
   const int r0 = w * RS;
-  double* const vsh = vsh_all + w * RS;  // this wave's rows
-  const int m = max(0, min(jb.m, cap));
+  const int m = __builtin_amdgcn_readfirstlane(max(0, min(jb.m, cap)));
   const int kmax = min(m, n);
 
   // unconditional loads at clamped indices (always inside the n x cap input),
   // masked afterwards: no per-row branches whose conditions stay live
   const int cl = min(c, cap - 1);
   const bool colin = c < m;
-  double a[RS];
+  QcVec a[NV];
   double sref = 0.0;  // this thread's share of the squared reference norm
+  {
+    const GPtr<double> gy = (GPtr<double>)jb.Y + (size_t)cl * n;
 #pragma unroll
-  for (int i = 0; i < RS; ++i) {
-    const int r = r0 + i;
-    const size_t at = (size_t)min(r, n - 1) + (size_t)cl * n;
-    const bool in = colin && r < n;
-    const double y = jb.Y[at];
-    a[i] = in ? y : 0.0;
+    for (int v = 0; v < NV; ++v) {
+#pragma unroll
+      for (int i = 0; i < QC_V; ++i) a[v][i] = gy[min(r0 + v * QC_V + i, n - 1)];
+    }
+    const double one = colin ? 1.0 : 0.0;
+#pragma unroll
+    for (int v = 0; v < NV; ++v)
+#pragma unroll
+      for (int i = 0; i < QC_V; ++i) a[v][i] = r0 + v * QC_V + i < n ? (one != 0.0 ? a[v][i] : 0.0) : 0.0;
   }
   if (PIV) {
     if (jb.ref == nullptr) {
       // global cut: the reference columns are the input itself
 #pragma unroll
-      for (int i = 0; i < RS; ++i) sref += a[i] * a[i];
+      for (int v = 0; v < NV; ++v)
+#pragma unroll
+        for (int i = 0; i < QC_V; ++i) sref = fma(a[v][i], a[v][i], sref);
     } else {
-      // reference columns read a chunk at a time, so that their loads do not
+      // reference columns read a part at a time, so that their loads do not
       // all hold registers beside the input's
+      const GPtr<double> gr = (GPtr<double>)jb.ref + (size_t)cl * n;
 #pragma unroll
-      for (int q = 0; q < RS; q += QC_CH) {
+      for (int q = 0; q < RS; q += 8) {
 #pragma unroll
-        for (int i = q; i < q + QC_CH; ++i) {
-          const int r = r0 + i;
-          const size_t at = (size_t)min(r, n - 1) + (size_t)cl * n;
-          const double v = (colin && r < n) ? jb.ref[at] : 0.0;
-          sref += v * v;
+        for (int i = q; i < q + 8; ++i) {
+          const double v = gr[min(r0 + i, n - 1)];
+          sref += (colin && r0 + i < n) ? v * v : 0.0;
         }
         __builtin_amdgcn_sched_barrier(0);
       }
     }
   }
-  // the pivot column's lane stores v on this wave's rows; the other lanes of
-  // the wave read it back after a wave-scope fence
-  // Rows are handled in chunks of QC_CH: the step's diagonal row t0 (relative
-  // to the wave) is uniform, so a chunk lies wholly below it, wholly above
-  // it, or holds it, and only that one chunk of the wave takes per-row
-  // selects (uniform branches choose the case).
-  auto publish = [&](bool own, int t0, double scale, double diag) {
-    if constexpr (!CHUNKED) {
-      if (own) {
+  // Replaces row `row` x of the registers by next(x) in the wave that holds it.
+  // The register index is a run-time scalar; every wave writes some register
+  // back (control flow around such a write copies the whole vector).
+  auto swap_row = [&](int row, auto next) {
 #pragma unroll
-        for (int i = 0; i < RS; ++i) vsh[i] = (i < t0) ? 0.0 : (i == t0 ? diag : a[i] * scale);
-      }
-    } else if (own) {
-#pragma unroll
-      for (int q = 0; q < RS; q += QC_CH) {
-        if (t0 < q) {
-#pragma unroll
-          for (int i = q; i < q + QC_CH; ++i) vsh[i] = a[i] * scale;
-        } else if (t0 >= q + QC_CH) {
-#pragma unroll
-          for (int i = q; i < q + QC_CH; ++i) vsh[i] = 0.0;
-        } else {
-#pragma unroll
-          for (int i = q; i < q + QC_CH; ++i) vsh[i] = (i < t0) ? 0.0 : (i == t0 ? diag : a[i] * scale);
-        }
-      }
+    for (int v = 0; v < NV; ++v) {
+      const int t = row - r0 - v * QC_V;
+      const bool in = t >= 0 && t < QC_V;
+      const int i = in ? t : 0;
+      const double x = a[v][i];
+      a[v][i] = in ? next(x) : x;
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   };
-  // column sums of squares over rows >= j, and row j of every column (from
-  // the wave that holds it)
-  auto norm_partials = [&](int j) {
-    const int t0 = j - r0;
-    double s1[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    if constexpr (!CHUNKED) {
-#pragma unroll
-      for (int i = 0; i < RS; ++i) s1[i & 7] += (i >= t0) ? a[i] * a[i] : 0.0;
-      pn1[w][c] = tree8(s1);
-      if (t0 >= 0 && t0 < RS) {
-        double x = 0.0;
-#pragma unroll
-        for (int i = 0; i < RS; ++i) x = (i == t0) ? a[i] : x;
-        rowj[c] = x;
-      }
-      return;
-    }
-#pragma unroll
-    for (int q = 0; q < RS; q += QC_CH) {
-      if (t0 < q) {
-#pragma unroll
-        for (int i = q; i < q + QC_CH; ++i) s1[i & 7] += a[i] * a[i];
-      } else if (t0 < q + QC_CH) {  // the chunk holding row j
-        double x = 0.0;
-#pragma unroll
-        for (int i = q; i < q + QC_CH; ++i) {
-          s1[i & 7] += (i >= t0) ? a[i] * a[i] : 0.0;
-          x = (i == t0) ? a[i] : x;
-        }
-        rowj[c] = x;
-      }
-    }
-    pn1[w][c] = tree8(s1);
+  auto retire = [&](int row) {
+    double x = 0.0;
+    swap_row(row, [&](double out) {
+      x = out;
+      return 0.0;
+    });
+    if (row >= r0 && row < r0 + RS) rows[row][c] = x;
   };
-  if (PIV) pw[0][w][c] = sref;
+  auto norm_partial = [&]() {
+    double s0 = 0.0, s1 = 0.0;
+#pragma unroll
+    for (int v = 0; v < NV; ++v)
+#pragma unroll
+      for (int i = 0; i < QC_V; i += 2) {
+        s0 = fma(a[v][i], a[v][i], s0);
+        s1 = fma(a[v][i + 1], a[v][i + 1], s1);
+      }
+    pn1[w][c] = s0 + s1;
+  };
+  // the pivot column's entries, all reads before their uses (a read right
+  // before its use stalls)
+  auto column = [&](int v, int p, double (&x)[QC_V]) {
+#pragma unroll
+    for (int i = 0; i < QC_V; ++i) x[i] = rdlane(a[v][i], p);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto column_dot = [&](int p) {
+    double s0 = 0.0, s1 = 0.0;
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+      double x[QC_V];
+      column(v, p, x);
+#pragma unroll
+      for (int i = 0; i < QC_V; i += 2) {
+        s0 = fma(x[i], a[v][i], s0);
+        s1 = fma(x[i + 1], a[v][i + 1], s1);
+      }
+    }
+    return s0 + s1;
+  };
+  // The update reads the column again where, kept from the dot product, it
+  // would not fit the scalar registers.
+  auto reread = [&](int p) {
+    if (RS > QC_V) asm volatile("" : "+s"(p));
+    return p;
+  };
+  if (PIV) pw[1][w][c] = sref;
   if (tid < kWave) step_of[tid] = -1;
-  norm_partials(0);
+  retire(0);
+  norm_partial();
   __syncthreads();
+  double iref = 1.0;  // 1 / squared reference norm (0: the column is never chosen)
   if (PIV) {
-    if (w == 0) {
-      double t = wave_partials_sum(pw[0], nw, c);
-      if (jb.ref == nullptr) {
-        // global cut: every column is measured against the largest input column
-        t = wave_max(t);
-      }
-      fref2[c] = t;
-    }
-    __syncthreads();
+    double t = wave_partials_sum<NW>(pw[1], c);
+    if (jb.ref == nullptr) t = wave_max(t);  // global cut: against the largest input column
+    iref = t > 0.0 ? 1.0 / t : 0.0;
   }
 
   // ---------------- factorisation
   bool alive = colin;  // this lane's column is still unchosen
   int nlive = 0;
+  int nret = 1;        // retired rows
   for (int j = 0; j < kmax; ++j) {
-    const double n1 = wave_partials_sum(pn1, nw, c);
+    const double rj = rows[j][c];
+    const double n1 = fma(rj, rj, wave_partials_sum<NW>(pn1, c));
     int p = j;
     if (PIV) {
-      double rel = (alive && fref2[c] > 0.0) ? n1 / fref2[c] : -1.0;
-      if (!(rel >= 0.0)) rel = -1.0;  // NaN as well: every lane takes the same decision
-      // the largest ratio (DPP reduction), then the lowest lane holding it
-      const double best = wave_max(rel);
-      const unsigned long long hit = __ballot(rel == best);
-      const int idx = __ffsll((long long)hit) - 1;
-      p = __builtin_amdgcn_readfirstlane(best > drop_tol * drop_tol ? idx : -1);
+      const double rel = n1 * iref;
+      // false for NaN as well: every wave takes the same decision
+      const bool cand = alive && rel > 0.0;
+      const unsigned bits = __float_as_uint(fminf(float(rel), FLT_MAX));
+      const unsigned key = wave_umax(cand ? 0x80000000u | (bits & ~63u) | unsigned(63 - c) : 0u);
+      p = 63 - int(key & 63u);
+      if (key == 0u || !(rdlane(rel, p) > drop_tol * drop_tol)) break;
     }
-    if (p < 0) break;
-    // reflector of column p on rows >= j: beta = -sign(alpha) ||x||; the
-    // column's norm over rows >= j is all that is needed besides alpha
-    const double alpha = rowj[p];
-    const double xx = rdlane(n1, p);
-    double beta, tau, scal;
-    if (xx == alpha * alpha) {  // nothing below the diagonal (to rounding): no reflection
-      beta = alpha;
-      tau = 0.0;
-      scal = 0.0;
-    } else {
-      beta = -copysign(sqrt(xx), alpha);
-      tau = (beta - alpha) / beta;
-      scal = 1.0 / (alpha - beta);
-    }
+    pw[0][w][c] = column_dot(p);
+    const Reflector rf = reflector(rdlane(rj, p), rdlane(n1, p));
     if (tid == 0) {
-      tau_s[j] = tau;
+      tau_s[j] = rf.tau;
+      scal_s[j] = rf.scal;
       piv_s[j] = p;
     }
     alive = alive && c != p;
-    const int t0 = j - r0;
-    const bool upd = tau != 0.0 && alive;
-    publish(c == p, t0, scal, 1.0);
-    double s[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    if constexpr (!CHUNKED) {
-#pragma unroll
-      for (int i = 0; i < RS; ++i) s[i & 7] += vsh[i] * a[i];
-    } else
-#pragma unroll
-    for (int q = 0; q < RS; q += QC_CH)
-      if (t0 < q + QC_CH) {  // rows above the diagonal row carry v = 0
-#pragma unroll
-        for (int i = q; i < q + QC_CH; ++i) s[i & 7] += vsh[i] * a[i];
-      }
-    pw[0][w][c] = upd ? tree8(s) : 0.0;
     __syncthreads();
-    const double wc = wave_partials_sum(pw[0], nw, c);
-    const double tw = upd ? tau * wc : 0.0;
-    // column p keeps its rows above j, takes beta at row j and the reflector
-    // below; the other columns take a - tw v (a no-op above row j)
-    const double keep = (c == p) ? 0.0 : 1.0;
-    const double twp = (c == p) ? -1.0 : tw;
-    if constexpr (!CHUNKED) {
+    // w_c = v^T a_c; the other columns take a - tau w_c v
+    const double wc = fma(rf.scal, wave_partials_sum<NW>(pw[0], c), rj);
+    const double tw = alive ? rf.tau * wc : 0.0;
+    const double mul = -tw * rf.scal;
+    if (w == 0) rows[j][c] = c == p ? rf.beta : rj - tw;
+    const int pu = reread(p);
 #pragma unroll
-      for (int i = 0; i < RS; ++i) {
-        const double v = vsh[i];
-        const double own = (i < t0) ? a[i] : (i == t0 ? beta : v);
-        a[i] = (c == p) ? own : a[i] - tw * v;
-      }
-    } else
+    for (int v = 0; v < NV; ++v) {
+      double x[QC_V];
+      column(v, pu, x);
 #pragma unroll
-    for (int q = 0; q < RS; q += QC_CH) {
-      if (t0 < q) {
-#pragma unroll
-        for (int i = q; i < q + QC_CH; ++i) a[i] = fma(-twp, vsh[i], keep * a[i]);
-      } else if (t0 < q + QC_CH) {
-#pragma unroll
-        for (int i = q; i < q + QC_CH; ++i) {
-          const double v = vsh[i];
-          const double own = (i < t0) ? a[i] : (i == t0 ? beta : v);
-          a[i] = (c == p) ? own : a[i] - tw * v;
-        }
-      }
+      for (int i = 0; i < QC_V; ++i) a[v][i] = fma(mul, x[i], a[v][i]);
     }
     nlive = j + 1;
-    norm_partials(j + 1);
+    if (j + 1 < kmax) {
+      retire(j + 1);
+      nret = j + 2;
+    }
+    norm_partial();
     __syncthreads();
   }
+  nlive = __builtin_amdgcn_readfirstlane(nlive);
+  nret = __builtin_amdgcn_readfirstlane(nret);
   if (tid < nlive) step_of[piv_s[tid]] = tid;
   __syncthreads();
+  const int jj = step_of[c];
 
-  // ---------------- R (and its transpose): row jj of every column
+  // ---------------- R (and its transpose)
   if (jb.R != nullptr || jb.Rt != nullptr) {
-#pragma unroll
-    for (int i = 0; i < RS; ++i) {
-      const int row = r0 + i;
-      if (row < cap && c < cap) {
-        const int sc = step_of[c];
-        const bool ok = PIV ? (row < nlive && c < m && (sc < 0 || sc >= row)) : (row < nlive && c < m && c >= row);
-        const double val = ok ? a[i] : 0.0;
+    for (int row = w; row < cap; row += NW) {
+      if (c < cap) {
+        const bool ok = row < nlive && c < m && (PIV ? (jj < 0 || jj >= row) : c >= row);
+        const double val = ok ? rows[ok ? row : 0][c] : 0.0;
         if (jb.R) jb.R[row + (size_t)c * cap] = val;
         if (jb.Rt) jb.Rt[c + (size_t)row * cap] = val;
       }
@@ -321,69 +295,69 @@ __global__ __launch_bounds__(NTB) void qr_cols_kernel(const Task* __restrict__ t
 
   // ---------------- Q by backward accumulation; basis column j sits in column piv[j]
   if (jb.Q == nullptr) return;  // R only (uniform over the block)
+  // the reflectors' entries on the retired rows come back, zeros from the
+  // diagonal up
+#pragma unroll
+  for (int v = 0; v < NV; ++v)
+#pragma unroll
+    for (int i = 0; i < QC_V; ++i) {
+      const int row = r0 + v * QC_V + i;
+      if (row < nret) {
+        const double x = rows[row][c];
+        a[v][i] = (jj >= 0 && jj < row) ? x : 0.0;
+      }
+    }
   bool later = false;  // this lane's column already holds a finished basis column
   for (int j = nlive - 1; j >= 0; --j) {
-    const int p = piv_s[j];
-    const double tau = tau_s[j];
-    const int t0 = j - r0;
+    const int p = __builtin_amdgcn_readfirstlane(piv_s[j]);
+    const double tau = tau_s[j], scal = scal_s[j];
     const int b = j & 1;
-    const bool upd = later && tau != 0.0;
-    publish(c == p, t0, 1.0, 1.0);
-    double s[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    if constexpr (!CHUNKED) {
-#pragma unroll
-      for (int i = 0; i < RS; ++i) s[i & 7] += vsh[i] * a[i];
-    } else
-#pragma unroll
-    for (int q = 0; q < RS; q += QC_CH)
-      if (t0 < q + QC_CH) {
-#pragma unroll
-        for (int i = q; i < q + QC_CH; ++i) s[i & 7] += vsh[i] * a[i];
-      }
-    pw[b][w][c] = upd ? tree8(s) : 0.0;
+    pw[b][w][c] = column_dot(p);
     __syncthreads();
-    const double wc = wave_partials_sum(pw[b], nw, c);
-    const double tw = upd ? tau * wc : 0.0;
     // column p becomes basis column j: 0 above row j, 1 - tau at row j,
-    // -tau v below; the other columns take a - tw v
-    const double keep = (c == p) ? 0.0 : 1.0;
-    const double twp = (c == p) ? tau : tw;
-    if constexpr (!CHUNKED) {
+    // -tau v below; the finished columns, zero at row j, take a - tau w_c v
+    const bool own = c == p;
+    const double tw = later ? tau * (scal * wave_partials_sum<NW>(pw[b], c)) : 0.0;
+    const double mul = (own ? -tau : -tw) * scal;
+    const double keep = own ? 0.0 : 1.0;
+    const int pu = reread(p);
 #pragma unroll
-      for (int i = 0; i < RS; ++i) {
-        const double v = vsh[i];
-        const double own = (i < t0) ? 0.0 : (i == t0 ? 1.0 - tau : -tau * v);
-        a[i] = (c == p) ? own : a[i] - tw * v;
-      }
-    } else
+    for (int v = 0; v < NV; ++v) {
+      double x[QC_V];
+      column(v, pu, x);
 #pragma unroll
-    for (int q = 0; q < RS; q += QC_CH) {
-      if (t0 < q) {
+      for (int i = 0; i < QC_V; ++i) a[v][i] = fma(mul, x[i], keep * a[v][i]);
+    }
+    swap_row(j, [&](double out) { return own ? 1.0 - tau : (later ? -tw : out); });
+    later = later || own;
+  }
 #pragma unroll
-        for (int i = q; i < q + QC_CH; ++i) a[i] = fma(-twp, vsh[i], keep * a[i]);
-      } else if (t0 >= q + QC_CH) {
+  for (int v = 0; v < NV; ++v)
 #pragma unroll
-        for (int i = q; i < q + QC_CH; ++i) a[i] = keep * a[i];
-      } else {
-#pragma unroll
-        for (int i = q; i < q + QC_CH; ++i) {
-          const double v = vsh[i];
-          const double own = (i < t0) ? 0.0 : (i == t0 ? 1.0 - tau : -tau * v);
-          a[i] = (c == p) ? own : a[i] - tw * v;
-        }
+    for (int i = 0; i < QC_V; ++i) {
+      const int row = r0 + v * QC_V + i;
+      if (row < n) {
+        if (jj >= 0) jb.Q[row + (size_t)jj * n] = a[v][i];
+        if (c >= nlive && c < cap) jb.Q[row + (size_t)c * n] = 0.0;
       }
     }
-    later = later || c == p;
-  }
-  const int jj = step_of[c];
-#pragma unroll
-  for (int i = 0; i < RS; ++i) {
-    const int row = r0 + i;
-    if (row < n) {
-      if (jj >= 0) jb.Q[row + (size_t)jj * n] = a[i];
-      if (c >= nlive && c < cap) jb.Q[row + (size_t)c * n] = 0.0;
-    }
-  }
+}
+
+// One launch of the kernel with the row blocks that cover n.
+template <bool PIV, typename Task>
+void qr_launch(const Task* tasks_d, int ntasks, int n, int cap, double drop_tol, const int* m_dev, hipStream_t st) {
+#define TK_QR_CASE(RS, NW)                                                                                       \
+  hipLaunchKernelGGL((qr_cols_kernel<PIV, Task, RS, NW>), dim3(ntasks), dim3(NW * kWave), 0, st, tasks_d, n, cap, \
+                     drop_tol, m_dev)
+  if (n <= 64)
+    TK_QR_CASE(16, 4);
+  else if (n <= 128)
+    TK_QR_CASE(32, 4);
+  else if (n <= 256)
+    TK_QR_CASE(32, 8);
+  else
+    TK_QR_CASE(64, 8);
+#undef TK_QR_CASE
 }
 
 constexpr int CH_NT = 1024;  // 16 waves: a trailing-update column of at most 64 rows takes <= 4 entries per thread
@@ -549,15 +523,7 @@ void qr_batched(const QrTask* tasks_d, int ntasks, int n, int cap, const int* m_
   TK_CHECK(n >= 1 && n <= QC_MAXROWS, kErrUnsupported, "Householder QR: more than 512 rows");
   TK_CHECK(cap <= kWave, kErrUnsupported, "Householder QR: more than 64 columns");
   timer_begin(kKcQr, st, qr_flops(ntasks, n, cap, true));
-  if (n <= 4 * QC_RS)
-    hipLaunchKernelGGL((qr_cols_kernel<false, QrTask, QC_NT_SMALL, QC_RS>), dim3(ntasks),
-                       dim3(kWave * ceil_div(n, QC_RS)), 0, st, tasks_d, n, cap, 0.0, m_dev);
-  else if (n <= 8 * QC_RS)
-    hipLaunchKernelGGL((qr_cols_kernel<false, QrTask, QC_NT, QC_RS>), dim3(ntasks), dim3(kWave * ceil_div(n, QC_RS)),
-                       0, st, tasks_d, n, cap, 0.0, m_dev);
-  else
-    hipLaunchKernelGGL((qr_cols_kernel<false, QrTask, QC_NT, 2 * QC_RS>), dim3(ntasks),
-                       dim3(kWave * ceil_div(n, 2 * QC_RS)), 0, st, tasks_d, n, cap, 0.0, m_dev);
+  qr_launch<false>(tasks_d, ntasks, n, cap, 0.0, m_dev, st);
   TK_LAUNCH_CHECK();
   timer_end(kKcQr, st);
 }
@@ -567,15 +533,7 @@ void qr_piv_batched(const QrPivTask* tasks_d, int ntasks, int n, int cap, double
   TK_CHECK(n >= 1 && n <= QC_MAXROWS && cap <= kWave, kErrUnsupported,
            "pivoted QR: more than 512 rows or 64 columns");
   timer_begin(kKcQr, st, qr_flops(ntasks, n, cap, true));
-  if (n <= 4 * QC_RS)
-    hipLaunchKernelGGL((qr_cols_kernel<true, QrPivTask, QC_NT_SMALL, QC_RS>), dim3(ntasks),
-                       dim3(kWave * ceil_div(n, QC_RS)), 0, st, tasks_d, n, cap, drop_tol, nullptr);
-  else if (n <= 8 * QC_RS)
-    hipLaunchKernelGGL((qr_cols_kernel<true, QrPivTask, QC_NT, QC_RS>), dim3(ntasks), dim3(kWave * ceil_div(n, QC_RS)),
-                       0, st, tasks_d, n, cap, drop_tol, nullptr);
-  else  // the pivoted form would spill with 64 rows per wave: 16 waves of 32
-    hipLaunchKernelGGL((qr_cols_kernel<true, QrPivTask, QC_NT_BIG, QC_RS>), dim3(ntasks),
-                       dim3(kWave * ceil_div(n, QC_RS)), 0, st, tasks_d, n, cap, drop_tol, nullptr);
+  qr_launch<true>(tasks_d, ntasks, n, cap, drop_tol, nullptr, st);
   TK_LAUNCH_CHECK();
   timer_end(kKcQr, st);
 }

@@ -3,6 +3,7 @@
 // (measure-only for the *_workspace queries), execution and export.
 #include <algorithm>
 #include <cmath>
+#include <map>
 #include <memory>
 #include <mutex>
 
@@ -61,76 +62,96 @@ void check_op(const tk_kron_op* op, int d, const int64_t* n) {
   TK_CHECK(op->nterms >= 1 && op->alpha != nullptr && op->A != nullptr, kErrInvalidArg, "operator has no terms");
 }
 
-// Host-side rank staging kept alive by the plan.
-struct HostInts {
-  int v[kMaxD] = {1, 1, 1, 1};
-};
-
-template <typename T>
-void emit_import(Seq& q, const Shape& sh, const tk_tucker& u, const TT<T>& t) {
-  auto hr = std::make_shared<HostInts>();
-  int sd[kMaxD] = {1, 1, 1, 1}, sv[kMaxD] = {1, 1, 1, 1}, dd[kMaxD] = {1, 1, 1, 1};
-  std::array<int, kMaxD> rk{}, ncol{};
+// The moves that bring a caller tensor into the capacity layout: core,
+// factors and ranks.
+template <typename D>
+void import_tasks(const Shape& sh, const tk_tucker& u, const TT<D>& t, std::vector<MoveTask<double, D>>& out) {
   const int d = sh.d;
-  for (int k = 0; k < d; ++k) {
-    hr->v[k] = int(u.r[k]);
-    sd[k] = int(u.rcap[k]);
-    sv[k] = int(u.r[k]);
-    dd[k] = sh.rc;
-    rk[k] = int(u.r[k]);
-    ncol[k] = sh.n[k];
+  MoveTask<double, D> c{};
+  c.src = u.core;
+  c.dst = t.core;
+  c.total = sh.core_len();
+  c.d = d;
+  c.rank = t.rank;
+  for (int k = 0; k < kMaxD; ++k) {
+    c.sd[k] = k < d ? int(u.rcap[k]) : 1;
+    c.sv[k] = k < d ? int(u.r[k]) : 1;
+    c.dd[k] = k < d ? sh.rc : 1;
+    c.rk[k] = k < d ? int(u.r[k]) : 1;
   }
-  const double* core = u.core;
-  std::array<const double*, kMaxD> U = {u.U[0], u.U[1], u.U[2], u.U[3]};
-  const int rc = sh.rc;
-  q.steps.push_back([=](hipStream_t st) {
-    core_recap<double>(core, sd, sv, t.core, dd, d, st);
-    for (int k = 0; k < d; ++k) mat_recap<double>(U[k], ncol[k], ncol[k], rk[k], t.U[k], ncol[k], ncol[k], rc, st);
-    TK_HIP(hipMemcpyAsync(t.rank, hr->v, sizeof(int) * kMaxD, hipMemcpyHostToDevice, st));
-  });
+  out.push_back(c);
+  for (int k = 0; k < d; ++k) {
+    MoveTask<double, D> f{};
+    f.src = u.U[k];
+    f.dst = t.U[k];
+    f.total = size_t(sh.n[k]) * sh.rc;
+    f.valid = size_t(sh.n[k]) * size_t(u.r[k]);
+    out.push_back(f);
+  }
 }
 
-// Copies an internal tensor out; ranks are read back first.
-void export_tt(const Shape& sh, const TT<double>& t, tk_tucker* u, hipStream_t st) {
-  int r[kMaxD] = {0, 0, 0, 0};
-  TK_HIP(hipMemcpyAsync(r, t.rank, sizeof(int) * kMaxD, hipMemcpyDeviceToHost, st));
-  TK_HIP(hipStreamSynchronize(st));
-  const int d = sh.d;
-  for (int k = 0; k < d; ++k)
-    TK_CHECK(r[k] >= 1 && r[k] <= u->rcap[k], kErrCapacity,
-             "output rank " + std::to_string(r[k]) + " exceeds the capacity of the output tensor");
-  int sd[kMaxD] = {1, 1, 1, 1}, sv[kMaxD] = {1, 1, 1, 1}, dd[kMaxD] = {1, 1, 1, 1};
-  for (int k = 0; k < d; ++k) {
-    sd[k] = sh.rc;
-    sv[k] = r[k];
-    dd[k] = int(u->rcap[k]);
-  }
-  core_recap<double>(t.core, sd, sv, u->core, dd, d, st);
-  for (int k = 0; k < d; ++k)
-    mat_recap<double>(t.U[k], sh.n[k], sh.n[k], r[k], u->U[k], sh.n[k], sh.n[k], int(u->rcap[k]), st);
-  for (int k = 0; k < d; ++k) u->r[k] = r[k];
-  TK_HIP(hipStreamSynchronize(st));
-}
-
-// Element-type conversion of an internal tensor (capacity layout) and of a
-// plain device array, as plan steps.
+// A plain array converted from S to D.
 template <typename S, typename D>
-void emit_cast_tt(Seq& q, const Shape& sh, const TT<S>& src, const TT<D>& dst) {
-  const size_t cl = sh.core_len();
-  const int d = sh.d;
-  std::array<size_t, kMaxD> fl{};
-  for (int k = 0; k < d; ++k) fl[k] = size_t(sh.n[k]) * sh.rc;
-  q.steps.push_back([=](hipStream_t st) {
-    cast_copy<S, D>(src.core, dst.core, cl, st);
-    for (int k = 0; k < d; ++k) cast_copy<S, D>(src.U[k], dst.U[k], fl[k], st);
-    copy_ints(src.rank, dst.rank, d, st);
-  });
+MoveTask<S, D> convert_task(const S* src, D* dst, size_t len) {
+  MoveTask<S, D> t{};
+  t.src = src;
+  t.dst = dst;
+  t.total = t.valid = len;
+  return t;
 }
-const float* emit_to_f32(Seq& q, Arena& ar, const double* src, size_t len) {
-  float* dst = ar.alloc<float>(len);
-  q.steps.push_back([=](hipStream_t st) { cast_copy<double, float>(src, dst, len, st); });
-  return dst;
+
+// One launch for all moves of a call (the table goes into the plan's blob).
+template <typename S, typename D>
+void emit_moves(Seq& q, Planner& pl, const std::vector<MoveTask<S, D>>& tasks) {
+  size_t mx = 0;
+  for (auto& t : tasks) mx = std::max<size_t>(mx, t.total);
+  const size_t off = pl.blob.add(tasks);
+  const int nt = int(tasks.size());
+  Blob* bl = &pl.blob;
+  q.steps.push_back([=](hipStream_t st) { move_parts<S, D>(bl->at<MoveTask<S, D>>(off), nt, mx, st); });
 }
+
+// Import of one tensor outside a plan (tasks as kernel arguments).
+void emit_import(Seq& q, const Shape& sh, const tk_tucker& u, const TT<double>& t) {
+  std::vector<MoveTask<double, double>> tasks;
+  import_tasks<double>(sh, u, t, tasks);
+  MoveSet<double, double> set;
+  for (auto& x : tasks) set.t[set.count++] = x;
+  q.steps.push_back([=](hipStream_t st) { move_set<double, double>(set, st); });
+}
+
+constexpr int kExportHdr = kMaxD + 1;  // ints of the export's header
+
+// Copies an internal tensor out and reads its ranks (and the width *s_dev)
+// back; `hdr` holds kExportHdr device ints.
+template <typename T>
+void export_tt(const Shape& sh, const TT<T>& t, tk_tucker* u, int* hdr, const int* s_dev, int32_t* s_out,
+               hipStream_t st) {
+  ExportArgs<T> a{};
+  a.core = t.core;
+  a.rank = t.rank;
+  a.s_dev = s_dev;
+  a.out_core = u->core;
+  a.d = sh.d;
+  a.rc = sh.rc;
+  a.hdr = hdr;
+  for (int k = 0; k < sh.d; ++k) {
+    a.U[k] = t.U[k];
+    a.out_U[k] = u->U[k];
+    a.n[k] = sh.n[k];
+    a.rcap[k] = int(u->rcap[k]);
+  }
+  export_parts<T>(a, st);
+  int h[kExportHdr] = {0};
+  TK_HIP(hipMemcpyAsync(h, hdr, sizeof(h), hipMemcpyDeviceToHost, st));
+  TK_HIP(hipStreamSynchronize(st));
+  if (s_out) *s_out = h[kMaxD];
+  for (int k = 0; k < sh.d; ++k)
+    TK_CHECK(h[k] >= 1 && h[k] <= u->rcap[k], kErrCapacity,
+             "output rank " + std::to_string(h[k]) + " exceeds the capacity of the output tensor");
+  for (int k = 0; k < sh.d; ++k) u->r[k] = h[k];
+}
+
 void check_form(int form) {
   TK_CHECK(form == TK_FORM_FP64 || form == TK_FORM_FP32 || form == TK_FORM_BF16, kErrUnsupported, "unknown form");
 }
@@ -165,26 +186,61 @@ int do_apply(const tk_kron_op* op, const tk_tucker* x, int transpose, int form, 
   pl.bf16_factors = form == TK_FORM_BF16;
   const bool f32 = form != TK_FORM_FP64;  // FP32 storage (FP32 and BF16-factor forms)
   Seq q;
-  std::array<const float*, kMaxD> U32{};
-  if (f32)
-    for (int k = 0; k < d; ++k) U32[k] = emit_to_f32(q, ar, x->U[k], size_t(x->n[k]) * x->rcap[k]);
+  // the products of one shape (mode size, rank capacity) share a launch
+  struct Product {
+    const double* A;
+    double* out;
+    int k;
+  };
+  std::map<std::pair<int, int>, std::vector<Product>> shapes;
   for (int j = 0; j < op->nterms; ++j)
     for (int k = 0; k < d; ++k) {
       const double* A = op->A[j * d + k];
       if (!A) continue;
       TK_CHECK(AU != nullptr && AU[j * d + k] != nullptr, kErrInvalidArg, "missing output buffer for a factor product");
-      const int n = int(x->n[k]), rcap = int(x->rcap[k]);
-      if (f32) {
-        const float* A32 = emit_to_f32(q, ar, A, size_t(n) * n);
-        float* P32 = ar.alloc<float>(size_t(n) * rcap);
-        plan_gemm<float>(q, pl, !transpose, false, n, rcap, n, A32, n, U32[k], n, P32, n, 1.0, 0.0, true);
-        double* dst = AU[j * d + k];
-        const size_t len = size_t(n) * rcap;
-        q.steps.push_back([=](hipStream_t st) { cast_copy<float, double>(P32, dst, len, st); });
-      } else {
-        plan_gemm<double>(q, pl, !transpose, false, n, rcap, n, A, n, x->U[k], n, AU[j * d + k], n, 1.0, 0.0);
-      }
+      shapes[{int(x->n[k]), int(x->rcap[k])}].push_back(Product{A, AU[j * d + k], k});
     }
+  // FP32 storage: operands rounded by one launch, results widened by one
+  std::map<std::pair<const double*, size_t>, const float*> narrow;
+  std::vector<MoveTask<double, float>> down;
+  std::vector<MoveTask<float, double>> up;
+  auto f32_of = [&](const double* src, size_t len) {
+    auto& p = narrow[{src, len}];
+    if (!p) {
+      float* dst = ar.alloc<float>(len);
+      down.push_back(convert_task<double, float>(src, dst, len));
+      p = dst;
+    }
+    return p;
+  };
+  Seq prod;
+  for (auto& sh : shapes) {
+    const int n = sh.first.first, rcap = sh.first.second;
+    const size_t len = size_t(n) * rcap;
+    if (f32) {
+      std::vector<const float*> a, b;
+      std::vector<float*> c;
+      for (auto& p : sh.second) {
+        a.push_back(f32_of(p.A, size_t(n) * n));
+        b.push_back(f32_of(x->U[p.k], len));
+        c.push_back(ar.alloc<float>(len));
+        up.push_back(convert_task<float, double>(c.back(), p.out, len));
+      }
+      plan_gemm_batched<float>(prod, pl, !transpose, false, n, rcap, n, a, n, b, n, c, n, 1.0, true);
+    } else {
+      std::vector<const double*> a, b;
+      std::vector<double*> c;
+      for (auto& p : sh.second) {
+        a.push_back(p.A);
+        b.push_back(x->U[p.k]);
+        c.push_back(p.out);
+      }
+      plan_gemm_batched<double>(prod, pl, !transpose, false, n, rcap, n, a, n, b, n, c, n, 1.0);
+    }
+  }
+  if (f32) emit_moves(q, pl, down);
+  for (auto& f : prod.steps) q.steps.push_back(f);
+  if (f32) emit_moves(q, pl, up);
   finish_blob(ar, blob, st);
   if (ar.measuring()) return 0;
   q.run(st);
@@ -248,14 +304,14 @@ struct FiniteCheck {
 };
 
 // ---------------------------------------------------------------- block sums
+template <typename T>
 struct Imported {
   Shape sh;
-  std::vector<TT<double>> t;
-  Blocks<double> blocks;
-  std::shared_ptr<std::vector<double>> coef;
+  Blocks<T> blocks;
 };
 
-Imported import_blocks(Seq& q, Arena& ar, const tk_block_sum* in, int cap, int p) {
+// Shape of a block sum (checked), without importing it.
+Shape shape_of_blocks(const tk_block_sum* in, int cap, int p) {
   TK_CHECK(in != nullptr && in->nblocks >= 1 && in->blocks != nullptr && in->coef != nullptr, kErrInvalidArg,
            "empty block sum");
   const tk_tucker& b0 = in->blocks[0];
@@ -266,27 +322,33 @@ Imported import_blocks(Seq& q, Arena& ar, const tk_block_sum* in, int cap, int p
     for (int k = 0; k < b0.d; ++k) rc = std::max<int>(rc, int(in->blocks[b].r[k]));
   }
   TK_CHECK(rc <= 128, kErrUnsupported, "ranks above 128 are not supported");
-  Imported im;
-  im.sh = shape_of(b0.d, b0.n, rc, cap, p);
-  im.coef = std::make_shared<std::vector<double>>(in->coef, in->coef + in->nblocks);
+  return shape_of(b0.d, b0.n, rc, cap, p);
+}
+
+// The blocks in the capacity layout, rounded to T; the moves are added to
+// `tasks` (launched by the caller together with its own).
+template <typename T>
+Imported<T> import_blocks(Arena& ar, const tk_block_sum* in, const Shape& sh, std::vector<MoveTask<double, T>>& tasks) {
+  Imported<T> im;
+  im.sh = sh;
   for (int b = 0; b < in->nblocks; ++b) {
-    TT<double> t = alloc_tt<double>(ar, im.sh);
-    emit_import<double>(q, im.sh, in->blocks[b], t);
-    im.t.push_back(t);
+    TT<T> t = alloc_tt<T>(ar, sh);
+    import_tasks<T>(sh, in->blocks[b], t, tasks);
     im.blocks.add(t, nullptr, in->coef[b]);
   }
   return im;
 }
 
-// The imported blocks rounded to FP32 (same coefficients).
-Blocks<float> blocks_f32(Seq& q, Arena& ar, const Imported& im) {
-  Blocks<float> out;
-  for (size_t b = 0; b < im.t.size(); ++b) {
-    TT<float> t = alloc_tt<float>(ar, im.sh);
-    emit_cast_tt<double, float>(q, im.sh, im.t[b], t);
-    out.add(t, nullptr, im.blocks.cscale[b]);
+// Sketch factors (n_k x w) rounded to FP32.
+std::array<const float*, kMaxD> sketch_f32(Arena& ar, const Shape& sh, const double* const* S, size_t w,
+                                           std::vector<MoveTask<double, float>>& tasks) {
+  std::array<const float*, kMaxD> o{};
+  for (int k = 0; k < sh.d; ++k) {
+    float* dst = ar.alloc<float>(size_t(sh.n[k]) * w);
+    tasks.push_back(convert_task<double, float>(S[k], dst, size_t(sh.n[k]) * w));
+    o[k] = dst;
   }
-  return out;
+  return o;
 }
 
 int do_sketch(const tk_block_sum* x, const double* const* S, int64_t s, int form, double* out, Arena& ar,
@@ -297,20 +359,24 @@ int do_sketch(const tk_block_sum* x, const double* const* S, int64_t s, int form
   Blob blob;
   Planner pl(ar, blob);
   Seq q;
-  Imported im = import_blocks(q, ar, x, 1, 0);
+  const Shape sh = shape_of_blocks(x, 1, 0);
   std::array<const double*, kMaxD> Sk{};
-  for (int k = 0; k < im.sh.d; ++k) {
+  for (int k = 0; k < sh.d; ++k) {
     TK_CHECK(S[k] != nullptr, kErrInvalidArg, "sketch factor is NULL");
     Sk[k] = S[k];
   }
   pl.bf16_factors = form == TK_FORM_BF16;
   if (form != TK_FORM_FP64) {
-    std::array<const float*, kMaxD> S32{};
-    for (int k = 0; k < im.sh.d; ++k) S32[k] = emit_to_f32(q, ar, Sk[k], size_t(im.sh.n[k]) * s);
-    Blocks<float> b32 = blocks_f32(q, ar, im);
-    plan_sketch<float>(q, pl, im.sh, b32, S32, int(s), out);
+    std::vector<MoveTask<double, float>> mv;
+    const auto S32 = sketch_f32(ar, sh, Sk.data(), size_t(s), mv);
+    const auto im = import_blocks<float>(ar, x, sh, mv);
+    emit_moves(q, pl, mv);
+    plan_sketch<float>(q, pl, sh, im.blocks, S32, int(s), out);
   } else {
-    plan_sketch<double>(q, pl, im.sh, im.blocks, Sk, int(s), out);
+    std::vector<MoveTask<double, double>> mv;
+    const auto im = import_blocks<double>(ar, x, sh, mv);
+    emit_moves(q, pl, mv);
+    plan_sketch<double>(q, pl, sh, im.blocks, Sk, int(s), out);
   }
   finish_blob(ar, blob, st);
   if (ar.measuring()) return 0;
@@ -328,8 +394,7 @@ int do_rhosvd(const tk_block_sum* in, const tk_round_params* prm, const double* 
   Blob blob;
   Planner pl(ar, blob);
   Seq q;
-  Imported im = import_blocks(q, ar, in, prm->rank_cap, prm->oversample);
-  const Shape& sh = im.sh;
+  const Shape sh = shape_of_blocks(in, prm->rank_cap, prm->oversample);
   TK_CHECK(prm->force_s < 0 || (prm->force_s >= 1 && prm->force_s <= sh.sc()), kErrInvalidArg,
            "force_s outside [1, rank_cap + oversample]");
   RoundCfg cfg;
@@ -345,17 +410,24 @@ int do_rhosvd(const tk_block_sum* in, const tk_round_params* prm, const double* 
   for (int k = 0; k < sh.d; ++k) om[k] = omega[k];
   if (out) check_dims(out->d, out->n);
   check_form(prm->form);
-  TT<double> o = alloc_tt<double>(ar, sh);
+  TT<double> o;
+  TT<float> o32;
   int* s_dev = nullptr;
+  int* hdr = ar.alloc<int>(kExportHdr);
+  const bool f32 = prm->form != TK_FORM_FP64;
   pl.bf16_factors = prm->form == TK_FORM_BF16;
-  if (prm->form != TK_FORM_FP64) {
-    std::array<const float*, kMaxD> om32{};
-    for (int k = 0; k < sh.d; ++k) om32[k] = emit_to_f32(q, ar, om[k], size_t(sh.n[k]) * sh.sc());
-    Blocks<float> b32 = blocks_f32(q, ar, im);
-    TT<float> o32 = alloc_tt<float>(ar, sh);
-    s_dev = plan_roundsum<float>(q, pl, sh, b32, cfg, om32, o32, nullptr).s_dev;
-    emit_cast_tt<float, double>(q, sh, o32, o);
+  if (f32) {
+    std::vector<MoveTask<double, float>> mv;
+    const auto om32 = sketch_f32(ar, sh, om.data(), size_t(sh.sc()), mv);
+    const auto im = import_blocks<float>(ar, in, sh, mv);
+    emit_moves(q, pl, mv);
+    o32 = alloc_tt<float>(ar, sh);
+    s_dev = plan_roundsum<float>(q, pl, sh, im.blocks, cfg, om32, o32, nullptr).s_dev;
   } else {
+    std::vector<MoveTask<double, double>> mv;
+    const auto im = import_blocks<double>(ar, in, sh, mv);
+    emit_moves(q, pl, mv);
+    o = alloc_tt<double>(ar, sh);
     s_dev = plan_roundsum<double>(q, pl, sh, im.blocks, cfg, om, o, nullptr).s_dev;
   }
   finish_blob(ar, blob, st);
@@ -363,10 +435,10 @@ int do_rhosvd(const tk_block_sum* in, const tk_round_params* prm, const double* 
   TK_CHECK(out != nullptr && out->d == sh.d, kErrInvalidArg, "output tensor missing or of wrong order");
   for (int k = 0; k < sh.d; ++k) TK_CHECK(out->n[k] == sh.n[k], kErrShape, "output mode size mismatch");
   q.run(st);
-  if (s_out) {
-    TK_HIP(hipMemcpyAsync(s_out, s_dev, sizeof(int), hipMemcpyDeviceToHost, st));
-  }
-  export_tt(sh, o, out, st);
+  if (f32)
+    export_tt<float>(sh, o32, out, hdr, s_dev, s_out, st);
+  else
+    export_tt<double>(sh, o, out, hdr, s_dev, s_out, st);
   return 0;
 }
 
@@ -374,8 +446,11 @@ int do_norm(const tk_block_sum* x, double* out, Arena& ar, hipStream_t st) {
   Blob blob;
   Planner pl(ar, blob);
   Seq q;
-  Imported im = import_blocks(q, ar, x, 1, 0);
-  TK_CHECK(im.sh.rc <= 64, kErrUnsupported, "exact norm: ranks above 64");
+  const Shape sh = shape_of_blocks(x, 1, 0);
+  TK_CHECK(sh.rc <= 64, kErrUnsupported, "exact norm: ranks above 64");
+  std::vector<MoveTask<double, double>> mv;
+  const auto im = import_blocks<double>(ar, x, sh, mv);
+  emit_moves(q, pl, mv);
   double* n2 = ar.alloc<double>(1);
   plan_exact_norm2(q, pl, im.sh, im.blocks, n2);
   finish_blob(ar, blob, st);
@@ -489,11 +564,11 @@ int do_solve(const tk_kron_op* op, const tk_tucker* b, const tk_sgmres_params* p
   Shape sh = shape_of(d, b->n, rc, prm->rank_cap, prm->oversample);
   Seq imp;
   TT<double> bi = alloc_tt<double>(ar, sh);
-  emit_import<double>(imp, sh, *b, bi);
+  emit_import(imp, sh, *b, bi);
   TT<double> x0i;
   if (prm->x0) {
     x0i = alloc_tt<double>(ar, sh);
-    emit_import<double>(imp, sh, *prm->x0, x0i);
+    emit_import(imp, sh, *prm->x0, x0i);
   }
   std::array<const double*, kMaxD> Sk{}, Ok{};
   for (int k = 0; k < d; ++k) {
@@ -502,6 +577,7 @@ int do_solve(const tk_kron_op* op, const tk_tucker* b, const tk_sgmres_params* p
   }
   auto solver = make_solver(ar, sh, op_dev(op), bi, solve_cfg(prm), Sk, Ok, prm->x0 ? &x0i : nullptr, st,
                             precond_of(prm, d));
+  int* hdr = ar.alloc<int>(kExportHdr);
   FiniteCheck fin;
   fin.add_tt(sh, bi);
   if (prm->x0) fin.add_tt(sh, x0i);
@@ -514,7 +590,7 @@ int do_solve(const tk_kron_op* op, const tk_tucker* b, const tk_sgmres_params* p
   TT<double> xo;
   SolveInfo si;
   solver_run(*solver, xo, si, st);
-  export_tt(sh, xo, x, st);
+  export_tt<double>(sh, xo, x, hdr, nullptr, nullptr, st);
   fill_info(si, info, d);
   return si.status;
 }
@@ -547,13 +623,13 @@ int do_backward(const tk_kron_op* op, const tk_tucker* x, const tk_block_sum* xb
   Seq imp, pre, post;
   // import x and the cotangent blocks, round the cotangent (FP64)
   TT<double> xi = alloc_tt<double>(ar, sh);
-  emit_import<double>(imp, sh, *x, xi);
+  emit_import(imp, sh, *x, xi);
   FiniteCheck fin;
   fin.add_tt(sh, xi);
   Blocks<double> xb;
   for (int b = 0; b < xbar->nblocks; ++b) {
     TT<double> t = alloc_tt<double>(ar, sh);
-    emit_import<double>(imp, sh, xbar->blocks[b], t);
+    emit_import(imp, sh, xbar->blocks[b], t);
     fin.add_tt(sh, t);
     TK_CHECK(std::isfinite(xbar->coef[b]), kErrNonFinite, "cotangent coefficient is not finite");
     xb.add(t, nullptr, xbar->coef[b]);
@@ -574,6 +650,7 @@ int do_backward(const tk_kron_op* op, const tk_tucker* x, const tk_block_sum* xb
   auto solver = make_solver(ar, sh, od, xbr, scfg, Sk, Ok, nullptr, st, precond_of(prm, d));
   // gradient contractions, planned for every solution slot of the solver
   double* dal = ar.alloc<double>(op->nterms);
+  int* hdr = ar.alloc<int>(kExportHdr);
   Seq grad[3];
   for (int slot = 0; slot < 3; ++slot) {
     const TT<double> lam = solver_slot(*solver, slot);
@@ -621,7 +698,7 @@ int do_backward(const tk_kron_op* op, const tk_tucker* x, const tk_block_sum* xb
     TK_HIP(hipMemcpyAsync(dalpha, dal, sizeof(double) * op->nterms, hipMemcpyDeviceToHost, st));
   }
   TK_HIP(hipStreamSynchronize(st));
-  if (lambda) export_tt(sh, lam, lambda, st);
+  if (lambda) export_tt<double>(sh, lam, lambda, hdr, nullptr, nullptr, st);
   fill_info(si, info, d);
   return si.status;
 }
@@ -645,7 +722,9 @@ int do_mln_sketch(const tk_block_sum* x, const double* const* Psi, int r, int p,
   Blob blob;
   Planner pl(ar, blob);
   Seq q;
-  Imported im = import_blocks(q, ar, x, 1, 0);
+  std::vector<MoveTask<double, double>> mv;
+  const auto im = import_blocks<double>(ar, x, shape_of_blocks(x, 1, 0), mv);
+  emit_moves(q, pl, mv);
   const int d = im.sh.d;
   const auto ps = psi_of(Psi, d);
   TK_CHECK(F != nullptr, kErrInvalidArg, "factor sketch outputs missing");
@@ -679,6 +758,7 @@ int do_mln_recover(const double* core, const double* const* F, const double* con
   sk.core = const_cast<double*>(core);
   for (int k = 0; k < d; ++k) sk.F[k] = const_cast<double*>(F[k]);
   TT<double> o = alloc_tt<double>(ar, sh);
+  int* hdr = ar.alloc<int>(kExportHdr);
   plan_mln_recovery(q, pl, sh, sk, ps, r, r + p, o);
   finish_blob(ar, blob, st);
   if (ar.measuring()) return 0;
@@ -688,7 +768,7 @@ int do_mln_recover(const double* core, const double* const* F, const double* con
     TK_CHECK(out->rcap[k] >= r, kErrCapacity, "output rank capacity below r");
   }
   q.run(st);
-  export_tt(sh, o, out, st);
+  export_tt<double>(sh, o, out, hdr, nullptr, nullptr, st);
   return 0;
 }
 
@@ -720,7 +800,7 @@ int do_mln_solve(const tk_kron_op* op, const tk_tucker* b, const tk_mln_params* 
   Shape sh = shape_of(d, b->n, prm->r, prm->r, prm->p);
   Seq imp;
   TT<double> bi = alloc_tt<double>(ar, sh);
-  emit_import<double>(imp, sh, *b, bi);
+  emit_import(imp, sh, *b, bi);
   MlnCfg cfg;
   cfg.r = prm->r;
   cfg.p = prm->p;
@@ -742,6 +822,7 @@ int do_mln_solve(const tk_kron_op* op, const tk_tucker* b, const tk_mln_params* 
       TK_CHECK(ar.measuring() || (pc.V[k] != nullptr && pc.lam[k] != nullptr), kErrInvalidArg,
                "preconditioner eigenpairs missing");
     }
+  int* hdr = ar.alloc<int>(kExportHdr);
   auto solver = make_mln_solver(ar, sh, op_dev(op), bi, cfg, ps, st, pc);
   if (ar.measuring()) return 0;
   TK_CHECK(x != nullptr, kErrInvalidArg, "x is NULL");
@@ -750,7 +831,7 @@ int do_mln_solve(const tk_kron_op* op, const tk_tucker* b, const tk_mln_params* 
   TT<double> xo;
   MlnInfo mi;
   mln_solver_run(*solver, xo, mi, st);
-  export_tt(sh, xo, x, st);
+  export_tt<double>(sh, xo, x, hdr, nullptr, nullptr, st);
   if (info) {
     SolveInfo si;
     si.status = mi.status;

@@ -1517,9 +1517,10 @@ void plan_gemm(Seq& q, Planner& pl, bool ta, bool tb, int M, int N, int K, const
 template <typename T>
 void plan_gemm_batched(Seq& q, Planner& pl, bool ta, bool tb, int M, int N, int K, const std::vector<const T*>& A,
                        int lda, const std::vector<const T*>& B, int ldb, const std::vector<T*>& C, int ldc,
-                       double alpha) {
+                       double alpha, bool factor_product) {
   TK_CHECK(A.size() == B.size() && A.size() == C.size(), kErrInvalidArg, "batched GEMM: table sizes differ");
   GemmDesc<T> g;
+  g.factor_product = factor_product;
   g.ta = ta;
   g.tb = tb;
   g.M = M;
@@ -1629,7 +1630,7 @@ void plan_precond(Seq& q, Planner& pl, const Shape& sh, const PrecondT<T>& pc, c
   template void plan_inner<T>(Seq&, Planner&, const Shape&, const std::vector<TT<T>>&, const Blocks<T>&,      \
                               double*, double, std::vector<T*>*);                                              \
   template void plan_gemm_batched<T>(Seq&, Planner&, bool, bool, int, int, int, const std::vector<const T*>&, \
-                                     int, const std::vector<const T*>&, int, const std::vector<T*>&, int, double); \
+                                     int, const std::vector<const T*>&, int, const std::vector<T*>&, int, double, bool); \
   template void plan_krp_range<T>(Seq&, Planner&, const Shape&, const Blocks<T>&, const double*,              \
                                   const std::array<const T*, kMaxD>&, int, const std::array<T*, kMaxD>&,     \
                                   const int*);                                                                 \

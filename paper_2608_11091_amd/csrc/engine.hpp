@@ -174,7 +174,7 @@ void plan_gemm(Seq& q, Planner& pl, bool ta, bool tb, int M, int N, int K, const
 template <typename T>
 void plan_gemm_batched(Seq& q, Planner& pl, bool ta, bool tb, int M, int N, int K, const std::vector<const T*>& A,
                        int lda, const std::vector<const T*>& B, int ldb, const std::vector<T*>& C, int ldc,
-                       double alpha);
+                       double alpha, bool factor_product = false);
 
 // Khatri-Rao range sketch of a block sum with per-block device coefficients
 // coef[b]: Y_k = sum_b coef_b U_bk MTTKRP(G_b; {U_bj^T L_j[:, :w]}_{j != k}, k)

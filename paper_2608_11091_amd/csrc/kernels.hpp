@@ -46,6 +46,54 @@ template <typename T>
 void dot_batched(const T* const* xs, const T* const* ys, size_t len, int n, double scale, double* out,
                  hipStream_t st);
 
+// Batched moves between caller tensors and internal buffers (one launch for
+// every part of every tensor of a call), converting S to D on the way.
+//   d == 0: dst[e] = e < valid ? src[e] : 0 for e < total (a matrix whose
+//           leading columns are kept, or a plain array);
+//   d >= 1: dst (dims dd, row-major) = the leading sv indices of src (dims sd),
+//           zero outside.
+// A task with `rank` also stores rk[0..kMaxD) there (one thread).
+template <typename S, typename D>
+struct MoveTask {
+  const S* src;
+  D* dst;
+  size_t total, valid;
+  int d;
+  int sd[kMaxD], sv[kMaxD], dd[kMaxD];
+  int* rank;
+  int rk[kMaxD];
+};
+template <typename S, typename D>
+void move_parts(const MoveTask<S, D>* tasks_d, int ntasks, size_t maxtotal, hipStream_t st);
+// The same for one tensor's parts, the tasks passed as kernel arguments.
+constexpr int kMoveSet = kMaxD + 1;
+template <typename S, typename D>
+struct MoveSet {
+  int count = 0;
+  MoveTask<S, D> t[kMoveSet];
+};
+template <typename S, typename D>
+void move_set(const MoveSet<S, D>& set, hipStream_t st);
+
+// Copies an internal tensor (core capacity rc in every mode, ranks on the
+// device) into a caller tensor of capacities rcap, zero beyond the ranks, and
+// stores {rank_0 .. rank_3, *s_dev} in hdr[0..5).  With a rank outside
+// 1 .. rcap nothing but hdr is written (the host raises the error from hdr).
+template <typename T>
+struct ExportArgs {
+  const T* core;
+  const T* U[kMaxD];
+  const int* rank;
+  const int* s_dev;  // optional
+  double* out_core;
+  double* out_U[kMaxD];
+  int d, rc;
+  int n[kMaxD], rcap[kMaxD];
+  int* hdr;
+};
+template <typename T>
+void export_parts(const ExportArgs<T>& a, hipStream_t st);
+
 // ---- elementwise --------------------------------------------------------------
 // y = alpha * x with alpha = scale * (*num) / (*den) (num/den optional device
 // scalars; a denominator that is not positive and finite gives alpha = 0).

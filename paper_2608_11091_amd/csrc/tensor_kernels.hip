@@ -218,6 +218,104 @@ __global__ void cast_multi_kernel(CastSet<A, B> set) {
     y[e] = B(x[e]);
 }
 
+// dst (dims dd, row-major, `total` elements) = the indices of src (dims sd)
+// below sv, zero outside.  I is unsigned where `total` fits in it (a 64-bit
+// remainder costs several times a 32-bit one).
+template <typename I, typename S, typename D>
+__device__ __forceinline__ void recap_loop(GPtr<S> src, D* dst, I total, int d, const int* dd, const int* sd,
+                                           const int* sv, I e0, I step) {
+  for (I e = e0; e < total; e += step) {
+    I rem = e;
+    size_t so = 0, sstr = 1;
+    bool inside = true;
+#pragma unroll
+    for (int k = kMaxD - 1; k >= 0; --k) {
+      if (k >= d) continue;
+      const int ik = int(rem % I(dd[k]));
+      rem /= I(dd[k]);
+      inside = inside && ik < sv[k] && ik < sd[k];
+      so += size_t(ik) * sstr;
+      sstr *= size_t(sd[k]);
+    }
+    dst[e] = inside ? D(src[so]) : D(0);
+  }
+}
+
+template <typename S, typename D>
+__device__ __forceinline__ void recap(GPtr<S> src, D* dst, size_t total, int d, const int* dd, const int* sd,
+                                      const int* sv) {
+  const unsigned e0 = blockIdx.x * blockDim.x + threadIdx.x, step = gridDim.x * blockDim.x;
+  if (total <= 0x7fffffffu)
+    recap_loop<unsigned>(src, dst, unsigned(total), d, dd, sd, sv, e0, step);
+  else
+    recap_loop<size_t>(src, dst, total, d, dd, sd, sv, size_t(e0), size_t(step));
+}
+
+template <typename S, typename D>
+__device__ __forceinline__ void move_one(const MoveTask<S, D>& t) {
+  const size_t e0 = size_t(blockIdx.x) * blockDim.x + threadIdx.x, step = size_t(gridDim.x) * blockDim.x;
+  if (t.rank != nullptr && e0 < kMaxD) t.rank[e0] = t.rk[e0];
+  const GPtr<S> src = (GPtr<S>)t.src;
+  if (t.d == 0) {
+    for (size_t e = e0; e < t.total; e += step) t.dst[e] = e < t.valid ? D(src[e]) : D(0);
+  } else {
+    recap(src, t.dst, t.total, t.d, t.dd, t.sd, t.sv);
+  }
+}
+
+// Latency: a part is 1 to 24 KB per block at working sizes, so what counts is
+// that all parts of all blocks go in one launch (three rank-48 blocks at
+// n = 512: 15 launches and three rank copies, 36 us, before).
+template <typename S, typename D>
+__global__ __launch_bounds__(256) void move_parts_kernel(const MoveTask<S, D>* __restrict__ tasks) {
+  const MoveTask<S, D> t = tasks[blockIdx.y];
+  move_one(t);
+}
+
+template <typename S, typename D>
+__global__ __launch_bounds__(256) void move_set_kernel(MoveSet<S, D> set) {
+#pragma unroll
+  for (int i = 0; i < kMoveSet; ++i)
+    if (i == int(blockIdx.y)) move_one(set.t[i]);
+}
+
+// Ranks are read on the device, so the copies do not wait for a round trip of
+// the ranks through the host: one launch, one copy back and one wait in place
+// of d + 1 launches, two copies and two waits.
+template <typename T>
+__global__ __launch_bounds__(256) void export_kernel(ExportArgs<T> a) {
+  int r[kMaxD], sd[kMaxD];
+  bool fits = true;
+#pragma unroll
+  for (int k = 0; k < kMaxD; ++k) {
+    r[k] = k < a.d ? a.rank[k] : 1;
+    sd[k] = a.rc;
+    if (k < a.d) fits = fits && r[k] >= 1 && r[k] <= a.rcap[k];
+  }
+  if (blockIdx.y == 0 && blockIdx.x == 0 && threadIdx.x == 0) {
+#pragma unroll
+    for (int k = 0; k < kMaxD; ++k) a.hdr[k] = k < a.d ? r[k] : 0;
+    a.hdr[kMaxD] = a.s_dev ? *a.s_dev : 0;
+  }
+  if (!fits) return;
+  if (blockIdx.y == 0) {
+    size_t total = 1;
+#pragma unroll
+    for (int k = 0; k < kMaxD; ++k) total *= k < a.d ? size_t(a.rcap[k]) : size_t(1);
+    recap<T, double>((GPtr<T>)a.core, a.out_core, total, a.d, a.rcap, sd, r);
+    return;
+  }
+  const size_t e0 = size_t(blockIdx.x) * blockDim.x + threadIdx.x, step = size_t(gridDim.x) * blockDim.x;
+#pragma unroll
+  for (int k = 0; k < kMaxD; ++k)
+    if (k + 1 == int(blockIdx.y)) {
+      const GPtr<T> src = (GPtr<T>)a.U[k];
+      const size_t total = size_t(a.n[k]) * size_t(a.rcap[k]);
+      const size_t valid = size_t(a.n[k]) * size_t(min(r[k], a.rc));
+      for (size_t e = e0; e < total; e += step) a.out_U[k][e] = e < valid ? double(src[e]) : 0.0;
+    }
+}
+
 template <typename T>
 __global__ void core_recap_kernel(const T* __restrict__ src, Dims4 sd, Dims4 sv, T* __restrict__ dst, Dims4 dd,
                                   int d, size_t total) {
@@ -405,6 +503,37 @@ void cast_copy(const A* x, B* y, size_t len, hipStream_t st) {
   TK_LAUNCH_CHECK();
 }
 
+template <typename S, typename D>
+void move_parts(const MoveTask<S, D>* tasks_d, int ntasks, size_t maxtotal, hipStream_t st) {
+  if (ntasks <= 0 || maxtotal == 0) return;
+  const unsigned gx = unsigned(std::min<size_t>((maxtotal + 1023) / 1024, 512));  // about 4 elements a thread
+  hipLaunchKernelGGL((move_parts_kernel<S, D>), dim3(gx, ntasks), dim3(256), 0, st, tasks_d);
+  TK_LAUNCH_CHECK();
+}
+
+template <typename S, typename D>
+void move_set(const MoveSet<S, D>& set, hipStream_t st) {
+  TK_CHECK(set.count >= 1 && set.count <= kMoveSet, kErrInvalidArg, "move_set: number of parts");
+  size_t mx = 1;
+  for (int i = 0; i < set.count; ++i) mx = std::max<size_t>(mx, set.t[i].total);
+  const unsigned gx = unsigned(std::min<size_t>((mx + 1023) / 1024, 512));
+  hipLaunchKernelGGL((move_set_kernel<S, D>), dim3(gx, set.count), dim3(256), 0, st, set);
+  TK_LAUNCH_CHECK();
+}
+
+template <typename T>
+void export_parts(const ExportArgs<T>& a, hipStream_t st) {
+  size_t mx = 1, core = 1;
+  for (int k = 0; k < a.d; ++k) {
+    core *= size_t(a.rcap[k]);
+    mx = std::max(mx, size_t(a.n[k]) * a.rcap[k]);
+  }
+  mx = std::max(mx, core);
+  const unsigned gx = unsigned(std::min<size_t>((mx + 1023) / 1024, 512));
+  hipLaunchKernelGGL((export_kernel<T>), dim3(gx, a.d + 1), dim3(256), 0, st, a);
+  TK_LAUNCH_CHECK();
+}
+
 template <typename T>
 void core_recap(const T* src, const int* sd, const int* sv, T* dst, const int* dd, int d, hipStream_t st) {
   Dims4 a{}, v{}, b{};
@@ -483,6 +612,12 @@ void sketch_width(const int* rt, int d, int p, int cap, int force, int* s_out, h
 TK_INST(double)
 TK_INST(float)
 #undef TK_INST
+template void move_parts<double, double>(const MoveTask<double, double>*, int, size_t, hipStream_t);
+template void move_parts<double, float>(const MoveTask<double, float>*, int, size_t, hipStream_t);
+template void move_parts<float, double>(const MoveTask<float, double>*, int, size_t, hipStream_t);
+template void move_set<double, double>(const MoveSet<double, double>&, hipStream_t);
+template void export_parts<double>(const ExportArgs<double>&, hipStream_t);
+template void export_parts<float>(const ExportArgs<float>&, hipStream_t);
 template void cast_copy<double, float>(const double*, float*, size_t, hipStream_t);
 template void cast_multi<double, float>(const CastSet<double, float>&, hipStream_t);
 template void cast_multi<float, double>(const CastSet<float, double>&, hipStream_t);

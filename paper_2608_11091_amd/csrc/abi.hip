@@ -874,7 +874,7 @@ int do_tikhonov(const double* M, const double* b, int s, int k, double lam_fixed
   if (ar.measuring()) return 0;
   TK_CHECK(M != nullptr && b != nullptr && y != nullptr && out != nullptr, kErrInvalidArg, "NULL argument");
   TK_HIP(hipMemcpyAsync(tab, &b, sizeof(b), hipMemcpyHostToDevice, st));
-  dot_batched<double>(tab, tab, size_t(s), 1, 1.0, bn2, st);
+  dot_batched<double>(tab, tab, size_t(s), 1, 1.0, bn2, nullptr, st);
   vec_sqrt(bn2, bn, 1, st);
   ls_init(ls, s, st);
   for (int j = 0; j < k; ++j) ls_add_column(ls, s, k, j, 0.0, 0.0, st);

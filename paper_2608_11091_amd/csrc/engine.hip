@@ -33,6 +33,7 @@ struct GemmDesc {
   const int* nb = nullptr;
   std::function<int(int)> ngroups_of;  // active groups as a function of *nb
   bool terms_are_blocks = false;       // clamp each group's terms to *nb
+  bool mixed = false;                  // groups were added with dims of their own (group_dims)
   bool factor_product = false;         // a product with a Tucker factor (BF16 in the BF16-factor form)
   // optional: the only consumer of C sums the split-K partials itself, which
   // saves the reduction launch (C is then not written); needs beta = 0,
@@ -40,12 +41,22 @@ struct GemmDesc {
   SplitOut<T>* split_out = nullptr;
 
   void group(T* C, const std::vector<GemmTerm<T>>& ts) {
-    GemmGroup<T> g;
+    GemmGroup<T> g{};
     g.C = C;
     g.t0 = int(terms.size());
     for (auto& t : ts) terms.push_back(t);
     g.t1 = int(terms.size());
     groups.push_back(g);
+  }
+  // dims of the group added last (a mixed launch: N is common)
+  void group_dims(int m, int k, int la, int lb, int lc) {
+    GemmGroup<T>& g = groups.back();
+    g.M = m;
+    g.K = k;
+    g.lda = la;
+    g.ldb = lb;
+    g.ldc = lc;
+    mixed = true;
   }
   void group1(T* C, const T* A, const T* B, const double* c1 = nullptr, const double* c2 = nullptr,
               const double* c3 = nullptr, double scale = 1.0) {
@@ -65,19 +76,46 @@ void emit_gemm(Seq& q, Planner& pl, GemmDesc<T>&& g) {
   const int ng = int(g.groups.size());
   int maxt = 1;
   for (auto& gr : g.groups) maxt = std::max(maxt, gr.t1 - gr.t0);
+  for (auto& gr : g.groups)
+    if (!g.mixed) {
+      gr.M = g.M;
+      gr.K = g.K;
+      gr.lda = g.lda;
+      gr.ldb = g.ldb;
+      gr.ldc = g.ldc;
+    } else {
+      g.M = std::max(g.M, gr.M);
+      g.K = std::max(g.K, gr.K);
+    }
   const long tiles = long(ceil_div(g.M, 64)) * ceil_div(g.N, 64) * ng;
-  const long slabs = long(maxt) * ceil_div(g.K, 16);  // in units of 16 of K
-  // Split-K for the path's small, long-K products: about 64 of K (two of the
-  // kernel's 32-deep slabs) per workgroup (measured on the path's shapes: a
+  const long slabs = long(maxt) * ceil_div(g.K, 32);
+  // Split-K for the path's small, long-K products.  With a reduction launch of
+  // its own (4 us) about two slabs per workgroup, from 8 slabs on (a
   // 48 x 53 x 512 product took 44.9 / 16.4 / 12.1 / 11.5 us at 1 / 4 / 8 / 16
-  // splits, kernel and reduction); products that already fill the chip or
-  // have little K run whole.
-  int splits = 1;
-  if (tiles < 256 && slabs >= 16) {
-    splits = int(std::min<long>(slabs / 4, std::max<long>(1, 512 / tiles)));
-    splits = std::max(1, std::min(splits, 32));
+  // splits, kernel and reduction).  Where the consumer sums the partials, one
+  // slab per workgroup up to 16, then two (a workgroup spends 2 us a slab: the
+  // 15 x 15 Gram of 15 slabs took 37 us whole); beyond 32 partials the
+  // consumer's one workgroup would read longer than it saves, so products with
+  // more than 8 slabs left per workgroup take up to 256 of them and a launch
+  // that folds the partials to 16.  Products that already fill the chip or have
+  // little K run whole.
+  int splits = 1, folds = 0;
+  if (tiles < 256) {
+    const long room = std::max<long>(1, 512 / tiles);
+    if (g.split_out) {
+      if (slabs > 256 && room >= 64) {
+        splits = int(std::min<long>({ceil_div(slabs, 4), room, 256}));
+        folds = 16;
+      } else if (slabs >= 2) {
+        splits = int(std::min<long>({slabs <= 16 ? slabs : std::max<long>(16, slabs / 2), room, 32}));
+      }
+    } else if (slabs >= 8) {
+      splits = int(std::min<long>({slabs / 2, room, 32}));
+    }
+    splits = std::max(1, splits);
   }
   T* partial = splits > 1 ? pl.ar.alloc<T>(size_t(ng) * splits * g.M * g.N) : nullptr;
+  T* folded = folds > 0 ? pl.ar.alloc<T>(size_t(ng) * folds * g.M * g.N) : nullptr;
   const size_t toff = pl.blob.add(g.terms), goff = pl.blob.add(g.groups);
   Blob* bl = &pl.blob;
   GemmLaunch<T> L;
@@ -100,15 +138,24 @@ void emit_gemm(Seq& q, Planner& pl, GemmDesc<T>&& g) {
     *g.split_out = SplitOut<T>{};
     if (splits > 1) {
       L.defer_reduce = true;
-      *g.split_out = SplitOut<T>{partial, splits, size_t(g.M) * g.N};
+      L.folds = folds;
+      L.folded = folded;
+      *g.split_out = SplitOut<T>{folds > 0 ? folded : partial, folds > 0 ? folds : splits, size_t(g.M) * g.N};
     }
   }
   const int* nb = g.nb;
   auto ngf = g.ngroups_of;
   const bool tb = g.terms_are_blocks;
+  L.mixed = g.mixed;
+  L.uniform_terms = maxt;
   std::vector<int> nterm;
-  for (auto& gr : g.groups) nterm.push_back(gr.t1 - gr.t0);
-  const double mnk2 = 2.0 * g.M * g.N * g.K;
+  std::vector<double> mnk2;
+  for (size_t i = 0; i < g.groups.size(); ++i) {
+    const auto& gr = g.groups[i];
+    nterm.push_back(gr.t1 - gr.t0);
+    mnk2.push_back(2.0 * gr.M * g.N * gr.K);
+    if (gr.t0 != int(i) * maxt || gr.t1 != gr.t0 + maxt) L.uniform_terms = 0;
+  }
   q.steps.push_back([=](hipStream_t st) {
     GemmLaunch<T> l = L;
     l.terms = bl->at<GemmTerm<T>>(toff);
@@ -119,7 +166,7 @@ void emit_gemm(Seq& q, Planner& pl, GemmDesc<T>&& g) {
     }
     if (timer_on(kKcGemm)) {
       double f = 0.0;
-      for (int i = 0; i < l.ngroups; ++i) f += mnk2 * std::min(nterm[i], l.max_terms);
+      for (int i = 0; i < l.ngroups; ++i) f += mnk2[i] * std::min(nterm[i], l.max_terms);
       l.flops = f;
     }
     gemm_run(l, st);
@@ -527,10 +574,11 @@ RoundSumOut<T> plan_roundsum(Seq& q, Planner& pl, const Shape& sh, const Blocks<
   bool any_force = false;
   for (int k = 0; k < d; ++k) any_force |= cfg.force_r[k] >= 0;
 
+  double* dws = dot_scratch(ar, corelen, nb);
   q.steps.push_back([=](hipStream_t st) {
     if (own_eps) TK_HIP(hipMemcpyAsync(const_cast<double*>(epsd), hp->ev, sizeof(hp->ev), hipMemcpyHostToDevice, st));
     if (any_force) TK_HIP(hipMemcpyAsync(force_dev, hp->force, sizeof(hp->force), hipMemcpyHostToDevice, st));
-    dot_batched<T>(bl->at<const T*>(off_cores), bl->at<const T*>(off_cores), corelen, nbA(), 1.0, sumsq, st);
+    dot_batched<T>(bl->at<const T*>(off_cores), bl->at<const T*>(off_cores), corelen, nbA(), 1.0, sumsq, dws, st);
     coef_weights_threshold(bl->at<const double*>(off_cptr), bl->at<double>(off_cscale), sumsq, nbA(), zero_tol, coef,
                            w, zthr, st);
   });
@@ -579,8 +627,9 @@ RoundSumOut<T> plan_roundsum(Seq& q, Planner& pl, const Shape& sh, const Blocks<
           const size_t off = blob.add(xs);
           const size_t len = size_t(n) * rc;
           double* out = fro + size_t(k) * nb;
+          double* fws = dot_scratch(ar, len, nb);
           q.steps.push_back([=](hipStream_t st) {
-            dot_batched<T>(bl->at<const T*>(off), bl->at<const T*>(off), len, nbA(), 1.0, out, st);
+            dot_batched<T>(bl->at<const T*>(off), bl->at<const T*>(off), len, nbA(), 1.0, out, fws, st);
           });
         }
       }
@@ -954,8 +1003,9 @@ RoundSumOut<T> plan_roundsum(Seq& q, Planner& pl, const Shape& sh, const Blocks<
     // total = ||C^||_F^2
     std::vector<const T*> pc = {Cb[0]};
     const size_t offc = blob.add(pc);
+    double* tws = dot_scratch(ar, sclen, 1);
     q.steps.push_back([=](hipStream_t st) {
-      dot_batched<T>(bl->at<const T*>(offc), bl->at<const T*>(offc), sclen, 1, 1.0, total, st);
+      dot_batched<T>(bl->at<const T*>(offc), bl->at<const T*>(offc), sclen, 1, 1.0, total, tws, st);
     });
   }
   T* G1 = ar.alloc<T>(size_t(d) * sc * sc);
@@ -1244,8 +1294,9 @@ void plan_inner(Seq& q, Planner& pl, const Shape& sh, const std::vector<TT<T>>& 
     b.push_back(cur + size_t(i) * corelen);
   }
   const size_t oa = pl.blob.add(a), ob = pl.blob.add(b);
+  double* dws = dot_scratch(pl.ar, corelen, np);
   q.steps.push_back([=](hipStream_t st) {
-    dot_batched<T>(bl->at<const T*>(oa), bl->at<const T*>(ob), corelen, np, scale, out, st);
+    dot_batched<T>(bl->at<const T*>(oa), bl->at<const T*>(ob), corelen, np, scale, out, dws, st);
   });
   if (grams_out)
     for (int i = 0; i < np; ++i)
@@ -1479,8 +1530,9 @@ void plan_exact_norm2(Seq& q, Planner& pl, const Shape& sh, const Blocks<double>
   const size_t corelen = size_t(ipow(Md, d));
   std::vector<const double*> pc = {core};
   const size_t offc = pl.blob.add(pc);
+  double* dws = dot_scratch(pl.ar, corelen, 1);
   q.steps.push_back([=](hipStream_t st) {
-    dot_batched<double>(bl->at<const double*>(offc), bl->at<const double*>(offc), corelen, 1, 1.0, out_norm2, st);
+    dot_batched<double>(bl->at<const double*>(offc), bl->at<const double*>(offc), corelen, 1, 1.0, out_norm2, dws, st);
   });
 }
 

@@ -170,6 +170,12 @@ template <typename T>
 void plan_gemm(Seq& q, Planner& pl, bool ta, bool tb, int M, int N, int K, const T* A, int lda, const T* B, int ldb,
                T* C, int ldc, double alpha, double beta, bool factor_product = false);
 
+// Scratch for dot_batched over n products of length len (nullptr: none needed).
+inline double* dot_scratch(Arena& ar, size_t len, int n) {
+  const int parts = dot_parts(len);
+  return parts > 1 ? ar.alloc<double>(size_t(n) * parts) : nullptr;
+}
+
 // C_i = alpha op(A_i) op(B_i) for equally shaped problems, one launch.
 template <typename T>
 void plan_gemm_batched(Seq& q, Planner& pl, bool ta, bool tb, int M, int N, int K, const std::vector<const T*>& A,

@@ -1,12 +1,18 @@
 // Grouped GEMM kernel on MFMA (v_mfma_f64_16x16x4f64 / v_mfma_f32_16x16x4f32).
 //
-// Tile: 64 x 64 outputs per workgroup of 256 threads (4 waves in a 2 x 2
-// arrangement), each wave owning a 32 x 32 sub-tile = 2 x 2 MFMA 16x16
-// accumulators so four independent MFMA chains hide the pipeline latency.
-// K is staged through LDS in slabs of 32 (16 in the bf16 form) with global
-// loads coalesced along the contiguous dimension of each operand; the alpha
-// of a term is folded into the A slab while it is staged.
+// Tile: 64 x 64 outputs per workgroup of 256 threads (4 waves).  A wave owns a
+// strip of 16 rows or 16 columns of the tile and up to four MFMA 16 x 16
+// accumulators along it; the strips run along the shorter live side, so a
+// product with 15, 32 or 37 columns issues 1, 2 or 3 MFMAs a step in place of
+// 4 (FP64 16x16x4: 64 cycles each on its SIMD).  K is staged through LDS in
+// slabs of 32 (16 in the bf16 form) with global loads coalesced along the
+// contiguous dimension of each operand; rows and k steps beyond the operands
+// are neither loaded nor multiplied, and the alpha of a term is folded into
+// the A slab while it is staged.
 #include "gemm.hpp"
+
+#include <type_traits>
+
 #include "kernels.hpp"
 
 namespace tk {
@@ -44,6 +50,15 @@ __device__ __forceinline__ f4 mfma_bf16(s4 a, s4 b, f4 c) {
 
 constexpr int BM = 64, BN = 64, NT = 256;
 
+// Whether a value that is the same in every lane is zero, as a scalar condition.
+__device__ __forceinline__ bool uniform_zero(float x) {
+  return (__builtin_amdgcn_readfirstlane(__float_as_int(x)) & 0x7fffffff) == 0;
+}
+__device__ __forceinline__ bool uniform_zero(double x) {
+  const int lo = __builtin_amdgcn_readfirstlane(__double2loint(x));
+  const int hi = __builtin_amdgcn_readfirstlane(__double2hiint(x));
+  return (lo | (hi & 0x7fffffff)) == 0;
+}
 
 // Split-K: the (term, K-slab) iteration space of a group is divided evenly
 // over `splits` workgroups per output tile; each writes its partial tile and a
@@ -54,7 +69,8 @@ template <typename T, bool TA, bool TB, bool BF = false>
 __global__ __launch_bounds__(NT) void gemm_kernel(int M, int N, int K, int lda, int ldb, int ldc,
                                                   const GemmTerm<T>* __restrict__ terms,
                                                   const GemmGroup<T>* __restrict__ groups, double beta,
-                                                  int splits, T* __restrict__ partial, int max_terms) {
+                                                  int splits, T* __restrict__ partial, size_t pstride,
+                                                  int max_terms, int uniform_terms, bool mixed) {
   static_assert(!BF || sizeof(T) == 4, "bf16 operands with FP32 storage only");
   // K depth of a slab: 32 (8 loads per operand and thread in flight at once,
   // half the slab iterations of a 16-deep slab on the path's short-K
@@ -62,150 +78,214 @@ __global__ __launch_bounds__(NT) void gemm_kernel(int M, int N, int K, int lda, 
   constexpr int KB = BF ? 16 : 32;
   constexpr int SA = (BM * KB) / NT, SB = (BN * KB) / NT;  // staged elements per thread
   constexpr int BKP = 16 + 4;  // bf16 row: 16 k values + 4 pad (40 bytes: conflict-free 8-byte reads)
-  __shared__ T As[BF ? 1 : KB][BM + 1];
-  __shared__ T Bs[BF ? 1 : KB][BN + 1];
+  static_assert(BM == BN, "one row length for both slabs");
+  __shared__ T slabs[2][BF ? 1 : KB][BM + 1];  // [A, B][k][m or n]
+  auto& As = slabs[0];
+  auto& Bs = slabs[1];
   __shared__ __align__(8) unsigned short Asb[BF ? BM : 1][BKP];  // [m][k]
   __shared__ __align__(8) unsigned short Bsb[BF ? BN : 1][BKP];  // [n][k]
   const int tid = threadIdx.x;
   const int lane = tid & 63;
-  const int wid = tid >> 6;
-  const int wm = wid & 1, wn = wid >> 1;
+  const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int m0 = blockIdx.x * BM, n0 = blockIdx.y * BN;
   const int g = blockIdx.z / splits;
   const int sp = blockIdx.z % splits;
+  // A launch of uniform groups knows its term range from the arguments, so the
+  // first term's record is not behind the group's.
   const GemmGroup<T> grp = groups[g];
+  int t0 = g * uniform_terms, t1 = t0 + uniform_terms;
+  if (uniform_terms == 0) {
+    t0 = grp.t0;
+    t1 = grp.t1;
+  }
+  if (mixed) {
+    M = grp.M;
+    K = grp.K;
+    lda = grp.lda;
+    ldb = grp.ldb;
+    ldc = grp.ldc;
+    if (m0 >= M) return;
+  }
 
   typedef typename Acc<T>::type AT;
-  AT acc[2][2];
+  AT acc[4];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < 4; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) acc[i][j][v] = T(0);
+    for (int v = 0; v < 4; ++v) acc[i][v] = T(0);
 
-  const int t1 = min(grp.t1, grp.t0 + max_terms);
-  const int nterm = max(0, t1 - grp.t0);
+  const int nterm = max(0, min(t1 - t0, max_terms));
   const int nks = (K + KB - 1) / KB;
   const int total = nterm * nks;
   const int per = (total + splits - 1) / splits;
   const int sb = sp * per, se = min(total, sb + per);
+  const int Ml = min(BM, M - m0), Nl = min(BN, N - n0);  // live rows and columns of the tile
+  const int mt = (Ml + 15) >> 4, nt = (Nl + 15) >> 4;
+  const bool by_rows = nt < mt;  // a wave owns 16 rows (else 16 columns) of the tile
+  const int live = by_rows ? (wid < mt ? nt : 0) : (wid < nt ? mt : 0);  // its accumulators
 
-  // staging coordinates of this thread (fixed over slabs)
-  int am[SA], ak[SA], bn[SB], bk[SB];
-#pragma unroll
-  for (int i = 0; i < SA; ++i) {
-    if (!TA) { am[i] = tid & 63; ak[i] = (tid >> 6) + 4 * i; }
-    else { ak[i] = tid % KB; am[i] = tid / KB + (NT / KB) * i; }
-  }
-#pragma unroll
-  for (int i = 0; i < SB; ++i) {
-    if (!TB) { bk[i] = tid % KB; bn[i] = tid / KB + (NT / KB) * i; }
-    else { bn[i] = tid & 63; bk[i] = (tid >> 6) + 4 * i; }
-  }
+  // staging coordinates of this thread (fixed over slabs): element i of A is
+  // row am0 + i * amd, k ak0 + i * akd of the slab
+  const int am0 = TA ? tid / KB : lane, ak0 = TA ? tid % KB : wid;
+  constexpr int amd = TA ? NT / KB : 0, akd = TA ? 0 : 4;
+  const int bn0 = TB ? lane : tid / KB, bk0 = TB ? wid : tid % KB;
+  constexpr int bnd = TB ? 0 : NT / KB, bkd = TB ? 4 : 0;
   // Slab s is fetched into registers one slab ahead of its use, so its global
-  // loads are in flight while the matrix cores work on slab s - 1.  The loads
-  // are unconditional (an out-of-range element reads element 0 of its live
-  // operand) and go through the global address space; the range test and the
-  // term's alpha are applied when the slab is staged into LDS: a select or a
+  // loads are in flight while the matrix cores work on slab s - 1; the record
+  // of the next term is fetched one term ahead, and a term's coefficients are
+  // first needed when its slab is staged.  The loads are unconditional up to
+  // halves of the slab (indices clamp to the operand) and go through the
+  // global address space; k steps beyond the operand become zeros and the
+  // term's alpha is applied when the slab is staged into LDS: a select or a
   // multiply right after a load, or a flat load (counted with the LDS
   // operations that every barrier waits for), would make the thread wait for
-  // that load before issuing the next.  A term with alpha == 0 stages zeros
-  // and reads neither operand.
-  int cur = -1;
-  T alpha = T(0);
-  T alpha_next = T(0);     // alpha of the fetched slab's term (uniform)
-  bool live_next = false;  // whether that alpha is nonzero (uniform)
-  const T* Ap = nullptr;
-  const T* Bp = nullptr;
+  // that load before issuing the next.  Rows and columns beyond the operands
+  // hold copies of the last one (or what the LDS held): they only reach
+  // accumulators that are not stored.  A term with alpha == 0 is not
+  // multiplied, whatever its operands hold.
+  int t = t0, kf = 0;  // term and k of the slab to fetch
+  GemmTerm<T> tm = {}, tn = {};
+  double c1 = 1.0, c2 = 1.0, c3 = 1.0, sc = 0.0;  // coefficients of the fetched slab's term
   T ra[SA], rb[SB];
-  auto fetch = [&](int slab) {
-    const int t = grp.t0 + slab / nks;
-    const int k0 = (slab % nks) * KB;
-    if (t != cur) {
-      const GemmTerm<T> tm = terms[t];
-      double al = tm.scale;
-      if (tm.c1) al *= *tm.c1;
-      if (tm.c2) al *= *tm.c2;
-      if (tm.c3) al *= *tm.c3;
-      alpha = T(al);
-      Ap = tm.A;
-      Bp = tm.B;
-      cur = t;
-    }
-    alpha_next = alpha;
-    live_next = alpha != T(0);
-    if (!live_next) return;
-    const GPtr<T> ga = (GPtr<T>)Ap;
-    const GPtr<T> gb = (GPtr<T>)Bp;
-#pragma unroll
-    for (int i = 0; i < SA; ++i) {
-      const int gm = m0 + am[i], gk = k0 + ak[i];
-      const size_t at = (gm < M && gk < K) ? (TA ? gk + (size_t)gm * lda : gm + (size_t)gk * lda) : 0;
-      ra[i] = ga[at];
-    }
-#pragma unroll
-    for (int i = 0; i < SB; ++i) {
-      const int gn = n0 + bn[i], gk = k0 + bk[i];
-      const size_t at = (gn < N && gk < K) ? (TB ? gn + (size_t)gk * ldb : gk + (size_t)gn * ldb) : 0;
-      rb[i] = gb[at];
-    }
+  auto coefs = [&]() {
+    sc = tm.scale;
+    c1 = tm.c1 ? *tm.c1 : 1.0;
+    c2 = tm.c2 ? *tm.c2 : 1.0;
+    c3 = tm.c3 ? *tm.c3 : 1.0;
   };
-  if (sb < se) fetch(sb);
+  auto load = [&]() {
+    const GPtr<T> ga = (GPtr<T>)tm.A;
+    const GPtr<T> gb = (GPtr<T>)tm.B;
+    const bool a2 = SA / 2 * amd < Ml && kf + SA / 2 * akd < K, b2 = SB / 2 * bnd < Nl && kf + SB / 2 * bkd < K;
+    auto la = [&](int i) {
+      const int gm = min(m0 + am0 + i * amd, M - 1), gk = min(kf + ak0 + i * akd, K - 1);
+      ra[i] = TA ? ga[gk + (size_t)gm * lda] : ga[gm + (size_t)gk * lda];
+    };
+    auto lb = [&](int i) {
+      const int gn = min(n0 + bn0 + i * bnd, N - 1), gk = min(kf + bk0 + i * bkd, K - 1);
+      rb[i] = TB ? gb[gn + (size_t)gk * ldb] : gb[gk + (size_t)gn * ldb];
+    };
+#pragma unroll
+    for (int i = 0; i < SA / 2; ++i) la(i);
+#pragma unroll
+    for (int i = 0; i < SB / 2; ++i) lb(i);
+    if (a2)
+#pragma unroll
+      for (int i = SA / 2; i < SA; ++i) la(i);
+    if (b2)
+#pragma unroll
+      for (int i = SB / 2; i < SB; ++i) lb(i);
+  };
+  if (sb < se) {
+    t = t0 + sb / nks;
+    kf = (sb - (t - t0) * nks) * KB;
+    tm = terms[t];
+    if (t + 1 < t0 + nterm) tn = terms[t + 1];
+    load();
+    coefs();
+  }
+  T alpha = T(0);
+  int ks = 0;  // k of the slab being staged
+  bool fresh = true;  // its term's coefficients have not been multiplied yet
   for (int slab = sb; slab < se; ++slab) {
+    ks = kf;
+    if (fresh) {
+      double al = sc;
+      al *= c1;
+      al *= c2;
+      al *= c3;
+      alpha = T(al);
+    }
+    auto next = [&]() {  // fetch the following slab
+      fresh = false;
+      if (slab + 1 >= se) return;
+      kf += KB;
+      if (kf >= K) {
+        kf = 0;
+        ++t;
+        tm = tn;
+        if (t + 1 < t0 + nterm) tn = terms[t + 1];
+        fresh = true;
+      }
+      load();
+      if (fresh) coefs();
+    };
     // a slab of a zero-coefficient term (e.g. a disabled Gram block) adds
-    // nothing: it is neither staged nor multiplied (the branch is uniform)
-    const bool lv = live_next;
-    const T al = alpha_next;
-    if (!lv) {
-      if (slab + 1 < se) fetch(slab + 1);
+    // nothing: it is neither staged nor multiplied
+    if (uniform_zero(alpha)) {
+      next();
       continue;
     }
-    const int k0 = (slab % nks) * KB;
-    T va[SA], vb[SB];
-#pragma unroll
-    for (int i = 0; i < SA; ++i) va[i] = (m0 + am[i] < M && k0 + ak[i] < K) ? ra[i] * al : T(0);
-#pragma unroll
-    for (int i = 0; i < SB; ++i) vb[i] = (n0 + bn[i] < N && k0 + bk[i] < K) ? rb[i] : T(0);
+    const int kl = K - ks;  // live k of the slab
     if constexpr (BF) {
 #pragma unroll
-      for (int i = 0; i < SA; ++i) Asb[am[i]][ak[i]] = bf16_rne(float(va[i]));
+      for (int i = 0; i < SA; ++i)
+        Asb[am0 + i * amd][ak0 + i * akd] =
+            bf16_rne(float(ak0 + i * akd < kl ? ra[i] * alpha : T(0)));
 #pragma unroll
-      for (int i = 0; i < SB; ++i) Bsb[bn[i]][bk[i]] = bf16_rne(float(vb[i]));
+      for (int i = 0; i < SB; ++i)
+        Bsb[bn0 + i * bnd][bk0 + i * bkd] =
+            bf16_rne(float(bk0 + i * bkd < kl ? rb[i] : T(0)));
     } else {
+      auto sa = [&](int i) { As[ak0 + i * akd][am0 + i * amd] = ak0 + i * akd < kl ? ra[i] * alpha : T(0); };
+      auto sb_ = [&](int i) { Bs[bk0 + i * bkd][bn0 + i * bnd] = bk0 + i * bkd < kl ? rb[i] : T(0); };
 #pragma unroll
-      for (int i = 0; i < SA; ++i) As[ak[i]][am[i]] = va[i];
+      for (int i = 0; i < SA / 2; ++i) sa(i);
 #pragma unroll
-      for (int i = 0; i < SB; ++i) Bs[bk[i]][bn[i]] = vb[i];
+      for (int i = 0; i < SB / 2; ++i) sb_(i);
+      if (SA / 2 * amd < Ml && SA / 2 * akd < kl)
+#pragma unroll
+        for (int i = SA / 2; i < SA; ++i) sa(i);
+      if (SB / 2 * bnd < Nl && SB / 2 * bkd < kl)
+#pragma unroll
+        for (int i = SB / 2; i < SB; ++i) sb_(i);
     }
     __syncthreads();
-    if (slab + 1 < se) fetch(slab + 1);
+    next();
     if constexpr (BF) {
       // the whole 16-deep slab in one MFMA per 16 x 16 output tile
-      const int kq = 4 * (lane >> 4);
-      s4 a[2], b[2];
+      const int kq = 4 * (lane >> 4), c = lane & 15;
+      if (by_rows) {
+        const s4 a = *reinterpret_cast<const s4*>(&Asb[wid * 16 + c][kq]);
 #pragma unroll
-      for (int i = 0; i < 2; ++i) a[i] = *reinterpret_cast<const s4*>(&Asb[wm * 32 + i * 16 + (lane & 15)][kq]);
+        for (int j = 0; j < 4; ++j)
+          if (j < live) acc[j] = mfma_bf16(a, *reinterpret_cast<const s4*>(&Bsb[j * 16 + c][kq]), acc[j]);
+      } else {
+        const s4 b = *reinterpret_cast<const s4*>(&Bsb[wid * 16 + c][kq]);
 #pragma unroll
-      for (int j = 0; j < 2; ++j) b[j] = *reinterpret_cast<const s4*>(&Bsb[wn * 32 + j * 16 + (lane & 15)][kq]);
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = mfma_bf16(a[i], b[j], acc[i][j]);
-    } else {
-#pragma unroll
-      for (int kk = 0; kk < KB; kk += 4) {
-        const int kr = kk + (lane >> 4);
-        T a[2], b[2];
-#pragma unroll
-        for (int i = 0; i < 2; ++i) a[i] = As[kr][wm * 32 + i * 16 + (lane & 15)];
-#pragma unroll
-        for (int j = 0; j < 2; ++j) b[j] = Bs[kr][wn * 32 + j * 16 + (lane & 15)];
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-          for (int j = 0; j < 2; ++j) acc[i][j] = mfma(a[i], b[j], acc[i][j]);
+        for (int j = 0; j < 4; ++j)
+          if (j < live) acc[j] = mfma_bf16(*reinterpret_cast<const s4*>(&Asb[j * 16 + c][kq]), b, acc[j]);
       }
+    } else {
+      // strip operand x (one 16-wide strip) against y (`live` strips)
+      const auto& xs = slabs[by_rows ? 0 : 1];
+      const auto& ys = slabs[by_rows ? 1 : 0];
+      auto strips = [&](auto lv, auto rows) {
+        constexpr int LV = decltype(lv)::value;
+        auto half = [&](int k0) {
+#pragma unroll
+          for (int kk = 0; kk < 16; kk += 4) {
+            const int kr = k0 + kk + (lane >> 4), c = lane & 15;
+            const T x = xs[kr][wid * 16 + c];
+            T y[LV];
+#pragma unroll
+            for (int j = 0; j < LV; ++j) y[j] = ys[kr][j * 16 + c];
+#pragma unroll
+            for (int j = 0; j < LV; ++j)
+              acc[j] = decltype(rows)::value ? mfma(x, y[j], acc[j]) : mfma(y[j], x, acc[j]);
+          }
+        };
+        half(0);
+        if (kl > 16) half(16);
+      };
+      auto sized = [&](auto rows) {
+        if (live == 4) strips(std::integral_constant<int, 4>{}, rows);
+        else if (live == 3) strips(std::integral_constant<int, 3>{}, rows);
+        else if (live == 2) strips(std::integral_constant<int, 2>{}, rows);
+        else if (live == 1) strips(std::integral_constant<int, 1>{}, rows);
+      };
+      if (by_rows) sized(std::true_type{});
+      else sized(std::false_type{});
     }
     __syncthreads();
   }
@@ -214,35 +294,61 @@ __global__ __launch_bounds__(NT) void gemm_kernel(int M, int N, int K, int lda, 
   // sits in lane c + 16*(r/4), element r%4; for FP64 in lane c + 16*(r%4),
   // element r/4.
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
+  for (int j = 0; j < 4; ++j)
+    if (j < live) {
+      const int ti = by_rows ? wid : j, tj = by_rows ? j : wid;
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const int r16 = Acc<T>::f64 ? 4 * v + (lane >> 4) : 4 * (lane >> 4) + v;
-        const int row = m0 + wm * 32 + i * 16 + r16;
-        const int col = n0 + wn * 32 + j * 16 + (lane & 15);
+        const int row = m0 + ti * 16 + r16;
+        const int col = n0 + tj * 16 + (lane & 15);
         if (row < M && col < N) {
           if (splits == 1) {
             T* c = grp.C + row + (size_t)col * ldc;
-            *c = (beta == 0.0) ? acc[i][j][v] : T(beta) * (*c) + acc[i][j][v];
+            *c = (beta == 0.0) ? acc[j][v] : T(beta) * (*c) + acc[j][v];
           } else {
-            partial[((size_t)blockIdx.z * N + col) * M + row] = acc[i][j][v];
+            partial[(size_t)blockIdx.z * pstride + (size_t)col * M + row] = acc[j][v];
           }
         }
       }
+    }
+}
+
+// Sums the partials of every group into `folds` of them.  A chunk's partials are summed in order, 16 loads in flight.
+template <typename T>
+__global__ __launch_bounds__(256) void splitk_fold(size_t MN, int splits, int folds, const T* __restrict__ partial,
+                                                   T* __restrict__ out) {
+  const int per = (splits + folds - 1) / folds;
+  const int s0 = blockIdx.y * per, s1 = min(splits, s0 + per);
+  const size_t e = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
+  if (e >= MN) return;
+  const GPtr<T> p = (GPtr<T>)(partial + (size_t)blockIdx.z * splits * MN + e);
+  T a = T(0);
+  for (int s = s0; s < s1; s += 16) {
+    T v[16];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) v[u] = p[size_t(min(s + u, s1 - 1)) * MN];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) a += s + u < s1 ? v[u] : T(0);
+  }
+  out[((size_t)blockIdx.z * folds + blockIdx.y) * MN + e] = a;
 }
 
 template <typename T>
 __global__ void splitk_reduce(int M, int N, int ldc, const GemmGroup<T>* __restrict__ groups, double beta,
-                              int splits, const T* __restrict__ partial) {
+                              int splits, const T* __restrict__ partial, size_t pstride, bool mixed) {
   const int g = blockIdx.y;
-  const size_t MN = (size_t)M * N;
-  for (size_t e = blockIdx.x * (size_t)blockDim.x + threadIdx.x; e < MN; e += (size_t)gridDim.x * blockDim.x) {
+  const GemmGroup<T> grp = groups[g];
+  if (mixed) {
+    M = grp.M;
+    ldc = grp.ldc;
+  }
+  const unsigned MN = unsigned(M) * unsigned(N);
+  for (unsigned e = blockIdx.x * blockDim.x + threadIdx.x; e < MN; e += gridDim.x * blockDim.x) {
     T s = T(0);
-    for (int sp = 0; sp < splits; ++sp) s += partial[((size_t)g * splits + sp) * MN + e];
-    const int row = int(e % M), col = int(e / M);
-    T* c = groups[g].C + row + (size_t)col * ldc;
+    for (int sp = 0; sp < splits; ++sp) s += partial[((size_t)g * splits + sp) * pstride + e];
+    const int row = int(e % unsigned(M)), col = int(e / unsigned(M));
+    T* c = grp.C + row + (size_t)col * ldc;
     *c = (beta == 0.0) ? s : T(beta) * (*c) + s;
   }
 }
@@ -254,12 +360,14 @@ void gemm_run(const GemmLaunch<T>& g, hipStream_t st) {
   if (g.ngroups <= 0 || g.M <= 0 || g.N <= 0) return;
   dim3 grid(ceil_div(g.M, BM), ceil_div(g.N, BN), g.ngroups * g.splits);
   T* part = g.splits > 1 ? g.partial : nullptr;
+  const size_t pstride = (size_t)g.M * g.N;
   timer_begin(kKcGemm, st, g.flops);
   TK_CHECK(!g.bf16 || sizeof(T) == 4, kErrUnsupported, "bf16 operands need FP32 storage");
 #define TK_GEMM_CASE(TA, TB, BF)                                                                          \
   if (g.ta == TA && g.tb == TB && g.bf16 == BF)                                                            \
     hipLaunchKernelGGL((gemm_kernel<T, TA, TB, BF && sizeof(T) == 4>), grid, dim3(NT), 0, st, g.M, g.N, g.K, \
-                       g.lda, g.ldb, g.ldc, g.terms, g.groups, g.beta, g.splits, part, g.max_terms);
+                       g.lda, g.ldb, g.ldc, g.terms, g.groups, g.beta, g.splits, part, pstride, g.max_terms,        \
+                       g.uniform_terms, g.mixed);
   TK_GEMM_CASE(false, false, false)
   TK_GEMM_CASE(false, true, false)
   TK_GEMM_CASE(true, false, false)
@@ -272,10 +380,17 @@ void gemm_run(const GemmLaunch<T>& g, hipStream_t st) {
   }
 #undef TK_GEMM_CASE
   TK_LAUNCH_CHECK();
+  if (g.folds > 0) {
+    TK_CHECK(g.defer_reduce && g.folded != nullptr && g.splits > 1 && g.ngroups <= 65535, kErrInvalidArg,
+             "internal: folded partials need a deferred reduction");
+    dim3 fg((unsigned)((pstride + 255) / 256), g.folds, g.ngroups);
+    hipLaunchKernelGGL((splitk_fold<T>), fg, dim3(256), 0, st, pstride, g.splits, g.folds, part, g.folded);
+    TK_LAUNCH_CHECK();
+  }
   if (g.splits > 1 && !g.defer_reduce) {
-    const size_t MN = (size_t)g.M * g.N;
-    dim3 rg((unsigned)std::min<size_t>((MN + 255) / 256, 64), g.ngroups);
-    hipLaunchKernelGGL((splitk_reduce<T>), rg, dim3(256), 0, st, g.M, g.N, g.ldc, g.groups, g.beta, g.splits, part);
+    dim3 rg((unsigned)std::min<size_t>((pstride + 255) / 256, 64), g.ngroups);
+    hipLaunchKernelGGL((splitk_reduce<T>), rg, dim3(256), 0, st, g.M, g.N, g.ldc, g.groups, g.beta, g.splits, part,
+                       pstride, g.mixed);
     TK_LAUNCH_CHECK();
   }
   timer_end(kKcGemm, st);

@@ -2,7 +2,8 @@
 //
 // One launch computes, for every group g,
 //     C_g = beta * C_g + sum_{t in terms(g)} alpha_t * op(A_t) * op(B_t)
-// with column-major operands of uniform shape M x N x K.  alpha_t is
+// with column-major operands, of uniform shape M x N x K unless the launch is
+// mixed.  alpha_t is
 // scale_t * (*c1_t) * (*c2_t) * (*c3_t) with optional device scalars, so
 // device-resident coefficients (inner products, least-squares solutions,
 // block weights) scale terms without a host round trip.  Term and group
@@ -27,9 +28,10 @@ template <typename T>
 struct GemmGroup {
   T* C;
   int t0, t1;  // term range [t0, t1)
+  int M, K, lda, ldb, ldc;  // read when the launch is mixed
 };
 
-// Launch descriptor: uniform dims/transposes, device tables.
+// Launch descriptor: uniform transposes and N, device tables.
 template <typename T>
 struct GemmLaunch {
   bool ta = false, tb = false;
@@ -40,6 +42,10 @@ struct GemmLaunch {
   double beta = 0.0;
   int splits = 1;          // split of the (term x K-slab) space (>1 uses `partial` + a reduction pass)
   T* partial = nullptr;    // ngroups * splits * M * N
+  T* folded = nullptr;     // folds > 0: the deferred partials are first summed into folds of them here
+  int folds = 0;           // (ngroups * folds * M * N)
+  int uniform_terms = 0;   // > 0: group g has the terms [g u, (g + 1) u)
+  bool mixed = false;      // groups have their own M, K, lda, ldb, ldc (M, K above: the largest)
   int max_terms = 1 << 30; // clamp every group to its first max_terms terms
   bool bf16 = false;       // FP32 storage: round the operands to bfloat16, BF16 matrix cores, FP32 accumulation
   bool defer_reduce = false;  // splits > 1: leave the partials for the consumer to sum (C is not written)

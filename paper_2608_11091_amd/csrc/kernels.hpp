@@ -43,8 +43,12 @@ void sumsq_batched(const T* base, size_t stride, size_t len, int n, double* out,
 void block_weights(const double* coef, const double* sumsq, int n, double* w, hipStream_t st);
 // out[i] = scale_i * sum_e x_i[e] * y_i[e]; x_i = xs[i], y_i = ys[i] (device pointer tables).
 template <typename T>
-void dot_batched(const T* const* xs, const T* const* ys, size_t len, int n, double scale, double* out,
+void dot_batched(const T* const* xs, const T* const* ys, size_t len, int n, double scale, double* out, double* part,
                  hipStream_t st);
+// `part` of dot_batched: n * dot_parts(len) doubles of scratch (nullptr: one
+// workgroup per product, whatever its length).
+constexpr int kDotParts = 64;
+int dot_parts(size_t len);
 
 // Batched moves between caller tensors and internal buffers (one launch for
 // every part of every tensor of a call), converting S to D on the way.

@@ -415,7 +415,7 @@ MlnSolverPtr make_mln_solver(Arena& ar, const Shape& sh, const OpDev<double>& op
     s.setup.steps.push_back([=](hipStream_t st) {
       scale_copy<double>(d0, bsv, size_t(rt), 1.0, be, nullptr, st);
       ls_init(lsv, rt, st);
-      dot_batched<double>(bl->at<const double*>(o2), bl->at<const double*>(o2), size_t(rt), 1, 1.0, n2, st);
+      dot_batched<double>(bl->at<const double*>(o2), bl->at<const double*>(o2), size_t(rt), 1, 1.0, n2, nullptr, st);
       vec_sqrt(n2, n1, 1, st);
     });
     ar.rewind(mk);

@@ -142,8 +142,9 @@ struct Cycle {
       std::vector<const T*> pc = {rhs.core};
       const size_t off = pl.blob.add(pc);
       const size_t cl = sh.core_len();
+      double* dws = dot_scratch(ar, cl, 1);
       setup.steps.push_back([=](hipStream_t st) {
-        dot_batched<T>(bl->at<const T*>(off), bl->at<const T*>(off), cl, 1, 1.0, beta2, st);
+        dot_batched<T>(bl->at<const T*>(off), bl->at<const T*>(off), cl, 1, 1.0, beta2, dws, st);
         vec_sqrt(beta2, beta, 1, st);
       });
       emit_copy_tt<T>(setup, sh, rhs, V[0], 1.0, beta);
@@ -167,7 +168,7 @@ struct Cycle {
         std::vector<const double*> pv = {bs};
         const size_t o2 = pl.blob.add(pv);
         setup.steps.push_back([=](hipStream_t st) {
-          dot_batched<double>(bl->at<const double*>(o2), bl->at<const double*>(o2), size_t(ss), 1, 1.0, n2, st);
+          dot_batched<double>(bl->at<const double*>(o2), bl->at<const double*>(o2), size_t(ss), 1, 1.0, n2, nullptr, st);
           vec_sqrt(n2, n1, 1, st);
         });
       }
@@ -230,8 +231,9 @@ struct Cycle {
       IterStatus* sd = st_dev;
       int* fl = flags;
       double* hcol = Mcols + size_t(k) * lr;
+      double* dws = dot_scratch(ar, cl, 2);
       q.steps.push_back([=](hipStream_t st) {
-        dot_batched<T>(bl->at<const T*>(off), bl->at<const T*>(off), cl, 2, 1.0, s2, st);
+        dot_batched<T>(bl->at<const T*>(off), bl->at<const T*>(off), cl, 2, 1.0, s2, dws, st);
         if (fa) {
           // Alg. 1: Hessenberg column (h_{1..k}, ||W||) in place of the sketch
           hess_column(hk, k + 1, s2 + 1, hcol, ss, st);
@@ -401,9 +403,10 @@ SolverPtr make_solver(Arena& ar, const Shape& sh, const OpDev<double>& op, const
     const size_t off = s.blob.add(pc);
     const size_t cl = sh.core_len();
     double* bn = s.bnorm2;
+    double* dws = dot_scratch(ar, cl, 1);
     s.s_setup.steps.push_back([=](hipStream_t st) {
       copy_ints(br, bor, d, st);
-      dot_batched<double>(bl->at<const double*>(off), bl->at<const double*>(off), cl, 1, 1.0, bn, st);
+      dot_batched<double>(bl->at<const double*>(off), bl->at<const double*>(off), cl, 1, 1.0, bn, dws, st);
     });
   }
 

@@ -113,54 +113,79 @@ __global__ void weights_kernel(const double* coef, const double* sumsq, int n, d
   if (i < n) w[i] = fabs(coef ? coef[i] : 1.0) * sqrt(sumsq[i]);
 }
 
-// One workgroup per dot product; 16-byte loads, four independent
-// accumulators per thread so that a wave keeps several loads in flight.
+// Dot products, `parts` workgroups each; 16-byte loads, eight in flight per
+// thread.  One CU reads about 50 GB/s, so a long product is spread: workgroup c
+// of a product takes the elements [c, c + 1) * chunk and leaves a partial sum
+// that dot_sum_kernel adds in order.
 template <typename T> struct Vec16;
-template <> struct Vec16<float> { using V = float4; static constexpr int W = 4; };
-template <> struct Vec16<double> { using V = double2; static constexpr int W = 2; };
+template <> struct Vec16<float> { typedef float V __attribute__((ext_vector_type(4))); static constexpr int W = 4; };
+template <> struct Vec16<double> { typedef double V __attribute__((ext_vector_type(2))); static constexpr int W = 2; };
 
 template <typename T>
 __device__ __forceinline__ double vdot(const typename Vec16<T>::V& a, const typename Vec16<T>::V& b);
 template <>
-__device__ __forceinline__ double vdot<float>(const float4& a, const float4& b) {
+__device__ __forceinline__ double vdot<float>(const Vec16<float>::V& a, const Vec16<float>::V& b) {
   return double(a.x) * double(b.x) + double(a.y) * double(b.y) + double(a.z) * double(b.z) + double(a.w) * double(b.w);
 }
 template <>
-__device__ __forceinline__ double vdot<double>(const double2& a, const double2& b) {
+__device__ __forceinline__ double vdot<double>(const Vec16<double>::V& a, const Vec16<double>::V& b) {
   return a.x * b.x + a.y * b.y;
 }
 
 constexpr int DOT_NT = 1024;
 
 template <typename T>
-__global__ __launch_bounds__(DOT_NT) void dot_kernel(const T* const* xs, const T* const* ys, size_t len, double scale,
-                                                     double* out) {
+__global__ __launch_bounds__(DOT_NT) void dot_kernel(const T* const* xs, const T* const* ys, size_t len, size_t chunk,
+                                                     double scale, double* out) {
   __shared__ double red[DOT_NT / kWave];
   using V = typename Vec16<T>::V;
   constexpr int W = Vec16<T>::W;
-  const T* x = xs[blockIdx.x];
-  const T* y = ys[blockIdx.x];
-  double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
+  const size_t at = blockIdx.x * chunk;
+  const T* x = xs[blockIdx.y] + at;
+  const T* y = ys[blockIdx.y] + at;
+  const size_t n = min(chunk, len - at);
+  double a[4] = {0.0, 0.0, 0.0, 0.0};
   size_t head = 0;
   if (((reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(y)) & 15) == 0) {
-    const V* xv = reinterpret_cast<const V*>(x);
-    const V* yv = reinterpret_cast<const V*>(y);
-    const size_t nv = len / W;
+    const GPtr<V> xv = (GPtr<V>)x;
+    const GPtr<V> yv = (GPtr<V>)y;
+    const size_t nv = n / W;
     size_t e = threadIdx.x;
-    for (; e + 3 * DOT_NT < nv; e += 4 * DOT_NT) {
-      const V x0 = xv[e], x1 = xv[e + DOT_NT], x2 = xv[e + 2 * DOT_NT], x3 = xv[e + 3 * DOT_NT];
-      const V y0 = yv[e], y1 = yv[e + DOT_NT], y2 = yv[e + 2 * DOT_NT], y3 = yv[e + 3 * DOT_NT];
-      a0 += vdot<T>(x0, y0);
-      a1 += vdot<T>(x1, y1);
-      a2 += vdot<T>(x2, y2);
-      a3 += vdot<T>(x3, y3);
+    if (x == y) {  // a squared norm reads its array once
+      for (; e + 7 * DOT_NT < nv; e += 8 * DOT_NT) {
+        V v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = xv[e + u * DOT_NT];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) a[u & 3] += vdot<T>(v[u], v[u]);
+      }
     }
-    for (; e < nv; e += DOT_NT) a0 += vdot<T>(xv[e], yv[e]);
+    for (; e + 3 * DOT_NT < nv; e += 4 * DOT_NT) {
+      V v[4], w[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[u] = xv[e + u * DOT_NT];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) w[u] = yv[e + u * DOT_NT];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) a[u] += vdot<T>(v[u], w[u]);
+    }
+    for (; e < nv; e += DOT_NT) {
+      const V v = xv[e], w = yv[e];
+      a[0] += vdot<T>(v, w);
+    }
     head = nv * W;
   }
-  for (size_t e = head + threadIdx.x; e < len; e += DOT_NT) a1 += double(x[e]) * double(y[e]);
-  const double sum = block_sum((a0 + a1) + (a2 + a3), red);
-  if (threadIdx.x == 0) out[blockIdx.x] = scale * sum;
+  for (size_t e = head + threadIdx.x; e < n; e += DOT_NT) a[1] += double(x[e]) * double(y[e]);
+  const double sum = block_sum((a[0] + a[1]) + (a[2] + a[3]), red);
+  if (threadIdx.x == 0) out[blockIdx.y * gridDim.x + blockIdx.x] = scale * sum;
+}
+
+// Adds the partial sums of one product, up to kDotParts of them, in order of a
+// tree over the lanes.
+__global__ __launch_bounds__(kWave) void dot_sum_kernel(const double* part, int parts, double scale, double* out) {
+  const int l = threadIdx.x;
+  const double v = wave_sum(l < parts ? part[size_t(blockIdx.x) * parts + l] : 0.0);
+  if (l == 0) out[blockIdx.x] = scale * v;
 }
 
 template <typename T>
@@ -455,12 +480,27 @@ void block_weights(const double* coef, const double* sumsq, int n, double* w, hi
   TK_LAUNCH_CHECK();
 }
 
+// A second launch costs 4 us and more, a single workgroup 1 us per 8 K
+// elements (FP64): spread from 64 K elements on (three squared norms of 110 K
+// elements 16.6 us in one workgroup each, FP64; one of 1.9 M elements 216 us).
+int dot_parts(size_t len) {
+  if (len < 65536) return 1;
+  return int(std::min<size_t>(kDotParts, len / 8192));
+}
+
 template <typename T>
-void dot_batched(const T* const* xs, const T* const* ys, size_t len, int n, double scale, double* out,
+void dot_batched(const T* const* xs, const T* const* ys, size_t len, int n, double scale, double* out, double* part,
                  hipStream_t st) {
   if (n <= 0) return;
-  hipLaunchKernelGGL((dot_kernel<T>), dim3(n), dim3(DOT_NT), 0, st, xs, ys, len, scale, out);
+  const int parts = part != nullptr ? dot_parts(len) : 1;
+  const size_t chunk = ((len + parts - 1) / parts + 3) / 4 * 4;  // keeps the 16-byte alignment
+  hipLaunchKernelGGL((dot_kernel<T>), dim3(parts, n), dim3(DOT_NT), 0, st, xs, ys, len, parts == 1 ? len : chunk,
+                     parts == 1 ? scale : 1.0, parts == 1 ? out : part);
   TK_LAUNCH_CHECK();
+  if (parts > 1) {
+    hipLaunchKernelGGL(dot_sum_kernel, dim3(n), dim3(kWave), 0, st, part, parts, scale, out);
+    TK_LAUNCH_CHECK();
+  }
 }
 
 template <typename T>
@@ -600,7 +640,7 @@ void sketch_width(const int* rt, int d, int p, int cap, int force, int* s_out, h
 #define TK_INST(T)                                                                                         \
   template void krp_reduce<T>(const KrpTask<T>*, int, int, const int*, int, int, hipStream_t);             \
   template void sumsq_batched<T>(const T*, size_t, size_t, int, double*, hipStream_t);                     \
-  template void dot_batched<T>(const T* const*, const T* const*, size_t, int, double, double*, hipStream_t); \
+  template void dot_batched<T>(const T* const*, const T* const*, size_t, int, double, double*, double*, hipStream_t); \
   template void scale_copy<T>(const T*, T*, size_t, double, const double*, const double*, hipStream_t);    \
   template void fill<T>(T*, size_t, T, hipStream_t);                                                       \
   template void core_recap<T>(const T*, const int*, const int*, T*, const int*, int, hipStream_t);         \

@@ -14,6 +14,8 @@
 #include <cstdint>
 #include <cstdio>
 #include <string>
+#include <type_traits>
+#include <utility>
 #include <vector>
 
 namespace tk {
@@ -124,6 +126,16 @@ __device__ __forceinline__ double dpp_mov(double v) {
   const unsigned lo = unsigned(__builtin_amdgcn_mov_dpp(int(b), CTRL, 0xF, 0xF, true));
   const unsigned hi = unsigned(__builtin_amdgcn_mov_dpp(int(b >> 32), CTRL, 0xF, 0xF, true));
   return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
+// f(std::integral_constant<int, 0>) .. f(std::integral_constant<int, N - 1>).
+template <typename F, int... I>
+__device__ __forceinline__ void for_constants_of(F& f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ void for_constants(F& f) {
+  for_constants_of(f, std::make_integer_sequence<int, N>{});
 }
 
 // Sum over the 64 lanes of a wave (all lanes active); every lane gets the

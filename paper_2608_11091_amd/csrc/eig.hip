@@ -16,6 +16,7 @@
 // effective rank / ST-HOSVD truncation) runs on the sorted spectrum.
 #include <cfloat>
 
+#include "chol.hpp"
 #include "kernels.hpp"
 
 namespace tk {
@@ -1018,12 +1019,9 @@ __global__ __launch_bounds__(1024) void jacobi_osj_kernel(const EigTask<T>* __re
 }
 
 // Rank certificate of the effective-rank rule, one workgroup per mode (the
-// statement is next to its declaration).  The Cholesky factorisation of
-// H - theta I follows the right-looking form of the Cholesky-QR kernel: every
-// thread reads the pivot after the step's barrier, so all threads stop at the
-// same failed pivot; lane j owns column j of the trailing update and the
-// waves stride over its rows.
-constexpr int CERT_NT = 256;
+// statement is next to its declaration): the Cholesky factorisation of
+// H - theta I (chol_rows), which stops at the first failed pivot.
+constexpr int CERT_NT = kCholWaves * kWave;
 constexpr int CERT_MAX = 64;
 
 // certificates tried and passed since the library was loaded (per device)
@@ -1034,13 +1032,12 @@ __global__ __launch_bounds__(CERT_NT) void rank_cert_kernel(const T* __restrict_
                                                             const double* __restrict__ fro, int nb_act,
                                                             const double* __restrict__ tau_dev, CertParams cp,
                                                             int* __restrict__ cert, int* __restrict__ rt) {
-  constexpr int NW = CERT_NT / kWave;
-  __shared__ double G[CERT_MAX][CERT_MAX + 1];
-  __shared__ double red[NW];
+  __shared__ double row_s[2][kCholWaves][kWave];
+  __shared__ double red[kCholWaves];
   const int k = blockIdx.x;
   const int tid = threadIdx.x;
   const int lane = tid & (kWave - 1);
-  const int wave = tid / kWave;
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
   const int m = cp.cap;
   const int nb = min(cp.nb, nb_act);
   double part = 0.0;
@@ -1049,25 +1046,17 @@ __global__ __launch_bounds__(CERT_NT) void rank_cert_kernel(const T* __restrict_
   const double tau = *tau_dev;
   const double theta = (4.0 * fmax(cp.delta, tau * tau) + cp.rnd[k]) * tr;
   const T* Hk = H + (size_t)k * m * m;
-  for (int e = tid; e < m * m; e += CERT_NT) {
-    const int i = e % m, j = e / m;
-    G[i][j] = double(Hk[i + (size_t)j * m]) - (i == j ? theta : 0.0);
+  // row i from column i of the symmetric H: contiguous over the lanes
+  double a[kCholRows];
+#pragma unroll
+  for (int r = 0; r < kCholRows; ++r) {
+    const int i = wave + kCholWaves * r;
+    a[r] = double(((GPtr<T>)Hk)[min(lane, m - 1) + (size_t)min(i, m - 1) * m]) - (i == lane ? theta : 0.0);
   }
-  __syncthreads();
   bool ok = tr > 0.0 && tr < INFINITY;  // the same in every thread
-  const int j = lane;
-  for (int kk = 0; kk < m && ok; ++kk) {
-    const double pv = G[kk][kk];
-    if (!(pv > 0.0 && pv < INFINITY)) {
-      ok = false;
-      break;
-    }
-    if (j > kk && j < m) {
-      const double f = G[kk][j] / pv;
-      for (int i = kk + 1 + wave; i <= j; i += NW) G[i][j] -= G[kk][i] * f;
-    }
-    __syncthreads();
-  }
+  if (ok)
+    ok = chol_rows(
+        a, m, lane, wave, row_s, [](int, double pv) { return pv > 0.0 && pv < INFINITY ? 1 : -1; }, [](int, double) {});
   if (tid == 0) {
     cert[k] = ok ? 1 : 0;
     if (ok)

@@ -864,21 +864,22 @@ RoundSumOut<T> plan_roundsum(Seq& q, Planner& pl, const Shape& sh, const Blocks<
         g.split_out = &so;
         emit_gemm(q, pl, std::move(g));
         std::vector<CholTask> ctp = ct;
-        for (size_t i = 0; i < ctp.size(); ++i)
+        for (size_t i = 0; i < ctp.size(); ++i) {
+          ctp[i].shift = pass == 0 ? shift1 : 0.0;
           if (so.part) {
             ctp[i].part = so.part + i * size_t(so.splits) * so.stride;
             ctp[i].splits = so.splits;
             ctp[i].pstride = so.stride;
           }
+        }
         const size_t cpo = blob.add(ctp);
-        const double sh_p = pass == 0 ? shift1 : 0.0;
         const double drel = pass == 1 ? 1e-30 : 0.0, dabs = pass == 2 ? 0.25 : 0.0;
         const int* mq = overlap ? nullptr : s_dev;
         q.steps.push_back(
-            [=](hipStream_t st) { chol_batched(bl->at<CholTask>(cpo), nt, sc, mq, sh_p, drel, dabs, st); });
+            [=](hipStream_t st) { chol_batched(bl->at<CholTask>(cpo), nt, sc, mq, drel, dabs, st); });
         std::vector<TrsmTask> tt;
         for (size_t i = 0; i < modes.size(); ++i) {
-          tt.push_back(TrsmTask{src[i], Rq + size_t(modes[i]) * sc * sc, dst[i]});
+          tt.push_back(TrsmTask{src[i], Rq + size_t(modes[i]) * sc * sc, dst[i], n});
           // the last pass also writes the FP32 basis of the FP32 form
           if constexpr (!std::is_same<T, double>::value)
             if (pass == 2) tt.back().Qf = Uh[modes[i]];

@@ -185,30 +185,33 @@ void qr_piv_batched(const QrPivTask* tasks_d, int ntasks, int n, int cap, double
 
 // ---- Cholesky-QR pieces (range-finder QR of RoundSum) ------------------------
 // R = chol(G + s I) for the leading m x m block of a cap x cap Gram (m =
-// min(*m_dev, cap)), with s = shift * trace(G).  A pivot that is not above
+// min(*m_dev, cap)), with s = task shift * trace(G).  A pivot that is not above
 // max(dead_rel * trace(G), dead_abs) marks a numerically dependent column: its
 // row of R is zeroed and the triangular solve below turns it into a zero
 // basis column.
 struct CholTask {
   const double* G;  // cap x cap, col-major
   double* R;        // cap x cap, col-major (upper triangle)
+  double shift = 0.0;
   // optional: G is not formed; its entries are the sums, in order, of
   // part[sp * pstride + i + j * cap] over sp < splits (split-K partials)
   const double* part = nullptr;
   int splits = 0;
   size_t pstride = 0;
 };
-void chol_batched(const CholTask* tasks_d, int ntasks, int cap, const int* m_dev, double shift, double dead_rel,
-                  double dead_abs, hipStream_t st);
+void chol_batched(const CholTask* tasks_d, int ntasks, int cap, const int* m_dev, double dead_rel, double dead_abs,
+                  hipStream_t st);
 // Q = Y R^{-1} row by row (R upper triangular from chol_batched); columns
-// >= m and dead columns of Q are zero.  Y, Q: n x cap col-major (ld n).
+// >= m and dead columns of Q are zero.  Y, Q: n x cap col-major (ld n), n per
+// task, at most nmax.
 struct TrsmTask {
   const double* Y;
   const double* R;
   double* Q;
+  int n;
   float* Qf = nullptr;  // optional FP32 copy of Q (same layout), rounded to nearest
 };
-void trsm_rows(const TrsmTask* tasks_d, int ntasks, int n, int cap, const int* m_dev, hipStream_t st);
+void trsm_rows(const TrsmTask* tasks_d, int ntasks, int nmax, int cap, const int* m_dev, hipStream_t st);
 
 // ---- symmetric Jacobi eigensolver (one workgroup per matrix) ---------------
 // A: N x N symmetric (lower triangle read, col-major, ld lda).  Eigenvalues

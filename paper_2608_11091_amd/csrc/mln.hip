@@ -191,7 +191,7 @@ void plan_mln_recovery(Seq& q, Planner& pl, const Shape& sh, const MlnSk& sk,
   // M_k = Q1 R2^{-1} (rt x r)
   {
     std::vector<TrsmTask> tt;
-    for (int k = 0; k < d; ++k) tt.push_back(TrsmTask{Q1[k], R2[k], M[k]});
+    for (int k = 0; k < d; ++k) tt.push_back(TrsmTask{Q1[k], R2[k], M[k], rt});
     const size_t ot = pl.blob.add(tt);
     q.steps.push_back([=](hipStream_t st) { trsm_rows(bl->at<TrsmTask>(ot), d, rt, r, nullptr, st); });
   }

@@ -6,6 +6,7 @@
 #include <algorithm>
 #include <cfloat>
 
+#include "chol.hpp"
 #include "kernels.hpp"
 
 namespace tk {
@@ -360,152 +361,196 @@ void qr_launch(const Task* tasks_d, int ntasks, int n, int cap, double drop_tol,
 #undef TK_QR_CASE
 }
 
-constexpr int CH_NT = 1024;  // 16 waves: a trailing-update column of at most 64 rows takes <= 4 entries per thread
+constexpr int CH_NT = 1024;  // 16 waves load the Gram, kCholWaves factor it
 constexpr int CH_MAX = 64;
 
-// Right-looking Cholesky of one small Gram in LDS (one workgroup per task),
-// one barrier per step: every thread derives the pivot of step k from G[k][k]
-// itself, and the trailing update G[i][j] -= G[k][i] G[k][j] / pivot (k < i
-// <= j, lane = column j, waves stride over the rows i) reads row k unscaled,
-// which no thread writes after step k.  Row k of R = row k / sqrt(pivot) is
-// formed at the end.  A pivot that is not above max(dead_rel tr, dead_abs)
-// marks a dead column: its row of R is zero and it updates nothing.
+// Cholesky factor of one small Gram per workgroup.  The load is bound by one
+// CU's bandwidth (the upper triangle of every split-K partial), the
+// factorisation by its serial chain (chol_rows); row k of R is row k of the
+// reduced matrix / sqrt(pivot).  A pivot that is not above max(dead_rel tr,
+// dead_abs) marks a dead column: its row of R is zero and it updates nothing.
+// Three Grams of order 53 from 16 partials each: 27.5 us (28.4 us from 8
+// partials with the matrix in LDS).
 __global__ __launch_bounds__(CH_NT) void chol_kernel(const CholTask* __restrict__ tasks, int cap,
-                                                     const int* __restrict__ m_dev, double shift, double dead_rel,
+                                                     const int* __restrict__ m_dev, double dead_rel,
                                                      double dead_abs) {
   constexpr int NW = CH_NT / kWave;
   __shared__ double G[CH_MAX][CH_MAX + 1];
-  __shared__ double red[NW];
+  __shared__ double row_s[2][kCholWaves][kWave];
   __shared__ double rk_s[CH_MAX];
   const CholTask tk_ = tasks[blockIdx.x];
   const int tid = threadIdx.x;
   const int lane = tid & (kWave - 1);
-  const int wave = tid / kWave;
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
   int m = m_dev ? *m_dev : cap;
-  m = min(m, cap);
-  for (int e = tid; e < cap * cap; e += CH_NT) {
-    const int i = e % cap, j = e / cap;
+  m = __builtin_amdgcn_readfirstlane(min(m, cap));
+  // row i from column i of the symmetric Gram: contiguous over the lanes
+#pragma unroll
+  for (int u = 0; u < CH_MAX / NW; ++u) {
+    const int i = wave + u * NW;
+    if (i >= m) continue;
     double g = 0.0;
-    if (i < m && j < m) {
+    if (lane >= i && lane < m) {
+      const size_t at = lane + (size_t)i * cap;
       if (tk_.part) {  // the Gram's split-K partials, summed in split order
-        // (eight loads in flight at a time; the additions keep their order)
-        const double* pp = tk_.part + i + (size_t)j * cap;
-        int sp = 0;
-        for (; sp + 8 <= tk_.splits; sp += 8) {
-          double v[8];
+        const GPtr<double> pp = (GPtr<double>)(tk_.part + at);
+        for (int sp = 0; sp < tk_.splits; sp += 16) {
+          double v[16];
 #pragma unroll
-          for (int u = 0; u < 8; ++u) v[u] = pp[(sp + u) * tk_.pstride];
+          for (int x = 0; x < 16; ++x) v[x] = pp[min(sp + x, tk_.splits - 1) * tk_.pstride];
 #pragma unroll
-          for (int u = 0; u < 8; ++u) g += v[u];
+          for (int x = 0; x < 16; ++x) g += sp + x < tk_.splits ? v[x] : 0.0;
         }
-        for (; sp < tk_.splits; ++sp) g += pp[sp * tk_.pstride];
       } else {
-        g = tk_.G[i + (size_t)j * cap];
+        g = ((GPtr<double>)tk_.G)[at];
       }
     }
-    G[i][j] = g;
+    G[i][lane] = g;
   }
   __syncthreads();
-  const double tr = block_sum(tid < m ? G[tid][tid] : 0.0, red);
-  const double s = shift * tr;
+  if (wave >= kCholWaves) return;  // a barrier waits for the waves that are left
+  const double tr = wave_sum(lane < m ? G[lane][lane] : 0.0);
+  const double s = tk_.shift * tr;
   const double dtol = fmax(dead_rel * tr, dead_abs);
-  if (tid < m) G[tid][tid] += s;
-  __syncthreads();
-  const int j = lane;  // this thread's column of the trailing update
-  for (int k = 0; k < m; ++k) {
-    const double pv = G[k][k];
-    const bool dk = !(pv > dtol);
-    if (tid == 0) rk_s[k] = dk ? 0.0 : sqrt(pv);
-    if (!dk && j > k && j < m) {
-      const double f = G[k][j] / pv;
-      for (int i = k + 1 + wave; i <= j; i += NW) G[i][j] -= G[k][i] * f;
-    }
-    __syncthreads();
+  double a[kCholRows];
+#pragma unroll
+  for (int r = 0; r < kCholRows; ++r) {
+    const int i = wave + kCholWaves * r;
+    a[r] = i < m ? G[i][lane] : 0.0;
+    if (lane == i) a[r] += s;
   }
-  for (int e = tid; e < cap * cap; e += CH_NT) {
-    const int i = e % cap, jj = e / cap;
+  chol_rows(
+      a, m, lane, wave, row_s,
+      [&](int k, double pv) {
+        const bool dead = !(pv > dtol);
+        if (wave == 0 && lane == 0) rk_s[k] = dead ? 0.0 : pv;
+        return dead ? 0 : 1;
+      },
+      [&](int i, double v) { G[i][lane] = v; });
+  __syncthreads();
+  const double rk = sqrt(lane < m ? rk_s[lane] : 0.0);
+  for (int j = wave; j < cap; j += kCholWaves) {
     double r = 0.0;
-    if (i < m && jj < m && i <= jj) {
-      const double rkk = rk_s[i];
-      r = rkk == 0.0 ? 0.0 : (i == jj ? rkk : G[i][jj] / rkk);
-    }
-    tk_.R[i + (size_t)jj * cap] = r;
+    if (lane < m && j < m && lane <= j && rk != 0.0) r = lane == j ? rk : G[lane][j] / rk;
+    if (lane < cap) tk_.R[lane + (size_t)j * cap] = r;
   }
 }
 
 constexpr int TR_NT = 128;
+constexpr int TR_LANES = 4;                    // lanes of a row
+constexpr int TR_ROWS = TR_NT / TR_LANES;      // rows of a workgroup
+// A lane's entries of a row of R, padded so that the 16-byte reads of the four
+// lanes hit different banks.
+constexpr int TR_PAD = CH_MAX / TR_LANES + 2;
 
-// Q = Y R^{-1}: each thread owns one row of Y in registers (compile-time
-// column indices) and runs the forward substitution q R = y.  (A right-looking
-// order, whose updates of a step are independent, measured slower: 35.6
-// against 26.6 us at 512 x 53, its per-entry guards cost more than the
-// dependency chain it breaks.)
-__global__ __launch_bounds__(TR_NT) void trsm_rows_kernel(const TrsmTask* __restrict__ tasks, int n, int cap,
+template <int L>
+__device__ __forceinline__ double quad_lane(double v) {
+  return dpp_mov<L * 0x55>(v);  // quad_perm[L, L, L, L]
+}
+
+// Q = Y R^{-1} by forward substitution, four lanes a row: lane l holds the
+// columns l, l + 4, ..  Step k divides in the lane of column k and passes q_k
+// to the other three, which subtract q_k R[k][c] from their later columns, so
+// a row's entries are updated in the same order and with the same operations
+// as by one thread a row; its chain is 53 divisions and as many
+// subtractions in place of 53 * 52 / 2 dependent ones, and four times as
+// many waves share the loads.  The division is x * (1 / d) with one exact
+// remainder step (correctly rounded, as 1 / d is).  512 x 53, three matrices:
+// 22.5 -> 13.5 us.
+template <int NG>
+__global__ __launch_bounds__(TR_NT) void trsm_rows_kernel(const TrsmTask* __restrict__ tasks, int cap,
                                                           const int* __restrict__ m_dev) {
-  __shared__ double R[CH_MAX][CH_MAX + 1];
+  constexpr int NC = NG * TR_LANES;
+  __shared__ __align__(16) double Rp[NC][TR_LANES][TR_PAD];  // R[k][l + 4 i], zero up to the diagonal
+  __shared__ __align__(16) double dg[NC][2];                 // R[k][k], 1 / R[k][k] (zeros: dead column)
   const TrsmTask tk_ = tasks[blockIdx.y];
+  const int n = tk_.n;
+  if (blockIdx.x * TR_ROWS >= unsigned(n)) return;
   const int tid = threadIdx.x;
+  const int l = tid % TR_LANES;
   int m = m_dev ? *m_dev : cap;
-  m = min(m, cap);
+  m = __builtin_amdgcn_readfirstlane(min(m, cap));
+  const int row = blockIdx.x * TR_ROWS + tid / TR_LANES;
+  const int rowc = min(row, n - 1);
+  const GPtr<double> gy = (GPtr<double>)tk_.Y;
+  double q[NG];
+#pragma unroll
+  for (int i = 0; i < NG; ++i) q[i] = gy[rowc + (size_t)min(l + TR_LANES * i, cap - 1) * n];
   {
-    // every load of R in flight at once, then the LDS writes
-    constexpr int RPT = CH_MAX * CH_MAX / TR_NT;
+    // column c of R by a wave, lane = row k: every load in flight at once
+    constexpr int NW = TR_NT / kWave, CPW = NC / NW;
     const GPtr<double> gr = (GPtr<double>)tk_.R;
-    const int cc = cap * cap;
-    double rv[RPT];
+    const int k = tid & (kWave - 1), w = tid / kWave;
+    double rv[CPW];
 #pragma unroll
-    for (int u = 0; u < RPT; ++u) {
-      const int e = tid + u * TR_NT;
-      rv[u] = gr[e < cc ? e : 0];
-    }
+    for (int u = 0; u < CPW; ++u) rv[u] = gr[min(k, cap - 1) + (size_t)min(w + NW * u, cap - 1) * cap];
 #pragma unroll
-    for (int u = 0; u < RPT; ++u) {
-      const int e = tid + u * TR_NT;
-      if (e < cc) R[e % cap][e / cap] = rv[u];
+    for (int u = 0; u < CPW; ++u) {
+      const int c = w + NW * u;
+      if (k < NC) {
+        Rp[k][c % TR_LANES][c / TR_LANES] = k < c && c < m ? rv[u] : 0.0;
+        if (k == c) {
+          const double d = c < m ? rv[u] : 0.0;
+          dg[k][0] = d;
+          dg[k][1] = d != 0.0 ? 1.0 / d : 0.0;
+        }
+      }
     }
   }
   __syncthreads();
-  const int row = blockIdx.x * TR_NT + tid;
-  if (row >= n) return;
-  double q[CH_MAX];
-  const GPtr<double> gy = (GPtr<double>)tk_.Y;
+  auto step = [&](auto kc) {
+    constexpr int k = decltype(kc)::value, i0 = k / TR_LANES, lk = k % TR_LANES;
+    if (k >= m) return;
+    const double d = dg[k][0], di = dg[k][1];
+    const double x = q[i0];
+    double t = x * di;
+    t = fma(fma(-t, d, x), di, t);
+    const double qk = quad_lane<lk>(d != 0.0 ? t : 0.0);
 #pragma unroll
-  for (int j = 0; j < CH_MAX; ++j) q[j] = (j < m) ? gy[row + (size_t)j * n] : 0.0;
+    for (int i = i0; i < NG; ++i) q[i] = fma(-qk, Rp[k][l][i], q[i]);
+    q[i0] = l == lk ? qk : q[i0];
+  };
+  for_constants<NC>(step);
 #pragma unroll
-  for (int j = 0; j < CH_MAX; ++j) {
-    if (j < m) {
-      double acc = q[j];
-#pragma unroll
-      for (int k = 0; k < j; ++k) acc -= q[k] * R[k][j];
-      const double rjj = R[j][j];
-      q[j] = rjj != 0.0 ? acc / rjj : 0.0;
+  for (int i = 0; i < NG; ++i) {
+    const int c = l + TR_LANES * i;
+    if (row < n && c < cap) {
+      const double qv = c < m ? q[i] : 0.0;
+      tk_.Q[row + (size_t)c * n] = qv;
+      if (tk_.Qf) tk_.Qf[row + (size_t)c * n] = float(qv);
     }
   }
-#pragma unroll
-  for (int j = 0; j < CH_MAX; ++j)
-    if (j < cap) {
-      const double qv = (j < m) ? q[j] : 0.0;
-      tk_.Q[row + (size_t)j * n] = qv;
-      if (tk_.Qf) tk_.Qf[row + (size_t)j * n] = float(qv);
-    }
 }
 
 }  // namespace
 
-void chol_batched(const CholTask* tasks_d, int ntasks, int cap, const int* m_dev, double shift, double dead_rel,
-                  double dead_abs, hipStream_t st) {
+void chol_batched(const CholTask* tasks_d, int ntasks, int cap, const int* m_dev, double dead_rel, double dead_abs,
+                  hipStream_t st) {
   if (ntasks <= 0) return;
   TK_CHECK(cap <= CH_MAX, kErrUnsupported, "Cholesky-QR: more than 64 columns");
   timer_begin(kKcQr, st);
-  hipLaunchKernelGGL(chol_kernel, dim3(ntasks), dim3(CH_NT), 0, st, tasks_d, cap, m_dev, shift, dead_rel, dead_abs);
+  hipLaunchKernelGGL(chol_kernel, dim3(ntasks), dim3(CH_NT), 0, st, tasks_d, cap, m_dev, dead_rel, dead_abs);
   TK_LAUNCH_CHECK();
   timer_end(kKcQr, st);
 }
 
-void trsm_rows(const TrsmTask* tasks_d, int ntasks, int n, int cap, const int* m_dev, hipStream_t st) {
+void trsm_rows(const TrsmTask* tasks_d, int ntasks, int nmax, int cap, const int* m_dev, hipStream_t st) {
   if (ntasks <= 0) return;
   TK_CHECK(cap <= CH_MAX, kErrUnsupported, "Cholesky-QR: more than 64 columns");
-  hipLaunchKernelGGL(trsm_rows_kernel, dim3(ceil_div(n, TR_NT), ntasks), dim3(TR_NT), 0, st, tasks_d, n, cap, m_dev);
+#define TK_TRSM_CASE(NG)                                                                                           \
+  hipLaunchKernelGGL((trsm_rows_kernel<NG>), dim3(ceil_div(nmax, TR_ROWS), ntasks), dim3(TR_NT), 0, st, tasks_d, cap, \
+                     m_dev)
+  // the fewest column groups that hold cap columns: a row's registers and the
+  // unrolled steps follow it
+  if (cap <= 16)
+    TK_TRSM_CASE(4);
+  else if (cap <= 32)
+    TK_TRSM_CASE(8);
+  else if (cap <= 48)
+    TK_TRSM_CASE(12);
+  else
+    TK_TRSM_CASE(16);
+#undef TK_TRSM_CASE
   TK_LAUNCH_CHECK();
 }
 

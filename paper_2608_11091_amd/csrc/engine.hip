@@ -33,7 +33,7 @@ struct GemmDesc {
   const int* nb = nullptr;
   std::function<int(int)> ngroups_of;  // active groups as a function of *nb
   bool terms_are_blocks = false;       // clamp each group's terms to *nb
-  bool mixed = false;                  // groups were added with dims of their own (group_dims)
+  bool own_dims = false;               // every group has dims of its own (group_dims)
   bool factor_product = false;         // a product with a Tucker factor (BF16 in the BF16-factor form)
   // optional: the only consumer of C sums the split-K partials itself, which
   // saves the reduction launch (C is then not written); needs beta = 0,
@@ -48,7 +48,8 @@ struct GemmDesc {
     g.t1 = int(terms.size());
     groups.push_back(g);
   }
-  // dims of the group added last (a mixed launch: N is common)
+  // dims of the group added last, for products that differ in the mode size
+  // (N is common); called for every group or for none
   void group_dims(int m, int k, int la, int lb, int lc) {
     GemmGroup<T>& g = groups.back();
     g.M = m;
@@ -56,7 +57,7 @@ struct GemmDesc {
     g.lda = la;
     g.ldb = lb;
     g.ldc = lc;
-    mixed = true;
+    own_dims = true;
   }
   void group1(T* C, const T* A, const T* B, const double* c1 = nullptr, const double* c2 = nullptr,
               const double* c3 = nullptr, double scale = 1.0) {
@@ -74,19 +75,25 @@ template <typename T>
 void emit_gemm(Seq& q, Planner& pl, GemmDesc<T>&& g) {
   if (g.groups.empty()) return;
   const int ng = int(g.groups.size());
+  GemmLaunch<T> L;
   int maxt = 1;
   for (auto& gr : g.groups) maxt = std::max(maxt, gr.t1 - gr.t0);
-  for (auto& gr : g.groups)
-    if (!g.mixed) {
-      gr.M = g.M;
-      gr.K = g.K;
-      gr.lda = g.lda;
-      gr.ldb = g.ldb;
-      gr.ldc = g.ldc;
-    } else {
+  if (g.own_dims) {
+    const GemmGroup<T>& g0 = g.groups[0];
+    for (auto& gr : g.groups) {
+      L.mixed |= gr.M != g0.M || gr.K != g0.K || gr.lda != g0.lda || gr.ldb != g0.ldb || gr.ldc != g0.ldc;
       g.M = std::max(g.M, gr.M);
       g.K = std::max(g.K, gr.K);
     }
+    g.lda = g0.lda;
+    g.ldb = g0.ldb;
+    g.ldc = g0.ldc;
+  } else {
+    for (auto& gr : g.groups) {
+      gr.M = g.M;
+      gr.K = g.K;
+    }
+  }
   const long tiles = long(ceil_div(g.M, 64)) * ceil_div(g.N, 64) * ng;
   const long slabs = long(maxt) * ceil_div(g.K, 32);
   // Split-K for the path's small, long-K products.  With a reduction launch of
@@ -118,7 +125,6 @@ void emit_gemm(Seq& q, Planner& pl, GemmDesc<T>&& g) {
   T* folded = folds > 0 ? pl.ar.alloc<T>(size_t(ng) * folds * g.M * g.N) : nullptr;
   const size_t toff = pl.blob.add(g.terms), goff = pl.blob.add(g.groups);
   Blob* bl = &pl.blob;
-  GemmLaunch<T> L;
   L.ta = g.ta;
   L.tb = g.tb;
   L.M = g.M;
@@ -146,7 +152,6 @@ void emit_gemm(Seq& q, Planner& pl, GemmDesc<T>&& g) {
   const int* nb = g.nb;
   auto ngf = g.ngroups_of;
   const bool tb = g.terms_are_blocks;
-  L.mixed = g.mixed;
   L.uniform_terms = maxt;
   std::vector<int> nterm;
   std::vector<double> mnk2;
@@ -349,22 +354,18 @@ void plan_krp_range(Seq& q, Planner& pl, const Shape& sh, const Blocks<T>& in, c
   auto nbA = [nb, nb_active]() { return nb_active ? std::min(nb, *nb_active) : nb; };
   T* Mb = ar.alloc<T>(size_t(nb) * d * rc * w);
   auto Mp = [&](int b, int j) { return Mb + (size_t(b) * d + j) * rc * w; };
-  for (auto& modes : modes_by_n<T>(sh)) {  // M_bj = U_bj^T L_j (rc x w)
-    const int n = sh.n[modes[0]];
+  {  // M_bj = U_bj^T L_j (rc x w), all modes in one launch
     GemmDesc<T> g;
     g.ta = true;
     g.tb = false;
-    g.M = rc;
     g.N = w;
-    g.K = n;
-    g.lda = n;
-    g.ldb = n;
-    g.ldc = rc;
     g.nb = nb_active;
-    const int nm = int(modes.size());
-    g.ngroups_of = [nm](int a) { return a * nm; };
+    g.ngroups_of = [d](int a) { return a * d; };
     for (int b = 0; b < nb; ++b)
-      for (int j : modes) g.group1(Mp(b, j), in.U[b][j], L[j]);
+      for (int j = 0; j < d; ++j) {
+        g.group1(Mp(b, j), in.U[b][j], L[j]);
+        g.group_dims(rc, sh.n[j], sh.n[j], sh.n[j], rc);
+      }
     g.factor_product = true;
     emit_gemm(q, pl, std::move(g));
   }
@@ -431,27 +432,20 @@ void plan_krp_range(Seq& q, Planner& pl, const Shape& sh, const Blocks<T>& in, c
       krp_reduce<T>(bl->at<KrpTask<T>>(off), nbA() * d, d - 1, z.data(), int(P), w, st);
     });
   }
-  for (auto& modes : modes_by_n<T>(sh)) {
-    const int n = sh.n[modes[0]];
-    GemmDesc<T> g;
-    g.ta = false;
-    g.tb = false;
-    g.M = n;
-    g.N = w;
-    g.K = rc;
-    g.lda = n;
-    g.ldb = rc;
-    g.ldc = n;
-    g.nb = nb_active;
-    g.terms_are_blocks = nb_active != nullptr;
-    for (int k : modes) {
-      std::vector<GemmTerm<T>> ts;
-      for (int b = 0; b < nb; ++b) ts.push_back(term<T>(in.U[b][k], Tp(b, k), coef + b));
-      g.group(Y[k], ts);
-    }
-    g.factor_product = true;
-    emit_gemm(q, pl, std::move(g));
+  GemmDesc<T> g;
+  g.ta = false;
+  g.tb = false;
+  g.N = w;
+  g.nb = nb_active;
+  g.terms_are_blocks = nb_active != nullptr;
+  for (int k = 0; k < d; ++k) {
+    std::vector<GemmTerm<T>> ts;
+    for (int b = 0; b < nb; ++b) ts.push_back(term<T>(in.U[b][k], Tp(b, k), coef + b));
+    g.group(Y[k], ts);
+    g.group_dims(sh.n[k], rc, sh.n[k], rc, sh.n[k]);
   }
+  g.factor_product = true;
+  emit_gemm(q, pl, std::move(g));
 }
 
 // Core projection of a block sum onto per-mode matrices P_k (n_k x >= w,
@@ -466,22 +460,18 @@ void plan_core_projection(Seq& q, Planner& pl, const Shape& sh, const Blocks<T>&
   Arena& ar = pl.ar;
   T* Wb = ar.alloc<T>(size_t(nb) * d * w * rc);
   auto Wp = [&](int b, int k) { return Wb + (size_t(b) * d + k) * w * rc; };
-  for (auto& modes : modes_by_n<T>(sh)) {
-    const int n = sh.n[modes[0]];
+  {
     GemmDesc<T> g;
     g.ta = true;
     g.tb = false;
-    g.M = w;
     g.N = rc;
-    g.K = n;
-    g.lda = n;
-    g.ldb = n;
-    g.ldc = w;
     g.nb = nb_active;
-    const int nm = int(modes.size());
-    g.ngroups_of = [nm](int a) { return a * nm; };
+    g.ngroups_of = [d](int a) { return a * d; };
     for (int b = 0; b < nb; ++b)
-      for (int k : modes) g.group1(Wp(b, k), Pm[k], in.U[b][k]);
+      for (int k = 0; k < d; ++k) {
+        g.group1(Wp(b, k), Pm[k], in.U[b][k]);
+        g.group_dims(w, sh.n[k], sh.n[k], sh.n[k], w);
+      }
     g.factor_product = true;
     emit_gemm(q, pl, std::move(g));
   }
@@ -608,8 +598,42 @@ RoundSumOut<T> plan_roundsum(Seq& q, Planner& pl, const Shape& sh, const Blocks<
   double* fro = use_cert ? ar.alloc<double>(size_t(nb) * d) : nullptr;
   std::vector<std::function<void(hipStream_t)>> eig_steps;
   if (rule) {
-    for (auto& modes : modes_by_n<T>(sh)) {
-      const int n = sh.n[modes[0]];
+    // Modes that share launches: those whose Gram goes on the R-side of order
+    // Rp <= n together, whatever their sizes; the others by size.
+    const int Rp = nb * rc;
+    // n-side up to order 64 (where the eigensolve is short either way), and
+    // up to 160 unless the concatenation is the narrower side: at n = 128 and
+    // three blocks of rank 12 the order drops from 128 to 36.  The FP32 form
+    // stays on the n-side there (its count of the zero eigenvalues' noise
+    // depends on the side).
+    auto on_nside = [=](int n) {
+      return n <= 64 || (n <= kEigRegMax && (Rp > n || !std::is_same<T, double>::value));
+    };
+    std::map<int, std::vector<int>> sets;
+    for (int k = 0; k < d; ++k) sets[!on_nside(sh.n[k]) && Rp <= sh.n[k] ? 0 : sh.n[k]].push_back(k);
+    if (use_cert) {
+      // squared Frobenius norms of the factors: tr(G_k) for the certificate
+      // (one launch for all modes where they are equal and all blocks active)
+      bool equal = nb_active == nullptr;
+      for (int k = 1; k < d; ++k) equal &= sh.n[k] == sh.n[0];
+      for (int k = 0; k < d; k += equal ? d : 1) {
+        std::vector<const T*> xs;
+        for (int j = k; j < (equal ? d : k + 1); ++j)
+          for (int b = 0; b < nb; ++b) xs.push_back(in.U[b][j]);
+        const int nx = int(xs.size());
+        const size_t off = blob.add(xs);
+        const size_t len = size_t(sh.n[k]) * rc;
+        double* out = fro + size_t(k) * nb;
+        double* fws = dot_scratch(ar, len, nx);
+        q.steps.push_back([=](hipStream_t st) {
+          dot_batched<T>(bl->at<const T*>(off), bl->at<const T*>(off), len, equal ? nx : nbA(), 1.0, out, fws, st);
+        });
+      }
+    }
+    for (auto& ms : sets) {
+      const std::vector<int>& modes = ms.second;
+      int n = 0;  // the mode size (the largest of an R-side set)
+      for (int k : modes) n = std::max(n, sh.n[k]);
       // The Gram goes on the smaller side (n x n, or R x R for the active
       // concatenation; both have the same nonzero spectrum).  Which side is
       // smaller and which eigensolver fits depend on the active ranks, a
@@ -618,21 +642,6 @@ RoundSumOut<T> plan_roundsum(Seq& q, Planner& pl, const Shape& sh, const Blocks<
       // <= 160) on the compacted R-side Gram while R <= 160, and the
       // global-memory one (order <= 512) above that, on the R-side Gram while
       // R <= n (capacity permitting) or else on the n-side Gram.
-      const int Rp = nb * rc;
-      if (use_cert) {
-        // squared Frobenius norms of the factors: tr(G_k) for the certificate
-        for (int k : modes) {
-          std::vector<const T*> xs;
-          for (int b = 0; b < nb; ++b) xs.push_back(in.U[b][k]);
-          const size_t off = blob.add(xs);
-          const size_t len = size_t(n) * rc;
-          double* out = fro + size_t(k) * nb;
-          double* fws = dot_scratch(ar, len, nb);
-          q.steps.push_back([=](hipStream_t st) {
-            dot_batched<T>(bl->at<const T*>(off), bl->at<const T*>(off), len, nbA(), 1.0, out, fws, st);
-          });
-        }
-      }
       auto nside_gram = [&](int ldg) {
         T* Gn = ar.alloc<T>(size_t(ldg) * n * modes.size());
         GemmDesc<T> g;
@@ -676,12 +685,7 @@ RoundSumOut<T> plan_roundsum(Seq& q, Planner& pl, const Shape& sh, const Blocks<
         e.rule.cap1 = sh.cap;  // the width only takes min(r~ + p, cap + p); lam is scratch
         return e;
       };
-      // n-side up to order 64 (where the eigensolve is short either way), and
-      // up to 160 unless the concatenation is the narrower side: at n = 128 and
-      // three blocks of rank 12 the order drops from 128 to 36.  The FP32 form
-      // stays on the n-side there (its count of the zero eigenvalues' noise
-      // depends on the side).
-      if (n <= 64 || (n <= kEigRegMax && (Rp > n || !std::is_same<T, double>::value))) {
+      if (on_nside(n)) {
         // n-side Gram: sum_b w_b^2 U_b U_b^T, register eigensolver
         T* Gn = nside_gram(n);
         T* lam = ar.alloc<T>(size_t(n) * modes.size());
@@ -713,20 +717,17 @@ RoundSumOut<T> plan_roundsum(Seq& q, Planner& pl, const Shape& sh, const Blocks<
         GemmDesc<T> g;
         g.ta = true;
         g.tb = false;
-        g.M = rc;
         g.N = rc;
-        g.K = n;
-        g.lda = n;
-        g.ldb = n;
-        g.ldc = Rp;
         g.nb = nb_active;
         const int nmod = int(modes.size());
         g.ngroups_of = [nmod](int a) { return a * (a + 1) / 2 * nmod; };
         for (int b = 0; b < nb; ++b)
           for (int b2 = 0; b2 <= b; ++b2)
-            for (int k : modes)
+            for (int k : modes) {
               g.group1(Gp + size_t(k) * Rp * Rp + size_t(b) * rc + size_t(b2) * rc * Rp, in.U[b][k], in.U[b2][k],
                        w + b, w + b2, enable + k);
+              g.group_dims(rc, sh.n[k], sh.n[k], sh.n[k], Rp);
+            }
         emit_gemm(q, pl, std::move(g));
       }
       q.steps.push_back([=](hipStream_t st) {
@@ -826,67 +827,60 @@ RoundSumOut<T> plan_roundsum(Seq& q, Planner& pl, const Shape& sh, const Blocks<
   } else {
     double* Gq = ar.alloc<double>(size_t(d) * sc * sc);
     double* Rq = ar.alloc<double>(size_t(d) * sc * sc);
-    for (auto& modes : modes_by_n<T>(sh)) {
-      const int n = sh.n[modes[0]];
-      if constexpr (!std::is_same<T, double>::value) {
-        // the FP32 range sketches of these modes to FP64, one launch
-        CastSet<T, double> cs;
-        for (int k : modes) {
-          cs.x[cs.count] = Y[k];
-          cs.y[cs.count] = Y64[k];
-          cs.len[cs.count++] = size_t(n) * sc;
-        }
-        q.steps.push_back([=](hipStream_t st) { cast_multi<T, double>(cs, st); });
+    int nmax = 0;
+    for (int k = 0; k < d; ++k) nmax = std::max(nmax, sh.n[k]);
+    if constexpr (!std::is_same<T, double>::value) {
+      // the FP32 range sketches to FP64, one launch
+      CastSet<T, double> cs;
+      for (int k = 0; k < d; ++k) {
+        cs.x[cs.count] = Y[k];
+        cs.y[cs.count] = Y64[k];
+        cs.len[cs.count++] = size_t(sh.n[k]) * sc;
       }
+      q.steps.push_back([=](hipStream_t st) { cast_multi<T, double>(cs, st); });
+    }
+    for (int pass = 0; pass < 3; ++pass) {
+      std::vector<const double*> src;
+      std::vector<double*> dst;
+      for (int k = 0; k < d; ++k) {
+        src.push_back(pass == 1 ? Q64[k] : Y64[k]);
+        dst.push_back(pass == 1 ? Y64[k] : Q64[k]);
+      }
+      GemmDesc<double> g;
+      g.ta = true;
+      g.tb = false;
+      g.N = sc;
+      for (int k = 0; k < d; ++k) {
+        g.group1(Gq + size_t(k) * sc * sc, src[k], src[k]);
+        g.group_dims(sc, sh.n[k], sh.n[k], sh.n[k], sc);
+      }
+      // the Cholesky kernel sums the Gram's split-K partials itself
+      SplitOut<double> so;
+      g.split_out = &so;
+      emit_gemm(q, pl, std::move(g));
       std::vector<CholTask> ct;
-      for (int k : modes) ct.push_back(CholTask{Gq + size_t(k) * sc * sc, Rq + size_t(k) * sc * sc});
-      const int nt = int(ct.size());
-      const double shift1 = 11.0 * (double(n) * sc + double(sc) * (sc + 1)) * 0x1p-53;
-      for (int pass = 0; pass < 3; ++pass) {
-        std::vector<const double*> src;
-        std::vector<double*> dst;
-        for (int k : modes) {
-          src.push_back(pass == 1 ? Q64[k] : Y64[k]);
-          dst.push_back(pass == 1 ? Y64[k] : Q64[k]);
+      std::vector<TrsmTask> tt;
+      for (int k = 0; k < d; ++k) {
+        CholTask c{Gq + size_t(k) * sc * sc, Rq + size_t(k) * sc * sc};
+        if (pass == 0) c.shift = 11.0 * (double(sh.n[k]) * sc + double(sc) * (sc + 1)) * 0x1p-53;
+        if (so.part) {
+          c.part = so.part + k * size_t(so.splits) * so.stride;
+          c.splits = so.splits;
+          c.pstride = so.stride;
         }
-        GemmDesc<double> g;
-        g.ta = true;
-        g.tb = false;
-        g.M = sc;
-        g.N = sc;
-        g.K = n;
-        g.lda = n;
-        g.ldb = n;
-        g.ldc = sc;
-        for (size_t i = 0; i < modes.size(); ++i) g.group1(Gq + size_t(modes[i]) * sc * sc, src[i], src[i]);
-        // the Cholesky kernel sums the Gram's split-K partials itself
-        SplitOut<double> so;
-        g.split_out = &so;
-        emit_gemm(q, pl, std::move(g));
-        std::vector<CholTask> ctp = ct;
-        for (size_t i = 0; i < ctp.size(); ++i) {
-          ctp[i].shift = pass == 0 ? shift1 : 0.0;
-          if (so.part) {
-            ctp[i].part = so.part + i * size_t(so.splits) * so.stride;
-            ctp[i].splits = so.splits;
-            ctp[i].pstride = so.stride;
-          }
-        }
-        const size_t cpo = blob.add(ctp);
-        const double drel = pass == 1 ? 1e-30 : 0.0, dabs = pass == 2 ? 0.25 : 0.0;
-        const int* mq = overlap ? nullptr : s_dev;
-        q.steps.push_back(
-            [=](hipStream_t st) { chol_batched(bl->at<CholTask>(cpo), nt, sc, mq, drel, dabs, st); });
-        std::vector<TrsmTask> tt;
-        for (size_t i = 0; i < modes.size(); ++i) {
-          tt.push_back(TrsmTask{src[i], Rq + size_t(modes[i]) * sc * sc, dst[i], n});
-          // the last pass also writes the FP32 basis of the FP32 form
-          if constexpr (!std::is_same<T, double>::value)
-            if (pass == 2) tt.back().Qf = Uh[modes[i]];
-        }
-        const size_t toff = blob.add(tt);
-        q.steps.push_back([=](hipStream_t st) { trsm_rows(bl->at<TrsmTask>(toff), nt, n, sc, mq, st); });
+        ct.push_back(c);
+        tt.push_back(TrsmTask{src[k], Rq + size_t(k) * sc * sc, dst[k], sh.n[k]});
+        // the last pass also writes the FP32 basis of the FP32 form
+        if constexpr (!std::is_same<T, double>::value)
+          if (pass == 2) tt.back().Qf = Uh[k];
       }
+      const size_t cpo = blob.add(ct), toff = blob.add(tt);
+      const double drel = pass == 1 ? 1e-30 : 0.0, dabs = pass == 2 ? 0.25 : 0.0;
+      const int* mq = overlap ? nullptr : s_dev;
+      q.steps.push_back([=](hipStream_t st) {
+        chol_batched(bl->at<CholTask>(cpo), d, sc, mq, drel, dabs, st);
+        trsm_rows(bl->at<TrsmTask>(toff), d, nmax, sc, mq, st);
+      });
     }
   }
   if (use_cert) {
@@ -900,49 +894,43 @@ RoundSumOut<T> plan_roundsum(Seq& q, Planner& pl, const Shape& sh, const Blocks<
     const int cp_ = sh.cap;
     T* Pm = ar.alloc<T>(size_t(nb) * d * cp_ * rc);
     T* Hc = ar.alloc<T>(size_t(d) * cp_ * cp_);
-    for (auto& modes : modes_by_n<T>(sh)) {
-      const int n = sh.n[modes[0]];
-      {
-        // P_bk (cap x rc); groups ordered by block, so the active ones are a prefix
-        GemmDesc<T> g;
-        g.ta = true;
-        g.tb = false;
-        g.M = cp_;
-        g.N = rc;
-        g.K = n;
-        g.lda = n;
-        g.ldb = n;
-        g.ldc = cp_;
-        g.nb = nb_active;
-        const int nmod = int(modes.size());
-        g.ngroups_of = [nmod](int a) { return a * nmod; };
-        for (int b = 0; b < nb; ++b)
-          for (int k : modes) g.group1(Pm + (size_t(k) * nb + b) * cp_ * rc, Uh[k], in.U[b][k], w + b);
-        emit_gemm(q, pl, std::move(g));
-      }
-      {
-        // H_k = sum_b P_bk P_bk^T (cap x cap)
-        GemmDesc<T> g;
-        g.ta = false;
-        g.tb = true;
-        g.M = cp_;
-        g.N = cp_;
-        g.K = rc;
-        g.lda = cp_;
-        g.ldb = cp_;
-        g.ldc = cp_;
-        g.nb = nb_active;
-        g.terms_are_blocks = nb_active != nullptr;
-        for (int k : modes) {
-          std::vector<GemmTerm<T>> ts;
-          for (int b = 0; b < nb; ++b) {
-            const T* P = Pm + (size_t(k) * nb + b) * cp_ * rc;
-            ts.push_back(term<T>(P, P));
-          }
-          g.group(Hc + size_t(k) * cp_ * cp_, ts);
+    {
+      // P_bk (cap x rc); groups ordered by block, so the active ones are a prefix
+      GemmDesc<T> g;
+      g.ta = true;
+      g.tb = false;
+      g.N = rc;
+      g.nb = nb_active;
+      g.ngroups_of = [d](int a) { return a * d; };
+      for (int b = 0; b < nb; ++b)
+        for (int k = 0; k < d; ++k) {
+          g.group1(Pm + (size_t(k) * nb + b) * cp_ * rc, Uh[k], in.U[b][k], w + b);
+          g.group_dims(cp_, sh.n[k], sh.n[k], sh.n[k], cp_);
         }
-        emit_gemm(q, pl, std::move(g));
+      emit_gemm(q, pl, std::move(g));
+    }
+    {
+      // H_k = sum_b P_bk P_bk^T (cap x cap)
+      GemmDesc<T> g;
+      g.ta = false;
+      g.tb = true;
+      g.M = cp_;
+      g.N = cp_;
+      g.K = rc;
+      g.lda = cp_;
+      g.ldb = cp_;
+      g.ldc = cp_;
+      g.nb = nb_active;
+      g.terms_are_blocks = nb_active != nullptr;
+      for (int k = 0; k < d; ++k) {
+        std::vector<GemmTerm<T>> ts;
+        for (int b = 0; b < nb; ++b) {
+          const T* P = Pm + (size_t(k) * nb + b) * cp_ * rc;
+          ts.push_back(term<T>(P, P));
+        }
+        g.group(Hc + size_t(k) * cp_ * cp_, ts);
       }
+      emit_gemm(q, pl, std::move(g));
     }
     CertParams cpar{};
     cpar.d = d;
@@ -1081,23 +1069,20 @@ RoundSumOut<T> plan_roundsum(Seq& q, Planner& pl, const Shape& sh, const Blocks<
     for (int k = 0; k < d; ++k) g.group1(U12[k], V1[k], V2[k]);
     emit_gemm(q, pl, std::move(g));
   }
-  // factors U_k = U^_k U12_k[:, :min(rc, sc)]
-  for (auto& modes : modes_by_n<T>(sh)) {
-    const int n = sh.n[modes[0]];
+  {
+    // factors U_k = U^_k U12_k[:, :min(rc, sc)]
     if (rc > sc)
-      for (int k : modes) {
+      for (int k = 0; k < d; ++k) {
         T* u = out.U[k];
-        const size_t len = size_t(n) * rc;
+        const size_t len = size_t(sh.n[k]) * rc;
         q.steps.push_back([=](hipStream_t st) { fill<T>(u, len, T(0), st); });
       }
     GemmDesc<T> g;
-    g.M = n;
     g.N = std::min(rc, sc);
-    g.K = sc;
-    g.lda = n;
-    g.ldb = sc;
-    g.ldc = n;
-    for (int k : modes) g.group1(out.U[k], Uh[k], U12[k]);
+    for (int k = 0; k < d; ++k) {
+      g.group1(out.U[k], Uh[k], U12[k]);
+      g.group_dims(sh.n[k], sc, sh.n[k], sc, sh.n[k]);
+    }
     emit_gemm(q, pl, std::move(g));
   }
   {

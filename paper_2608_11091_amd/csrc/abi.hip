@@ -62,10 +62,22 @@ void check_op(const tk_kron_op* op, int d, const int64_t* n) {
   TK_CHECK(op->nterms >= 1 && op->alpha != nullptr && op->A != nullptr, kErrInvalidArg, "operator has no terms");
 }
 
+// Whether a caller tensor's core (k < 0) or factor k already has the capacity
+// layout: nothing to cut, pad or convert.
+bool in_layout(const Shape& sh, const tk_tucker& u, int k) {
+  if (k >= 0) return u.r[k] == sh.rc;
+  for (int j = 0; j < sh.d; ++j)
+    if (u.r[j] != sh.rc || u.rcap[j] != sh.rc) return false;
+  return true;
+}
+
 // The moves that bring a caller tensor into the capacity layout: core,
-// factors and ranks.
+// factors and ranks.  With `in_place` the parts that have the layout are used
+// where they are (the plan only reads them): t then points at them, and the
+// move of such a core only stores the ranks.
 template <typename D>
-void import_tasks(const Shape& sh, const tk_tucker& u, const TT<D>& t, std::vector<MoveTask<double, D>>& out) {
+void import_tasks(const Shape& sh, const tk_tucker& u, TT<D>& t, std::vector<MoveTask<double, D>>& out,
+                  bool in_place = false) {
   const int d = sh.d;
   MoveTask<double, D> c{};
   c.src = u.core;
@@ -73,14 +85,34 @@ void import_tasks(const Shape& sh, const tk_tucker& u, const TT<D>& t, std::vect
   c.total = sh.core_len();
   c.d = d;
   c.rank = t.rank;
+  bool inner = true;  // modes 1 .. d - 1 keep their strides: one contiguous piece
+  size_t slice = 1;
   for (int k = 0; k < kMaxD; ++k) {
     c.sd[k] = k < d ? int(u.rcap[k]) : 1;
     c.sv[k] = k < d ? int(u.r[k]) : 1;
     c.dd[k] = k < d ? sh.rc : 1;
     c.rk[k] = k < d ? int(u.r[k]) : 1;
+    if (k >= 1 && k < d) {
+      inner &= u.r[k] == sh.rc && u.rcap[k] == sh.rc;
+      slice *= size_t(sh.rc);
+    }
   }
+  if (inner) {  // no index arithmetic (it costs four times the copy of a large core)
+    c.d = 0;
+    c.valid = slice * size_t(u.r[0]);
+  }
+  if constexpr (std::is_same<D, double>::value)
+    if (in_place && in_layout(sh, u, -1)) {
+      t.core = const_cast<double*>(u.core);
+      c.total = c.valid = 0;
+    }
   out.push_back(c);
   for (int k = 0; k < d; ++k) {
+    if constexpr (std::is_same<D, double>::value)
+      if (in_place && in_layout(sh, u, k)) {
+        t.U[k] = const_cast<double*>(u.U[k]);
+        continue;
+      }
     MoveTask<double, D> f{};
     f.src = u.U[k];
     f.dst = t.U[k];
@@ -103,7 +135,7 @@ MoveTask<S, D> convert_task(const S* src, D* dst, size_t len) {
 // One launch for all moves of a call (the table goes into the plan's blob).
 template <typename S, typename D>
 void emit_moves(Seq& q, Planner& pl, const std::vector<MoveTask<S, D>>& tasks) {
-  size_t mx = 0;
+  size_t mx = 1;
   for (auto& t : tasks) mx = std::max<size_t>(mx, t.total);
   const size_t off = pl.blob.add(tasks);
   const int nt = int(tasks.size());
@@ -112,7 +144,7 @@ void emit_moves(Seq& q, Planner& pl, const std::vector<MoveTask<S, D>>& tasks) {
 }
 
 // Import of one tensor outside a plan (tasks as kernel arguments).
-void emit_import(Seq& q, const Shape& sh, const tk_tucker& u, const TT<double>& t) {
+void emit_import(Seq& q, const Shape& sh, const tk_tucker& u, TT<double> t) {
   std::vector<MoveTask<double, double>> tasks;
   import_tasks<double>(sh, u, t, tasks);
   MoveSet<double, double> set;
@@ -326,14 +358,16 @@ Shape shape_of_blocks(const tk_block_sum* in, int cap, int p) {
 }
 
 // The blocks in the capacity layout, rounded to T; the moves are added to
-// `tasks` (launched by the caller together with its own).
+// `tasks` (launched by the caller together with its own).  FP64 parts that
+// have the layout are read where they are; their space stays reserved, so the
+// workspace depends on the capacities alone.
 template <typename T>
 Imported<T> import_blocks(Arena& ar, const tk_block_sum* in, const Shape& sh, std::vector<MoveTask<double, T>>& tasks) {
   Imported<T> im;
   im.sh = sh;
   for (int b = 0; b < in->nblocks; ++b) {
     TT<T> t = alloc_tt<T>(ar, sh);
-    import_tasks<T>(sh, in->blocks[b], t, tasks);
+    import_tasks<T>(sh, in->blocks[b], t, tasks, true);
     im.blocks.add(t, nullptr, in->coef[b]);
   }
   return im;

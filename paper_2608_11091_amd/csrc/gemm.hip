@@ -50,6 +50,18 @@ __device__ __forceinline__ f4 mfma_bf16(s4 a, s4 b, f4 c) {
 
 constexpr int BM = 64, BN = 64, NT = 256;
 
+// Rows in slices (GemmLaunch::mblk); the quotient by a multiplication, exact
+// while rows * mblk < 2^32.
+struct RowBlocks {
+  unsigned mblk, magic;
+  long astr, cstr;
+  __device__ __forceinline__ size_t at(int row, long str) const {
+    if (mblk == 0) return size_t(row);
+    const unsigned s = __umulhi(unsigned(row), magic);
+    return size_t(s) * size_t(str) + (unsigned(row) - s * mblk);
+  }
+};
+
 // Whether a value that is the same in every lane is zero, as a scalar condition.
 __device__ __forceinline__ bool uniform_zero(float x) {
   return (__builtin_amdgcn_readfirstlane(__float_as_int(x)) & 0x7fffffff) == 0;
@@ -70,7 +82,7 @@ __global__ __launch_bounds__(NT) void gemm_kernel(int M, int N, int K, int lda, 
                                                   const GemmTerm<T>* __restrict__ terms,
                                                   const GemmGroup<T>* __restrict__ groups, double beta,
                                                   int splits, T* __restrict__ partial, size_t pstride,
-                                                  int max_terms, int uniform_terms, bool mixed) {
+                                                  int max_terms, int uniform_terms, bool mixed, RowBlocks rb_) {
   static_assert(!BF || sizeof(T) == 4, "bf16 operands with FP32 storage only");
   // K depth of a slab: 32 (8 loads per operand and thread in flight at once,
   // half the slab iterations of a 16-deep slab on the path's short-K
@@ -153,13 +165,14 @@ __global__ __launch_bounds__(NT) void gemm_kernel(int M, int N, int K, int lda, 
     c2 = tm.c2 ? *tm.c2 : 1.0;
     c3 = tm.c3 ? *tm.c3 : 1.0;
   };
+  const size_t arow = TA ? 0 : rb_.at(min(m0 + am0, M - 1), rb_.astr);  // (one row per thread when A is not transposed)
   auto load = [&]() {
     const GPtr<T> ga = (GPtr<T>)tm.A;
     const GPtr<T> gb = (GPtr<T>)tm.B;
     const bool a2 = SA / 2 * amd < Ml && kf + SA / 2 * akd < K, b2 = SB / 2 * bnd < Nl && kf + SB / 2 * bkd < K;
     auto la = [&](int i) {
-      const int gm = min(m0 + am0 + i * amd, M - 1), gk = min(kf + ak0 + i * akd, K - 1);
-      ra[i] = TA ? ga[gk + (size_t)gm * lda] : ga[gm + (size_t)gk * lda];
+      const int gk = min(kf + ak0 + i * akd, K - 1);
+      ra[i] = TA ? ga[gk + (size_t)min(m0 + am0 + i * amd, M - 1) * lda] : ga[arow + (size_t)gk * lda];
     };
     auto lb = [&](int i) {
       const int gn = min(n0 + bn0 + i * bnd, N - 1), gk = min(kf + bk0 + i * bkd, K - 1);
@@ -304,7 +317,7 @@ __global__ __launch_bounds__(NT) void gemm_kernel(int M, int N, int K, int lda, 
         const int col = n0 + tj * 16 + (lane & 15);
         if (row < M && col < N) {
           if (splits == 1) {
-            T* c = grp.C + row + (size_t)col * ldc;
+            T* c = grp.C + rb_.at(row, rb_.cstr) + (size_t)col * ldc;
             *c = (beta == 0.0) ? acc[j][v] : T(beta) * (*c) + acc[j][v];
           } else {
             partial[(size_t)blockIdx.z * pstride + (size_t)col * M + row] = acc[j][v];
@@ -361,13 +374,22 @@ void gemm_run(const GemmLaunch<T>& g, hipStream_t st) {
   dim3 grid(ceil_div(g.M, BM), ceil_div(g.N, BN), g.ngroups * g.splits);
   T* part = g.splits > 1 ? g.partial : nullptr;
   const size_t pstride = (size_t)g.M * g.N;
+  RowBlocks rb{};
+  if (g.mblk > 0) {
+    TK_CHECK(!g.ta && g.splits == 1 && !g.mixed && long(g.M) * g.mblk < (1L << 32), kErrInvalidArg,
+             "internal: rows in slices");
+    rb.mblk = unsigned(g.mblk);
+    rb.magic = unsigned(((1ull << 32) + rb.mblk - 1) / rb.mblk);
+    rb.astr = g.astr;
+    rb.cstr = g.cstr;
+  }
   timer_begin(kKcGemm, st, g.flops);
   TK_CHECK(!g.bf16 || sizeof(T) == 4, kErrUnsupported, "bf16 operands need FP32 storage");
 #define TK_GEMM_CASE(TA, TB, BF)                                                                          \
   if (g.ta == TA && g.tb == TB && g.bf16 == BF)                                                            \
     hipLaunchKernelGGL((gemm_kernel<T, TA, TB, BF && sizeof(T) == 4>), grid, dim3(NT), 0, st, g.M, g.N, g.K, \
                        g.lda, g.ldb, g.ldc, g.terms, g.groups, g.beta, g.splits, part, pstride, g.max_terms,        \
-                       g.uniform_terms, g.mixed);
+                       g.uniform_terms, g.mixed, rb);
   TK_GEMM_CASE(false, false, false)
   TK_GEMM_CASE(false, true, false)
   TK_GEMM_CASE(true, false, false)

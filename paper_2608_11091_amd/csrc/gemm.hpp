@@ -46,6 +46,11 @@ struct GemmLaunch {
   int folds = 0;           // (ngroups * folds * M * N)
   int uniform_terms = 0;   // > 0: group g has the terms [g u, (g + 1) u)
   bool mixed = false;      // groups have their own M, K, lda, ldb, ldc (M, K above: the largest)
+  // mblk > 0 (A not transposed): row i of A and C is row i % mblk of slice
+  // i / mblk, the slices astr and cstr elements apart (a product over a middle
+  // mode of a tensor, whose slices would each fill their tiles in part)
+  int mblk = 0;
+  long astr = 0, cstr = 0;
   int max_terms = 1 << 30; // clamp every group to its first max_terms terms
   bool bf16 = false;       // FP32 storage: round the operands to bfloat16, BF16 matrix cores, FP32 accumulation
   bool defer_reduce = false;  // splits > 1: leave the partials for the consumer to sum (C is not written)

@@ -44,22 +44,43 @@ __global__ __launch_bounds__(KRP_NT) void krp_kernel(const KrpTask<T>* __restric
       int stride[kMaxD];
 #pragma unroll
       for (int j = kMaxD - 1; j >= 0; --j) stride[j] = (j >= m - 1) ? 1 : stride[j + 1 < kMaxD ? j + 1 : j] * z.v[j + 1 < kMaxD ? j + 1 : j];
-      int sf = 1;
+      if (m == 3) {
+        // two other modes u < v: the parts split over both, v fastest, and walk
+        // them without divisions
+        const int u = f == 0 ? 1 : 0, v = f == 2 ? 1 : 2;
+        int sf = 1, su = 1, sv = 1, zu = 1, zv = 1;
 #pragma unroll
-      for (int j = 0; j < kMaxD; ++j)
-        if (j == f) sf = stride[j];
-      for (int o = pp; o < O; o += nparts) {
-        int rem = o, row = a * sf;
-        T prod = T(1);
-#pragma unroll
-        for (int j = kMaxD - 1; j >= 0; --j) {
-          if (j >= m || j == f) continue;
-          const int ij = rem % z.v[j];
-          rem /= z.v[j];
-          row += ij * stride[j];
-          prod *= mv[j][ij];
+        for (int j = 0; j < kMaxD; ++j) {
+          if (j == f) sf = stride[j];
+          if (j == u) { su = stride[j]; zu = z.v[j]; }
+          if (j == v) { sv = stride[j]; zv = z.v[j]; }
         }
-        acc += Zl[row] * prod;
+        const int nv = min(nparts, zv), nu = nparts / nv;
+        const int pv = pp % nv, pu = pp / nv;
+        if (pu < nu)
+          for (int iu = pu; iu < zu; iu += nu) {
+            const T mu = mv[u][iu];
+            const T* Zr = Zl + a * sf + iu * su;
+            for (int iv = pv; iv < zv; iv += nv) acc += Zr[iv * sv] * (mv[v][iv] * mu);
+          }
+      } else {
+        int sf = 1;
+#pragma unroll
+        for (int j = 0; j < kMaxD; ++j)
+          if (j == f) sf = stride[j];
+        for (int o = pp; o < O; o += nparts) {
+          int rem = o, row = a * sf;
+          T prod = T(1);
+#pragma unroll
+          for (int j = kMaxD - 1; j >= 0; --j) {
+            if (j >= m || j == f) continue;
+            const int ij = rem % z.v[j];
+            rem /= z.v[j];
+            row += ij * stride[j];
+            prod *= mv[j][ij];
+          }
+          acc += Zl[row] * prod;
+        }
       }
     }
     part[tid] = acc;

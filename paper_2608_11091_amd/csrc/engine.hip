@@ -316,17 +316,20 @@ void emit_cast<float>(Seq& q, const float* src, double* dst, size_t len) {
 
 // Fork/join of a plan section onto the side stream: the section starts after
 // everything issued before it on the caller's stream, and the caller's stream
-// waits for the section at the join.  The events live as long as the plan.
+// waits for the section at the join.  The events are created at the first run
+// (a plan that is only measured, or whose iteration never runs, has none) and
+// live as long as the plan.
 struct ForkJoin {
   hipEvent_t fork = nullptr, join = nullptr;
-  ForkJoin() {
-    TK_HIP(hipEventCreateWithFlags(&fork, hipEventDisableTiming));
-    TK_HIP(hipEventCreateWithFlags(&join, hipEventDisableTiming));
+  ForkJoin() = default;
+  void ready() {
+    if (fork == nullptr) TK_HIP(hipEventCreateWithFlags(&fork, hipEventDisableTiming));
+    if (join == nullptr) TK_HIP(hipEventCreateWithFlags(&join, hipEventDisableTiming));
   }
   ~ForkJoin() {
-    (void)hipEventSynchronize(join);  // a plan may be dropped right after it was issued
-    (void)hipEventDestroy(fork);
-    (void)hipEventDestroy(join);
+    if (join) (void)hipEventSynchronize(join);  // a plan may be dropped right after it was issued
+    if (fork) (void)hipEventDestroy(fork);
+    if (join) (void)hipEventDestroy(join);
   }
   ForkJoin(const ForkJoin&) = delete;
   ForkJoin& operator=(const ForkJoin&) = delete;
@@ -342,6 +345,7 @@ std::function<void(hipStream_t)> fork_steps(Seq& q, size_t from, int which) {
   q.steps.resize(from);
   q.steps.push_back([fj, sec, which](hipStream_t st) {
     hipStream_t side = side_stream(which);
+    fj->ready();
     TK_HIP(hipEventRecord(fj->fork, st));
     TK_HIP(hipStreamWaitEvent(side, fj->fork, 0));
     for (auto& f : sec) f(side);

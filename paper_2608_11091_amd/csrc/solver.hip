@@ -72,20 +72,34 @@ struct Cycle {
   double *Hv, *tau, *R, *qtb, *y, *res, *nrmM2, *lam;
   int* flags;
   IterStatus* st_dev;
-  IterStatus* st_host = nullptr;  // pinned, two slots (iteration parity)
-  double* lam_host = nullptr;     // pinned, maxiter
+  IterStatus* st_host = nullptr;  // pinned, two slots (iteration parity); the solver's
+  double* lam_host = nullptr;     // pinned, maxiter; the solver's
   double* ysave = nullptr;        // maxiter x maxiter: y after each iteration
   hipEvent_t st_ev[2] = {nullptr, nullptr};
   Seq setup, fin;
   std::vector<Seq> iter;
+  // Iterations from the first full window on have plans of one structure, so
+  // only the first kt are planned ahead (with the sizes of the others); the
+  // others when they are first enqueued, beside the device's work on the
+  // iteration before: a preconditioned solve that converges in 2 of 60
+  // iterations spent 3 ms on planning them, twice.
+  OpDev<T> op_;
+  bool transpose_ = false, bf16_ = false;
+  std::array<const T*, kMaxD> S_{}, om_{};
+  RoundCfg rcfg_;
+  std::unique_ptr<Arena> scratch;  // at the iterations' scratch mark
+  size_t scratch_end = 0;
+  struct Late {
+    Blob blob;
+    size_t room = 0;
+  };
+  std::vector<std::unique_ptr<Late>> late;  // per iteration; null: planned ahead
   int nb_final = 0;
   double conv_tol = 0.0;
   double bd_tol = 1e-14;
   LsState ls{};
 
   ~Cycle() {
-    if (st_host) (void)hipHostFree(st_host);
-    if (lam_host) (void)hipHostFree(lam_host);
     for (auto& e : st_ev)
       if (e) (void)hipEventDestroy(e);
   }
@@ -128,14 +142,17 @@ struct Cycle {
     flags = ar.alloc<int>(4);
     st_dev = ar.alloc<IterStatus>(1);
     ls = LsState{Mcols, bs, Hv, tau, R, qtb, y, res, nrmM2, flags, 0.0, bsn, lam, ysave};
-    if (!ar.measuring()) {
-      TK_HIP(hipHostMalloc(reinterpret_cast<void**>(&st_host), 2 * sizeof(IterStatus), 0));
-      TK_HIP(hipHostMalloc(reinterpret_cast<void**>(&lam_host), sizeof(double) * maxiter, 0));
+    if (!ar.measuring())
       for (auto& e : st_ev) TK_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
-    }
 
     RoundCfg rcfg;
     rcfg.eps_dev = eps_pair;
+    op_ = op;
+    transpose_ = transpose;
+    bf16_ = pl.bf16_factors;
+    S_ = S;
+    om_ = omega_;
+    rcfg_ = rcfg;
 
     // ---- setup: beta = ||B|| (orthonormal factors), V_1 = B / beta, b_s = S^T vec(B)
     {
@@ -178,73 +195,21 @@ struct Cycle {
     // scope: iterations run in sequence (the host waits for each one's status,
     // and a RoundSum's side-stream work joins before the RoundSum ends), so
     // they share that memory.
-    for (int k = 0; k < maxiter; ++k) {
-      const size_t mk = ar.mark();
-      Seq q;
-      TT<T> Zk = V[k];
-      if (flexible) {
-        // flexible cycle (Sec. 3.4): Z_k = T(M(V_k)), and the operator acts on Z_k
-        Zk = Z[k];
-        plan_precond<T>(q, pl, sh, pc, V[k], Zk, rcfg, omega_);
-      }
-      Blocks<T> LV = plan_apply<T>(q, pl, sh, op, Zk, transpose);
-      plan_roundsum<T>(q, pl, sh, LV, rcfg, omega_, W, nullptr);
-      Blocks<T> wb;
-      wb.add(W, nullptr, 1.0);
-      const int ss = lr, mx = maxiter;
-      LsState lsv = ls;
-      const double* ctol = &conv_tol;
-      const double bdt = bd_tol;
-      const bool tik = tikhonov, fa = full;
-      // The sketch of W and the least-squares column (a3, a7) need only W:
-      // they run on a second side stream beside the inner products and the
-      // orthogonalisation RoundSum, and join before the status record.
-      std::function<void(hipStream_t)> ls_join;
-      if (!full) {
-        const size_t from = q.steps.size();
-        plan_sketch<T>(q, pl, sh, wb, S, s, Mcols + size_t(k) * s);
-        q.steps.push_back([=](hipStream_t st) {
-          ls_add_column(lsv, ss, mx, k, *ctol, bdt, st);
-          // regularised y_k and residual (Sec. 4.3); the breakdown test keeps
-          // the unregularised R factor
-          if (tik) ls_tikhonov(lsv, ss, mx, k, *ctol, -1.0, st);
-        });
-        ls_join = fork_steps(q, from, 1);
-      }
-      const int j0 = std::max(0, k - kt + 1);
-      std::vector<TT<T>> win(V.begin() + j0, V.begin() + k + 1);
-      double* hk = h + size_t(k) * kt;
-      plan_inner<T>(q, pl, sh, win, wb, hk, 1.0);
-      Blocks<T> ob;
-      ob.add(W, nullptr, 1.0);
-      for (size_t j = 0; j < win.size(); ++j) ob.add(win[j], hk + j, -1.0);
-      plan_roundsum<T>(q, pl, sh, ob, rcfg, omega_, V[k + 1], nullptr);
-      if (ls_join) q.steps.push_back(ls_join);
-      std::vector<const T*> pc = {W.core, V[k + 1].core};
-      const size_t off = pl.blob.add(pc);
-      const size_t cl = sh.core_len();
-      double* s2 = sumsq2 + 2 * k;
-      double* om = omega + k;
-      const double* resk = res + k;
-      const int* rk = V[k + 1].rank;
-      T* vc = V[k + 1].core;
-      IterStatus* sd = st_dev;
-      int* fl = flags;
-      double* hcol = Mcols + size_t(k) * lr;
-      double* dws = dot_scratch(ar, cl, 2);
-      q.steps.push_back([=](hipStream_t st) {
-        dot_batched<T>(bl->at<const T*>(off), bl->at<const T*>(off), cl, 2, 1.0, s2, dws, st);
-        if (fa) {
-          // Alg. 1: Hessenberg column (h_{1..k}, ||W||) in place of the sketch
-          hess_column(hk, k + 1, s2 + 1, hcol, ss, st);
-          ls_add_column(lsv, ss, mx, k, *ctol, bdt, st);
-          if (tik) ls_tikhonov(lsv, ss, mx, k, *ctol, -1.0, st);
-        }
-        iter_status(s2, fl, resk, rk, d, bdt, om, sd, st);
-        scale_copy<T>(vc, vc, cl, 1.0, nullptr, om, st);
-      });
-      iter.push_back(std::move(q));
+    scratch = std::make_unique<Arena>(ar);
+    const size_t mk = ar.mark();
+    iter.resize(maxiter);
+    late.resize(maxiter);
+    const int ahead = std::min(maxiter, std::max(kt, 1));
+    size_t tables = 0;
+    for (int k = 0; k < ahead; ++k) {
+      const size_t b0 = pl.blob.host.size();
+      plan_iter(pl, k);
+      tables = pl.blob.host.size() - b0;
       ar.rewind(mk);
+    }
+    for (int k = ahead; k < maxiter; ++k) {
+      late[k] = std::make_unique<Late>();
+      late[k]->room = tables + 32;  // (16 of alignment at either end)
     }
 
     // ---- final assembly X = RoundSum(sum_i y_i V_i) (sum_i y_i Z_i when flexible)
@@ -253,6 +218,97 @@ struct Cycle {
     plan_roundsum<T>(fin, pl, sh, fb, rcfg, omega_, dsol, &nb_final);
     // everything planned after the cycle lies past the iterations' scratch
     ar.seal();
+    scratch_end = ar.mark();
+    for (auto& l : late)
+      if (l) l->blob.dev = ar.alloc<unsigned char>(l->room);
+  }
+
+  // Plans iteration k (0-based) with the planner's arena at the scratch mark.
+  void plan_iter(Planner& pl, int k) {
+    Arena& ar = pl.ar;
+    Blob* bl = &pl.blob;
+    const int d = sh.d;
+    const bool flexible = pc.q > 0;
+    const int lr = ls_rows;
+    Seq q;
+    TT<T> Zk = V[k];
+    if (flexible) {
+      // flexible cycle (Sec. 3.4): Z_k = T(M(V_k)), and the operator acts on Z_k
+      Zk = Z[k];
+      plan_precond<T>(q, pl, sh, pc, V[k], Zk, rcfg_, om_);
+    }
+    Blocks<T> LV = plan_apply<T>(q, pl, sh, op_, Zk, transpose_);
+    plan_roundsum<T>(q, pl, sh, LV, rcfg_, om_, W, nullptr);
+    Blocks<T> wb;
+    wb.add(W, nullptr, 1.0);
+    const int ss = lr, mx = maxiter;
+    LsState lsv = ls;
+    const double* ctol = &conv_tol;
+    const double bdt = bd_tol;
+    const bool tik = tikhonov, fa = full;
+    // The sketch of W and the least-squares column (a3, a7) need only W:
+    // they run on a second side stream beside the inner products and the
+    // orthogonalisation RoundSum, and join before the status record.
+    std::function<void(hipStream_t)> ls_join;
+    if (!full) {
+      const size_t from = q.steps.size();
+      plan_sketch<T>(q, pl, sh, wb, S_, s, Mcols + size_t(k) * s);
+      q.steps.push_back([=](hipStream_t st) {
+        ls_add_column(lsv, ss, mx, k, *ctol, bdt, st);
+        // regularised y_k and residual (Sec. 4.3); the breakdown test keeps
+        // the unregularised R factor
+        if (tik) ls_tikhonov(lsv, ss, mx, k, *ctol, -1.0, st);
+      });
+      ls_join = fork_steps(q, from, 1);
+    }
+    const int j0 = std::max(0, k - kt + 1);
+    std::vector<TT<T>> win(V.begin() + j0, V.begin() + k + 1);
+    double* hk = h + size_t(k) * kt;
+    plan_inner<T>(q, pl, sh, win, wb, hk, 1.0);
+    Blocks<T> ob;
+    ob.add(W, nullptr, 1.0);
+    for (size_t j = 0; j < win.size(); ++j) ob.add(win[j], hk + j, -1.0);
+    plan_roundsum<T>(q, pl, sh, ob, rcfg_, om_, V[k + 1], nullptr);
+    if (ls_join) q.steps.push_back(ls_join);
+    std::vector<const T*> pc = {W.core, V[k + 1].core};
+    const size_t off = pl.blob.add(pc);
+    const size_t cl = sh.core_len();
+    double* s2 = sumsq2 + 2 * k;
+    double* om = omega + k;
+    const double* resk = res + k;
+    const int* rk = V[k + 1].rank;
+    T* vc = V[k + 1].core;
+    IterStatus* sd = st_dev;
+    int* fl = flags;
+    double* hcol = Mcols + size_t(k) * lr;
+    double* dws = dot_scratch(ar, cl, 2);
+    q.steps.push_back([=](hipStream_t st) {
+      dot_batched<T>(bl->at<const T*>(off), bl->at<const T*>(off), cl, 2, 1.0, s2, dws, st);
+      if (fa) {
+        // Alg. 1: Hessenberg column (h_{1..k}, ||W||) in place of the sketch
+        hess_column(hk, k + 1, s2 + 1, hcol, ss, st);
+        ls_add_column(lsv, ss, mx, k, *ctol, bdt, st);
+        if (tik) ls_tikhonov(lsv, ss, mx, k, *ctol, -1.0, st);
+      }
+      iter_status(s2, fl, resk, rk, d, bdt, om, sd, st);
+      scale_copy<T>(vc, vc, cl, 1.0, nullptr, om, st);
+    });
+    iter[k] = std::move(q);
+  }
+
+  // Enqueues iteration k, planned now if it was not planned ahead.
+  void run_iter(int k, hipStream_t st) {
+    if (late[k] && iter[k].steps.empty()) {
+      Late& l = *late[k];
+      Arena a = *scratch;
+      Planner pl(a, l.blob);
+      pl.bf16_factors = bf16_;
+      plan_iter(pl, k);
+      TK_CHECK(l.blob.host.size() <= l.room && a.used() <= scratch_end, kErrInvalidArg,
+               "internal: an iteration's plan outgrows its reservation");
+      TK_HIP(hipMemcpyAsync(l.blob.dev, l.blob.host.data(), l.blob.host.size(), hipMemcpyHostToDevice, st));
+    }
+    iter[k].run(st);
   }
 
   // Runs one cycle; returns (status, iterations).
@@ -272,7 +328,7 @@ struct Cycle {
     // converging cycle does not pay for an iteration it does not need.
     constexpr double kSpecMargin = 1e6;
     auto enqueue = [&](int k) {
-      iter[k].run(st);
+      run_iter(k, st);
       TK_HIP(hipMemcpyAsync(st_host + (k & 1), st_dev, sizeof(IterStatus), hipMemcpyDeviceToHost, st));
       TK_HIP(hipEventRecord(st_ev[k & 1], st));
     };
@@ -329,18 +385,19 @@ class Solver {
   std::unique_ptr<Cycle<float>> c32;
   Seq s_setup, s_x0, s_to_cycle, s_from_cycle, s_first_x, s_xupd[2], s_rnorm[2], s_rround[2], s_keep[2];
   double *bnorm2, *rnorm2;
-  double* host2 = nullptr;  // pinned scratch
+  void* pinned = nullptr;   // one allocation: the pieces below and the cycle's
+  double* host2 = nullptr;  // scratch
   // truncation tolerance of the refinement RoundSums, on the device so the
   // loop can tighten it (see solver_run); pinned staging for it and the ranks
   double* eps_out_dev = nullptr;
   double* host_eps = nullptr;
   int* host_rank = nullptr;
+  double* host_lam = nullptr;  // maxiter
+  IterStatus* host_st = nullptr;
   int xc = 0;
 
   ~Solver() {
-    if (host2) (void)hipHostFree(host2);
-    if (host_eps) (void)hipHostFree(host_eps);
-    if (host_rank) (void)hipHostFree(host_rank);
+    if (pinned) (void)hipHostFree(pinned);
   }
 };
 
@@ -373,9 +430,17 @@ SolverPtr make_solver(Arena& ar, const Shape& sh, const OpDev<double>& op, const
   s.rnorm2 = ar.alloc<double>(1);
   s.eps_out_dev = ar.alloc<double>(2);
   if (!ar.measuring()) {
-    TK_HIP(hipHostMalloc(reinterpret_cast<void**>(&s.host2), 2 * sizeof(double), 0));
-    TK_HIP(hipHostMalloc(reinterpret_cast<void**>(&s.host_eps), 2 * sizeof(double), 0));
-    TK_HIP(hipHostMalloc(reinterpret_cast<void**>(&s.host_rank), kMaxD * sizeof(int), 0));
+    static_assert(sizeof(IterStatus) % alignof(double) == 0 && kMaxD * sizeof(int) % alignof(double) == 0,
+                  "pieces of the pinned scratch stay aligned");
+    const size_t lam = sizeof(double) * cfg.maxiter;
+    TK_HIP(hipHostMalloc(&s.pinned, 4 * sizeof(double) + lam + 2 * sizeof(IterStatus) + kMaxD * sizeof(int), 0));
+    char* at = static_cast<char*>(s.pinned);
+    auto take = [&](size_t bytes) { return (at += bytes) - bytes; };
+    s.host2 = reinterpret_cast<double*>(take(2 * sizeof(double)));
+    s.host_eps = reinterpret_cast<double*>(take(2 * sizeof(double)));
+    s.host_lam = reinterpret_cast<double*>(take(lam));
+    s.host_st = reinterpret_cast<IterStatus*>(take(2 * sizeof(IterStatus)));
+    s.host_rank = reinterpret_cast<int*>(take(kMaxD * sizeof(int)));
   }
   Blob* bl = &s.blob;
 
@@ -430,6 +495,8 @@ SolverPtr make_solver(Arena& ar, const Shape& sh, const OpDev<double>& op, const
     c.s = cfg.s;
     c.tikhonov = cfg.tikhonov;
     c.full = cfg.method == 1;
+    c.st_host = s.host_st;
+    c.lam_host = s.host_lam;
     c.plan(pl, op, cfg.transpose, S, omega, precond);
     s.r = c.rhs;     // the cycle reads its right-hand side in place
     s.d64 = c.dsol;  // and leaves its solution in place
@@ -483,6 +550,8 @@ SolverPtr make_solver(Arena& ar, const Shape& sh, const OpDev<double>& op, const
     c.tikhonov = cfg.tikhonov;
     c.full = cfg.method == 1;
     c.bd_tol = 1e-6;
+    c.st_host = s.host_st;
+    c.lam_host = s.host_lam;
     c.plan(pl, s.op32, cfg.transpose, S32, O32, pc32);
     s.r = alloc_tt<double>(ar, sh);
     s.d64 = alloc_tt<double>(ar, sh);

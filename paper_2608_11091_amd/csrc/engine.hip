@@ -73,6 +73,8 @@ GemmTerm<T> term(const T* A, const T* B, const double* c1 = nullptr, const doubl
   return GemmTerm<T>{A, B, c1, c2, c3, scale};
 }
 
+constexpr long kSmallTiles = 256;  // 64 x 64 tiles below which a launch takes 32 x 32 ones (128 to 512: the same)
+
 template <typename T>
 void emit_gemm(Seq& q, Planner& pl, GemmDesc<T>&& g) {
   if (g.groups.empty()) return;
@@ -96,18 +98,27 @@ void emit_gemm(Seq& q, Planner& pl, GemmDesc<T>&& g) {
       gr.K = g.K;
     }
   }
-  const long tiles = long(ceil_div(g.M, 64)) * ceil_div(g.N, 64) * ng;
-  const long slabs = long(maxt) * ceil_div(g.K, 32);
+  L.bf16 = std::is_same<T, float>::value && pl.bf16_factors && g.factor_product;
+  // Tile: 32 x 32 while 64 x 64 ones would be fewer than the CUs (the 36
+  // products of a RoundSum of three rank-48 blocks at n = 512 took 300 us with
+  // the large tile, 210 with the small one); a very long reduction fills the
+  // chip with its splits and keeps the large tile, which reads less.
+  const long tiles64 = long(ceil_div(g.M, 64)) * ceil_div(g.N, 64) * ng;
+  const long slabs32 = long(maxt) * ceil_div(g.K, 32);
+  const bool small = !L.bf16 && tiles64 < kSmallTiles && slabs32 <= 256;
+  L.tile = small ? 32 : 64;
+  const long tiles = small ? long(ceil_div(g.M, 32)) * ceil_div(g.N, 32) * ng : tiles64;
+  const long slabs = small ? long(maxt) * ceil_div(g.K, 64) : slabs32;
   // Split-K for the path's small, long-K products.  With a reduction launch of
-  // its own (4 us) about two slabs per workgroup, from 8 slabs on (a
-  // 48 x 53 x 512 product took 44.9 / 16.4 / 12.1 / 11.5 us at 1 / 4 / 8 / 16
-  // splits, kernel and reduction).  Where the consumer sums the partials, one
-  // slab per workgroup up to 16, then two (a workgroup spends 2 us a slab: the
-  // 15 x 15 Gram of 15 slabs took 37 us whole); beyond 32 partials the
-  // consumer's one workgroup would read longer than it saves, so products with
-  // more than 8 slabs left per workgroup take up to 256 of them and a launch
-  // that folds the partials to 16.  Products that already fill the chip or have
-  // little K run whole.
+  // its own (3 to 4 us) one slab per workgroup, from 4 slabs on (twenty
+  // iterations at n = 256, four slabs of 64 a factor product: 14.4 ms split,
+  // 14.7 whole); the large tile two slabs, from 8 on.  Where the consumer sums
+  // the partials, one slab per workgroup up to 16, then two (a workgroup
+  // spends 1 to 2 us a slab: the 15 x 15 Gram of 15 slabs took 37 us whole);
+  // beyond 32 partials the consumer's one workgroup would read longer than it
+  // saves, so products with more than 8 slabs left per workgroup take up to
+  // 256 of them and a launch that folds the partials to 16.  Products that
+  // already fill the chip or have little K run whole.
   int splits = 1, folds = 0;
   if (tiles < 256) {
     const long room = std::max<long>(1, 512 / tiles);
@@ -118,8 +129,8 @@ void emit_gemm(Seq& q, Planner& pl, GemmDesc<T>&& g) {
       } else if (slabs >= 2) {
         splits = int(std::min<long>({slabs <= 16 ? slabs : std::max<long>(16, slabs / 2), room, 32}));
       }
-    } else if (slabs >= 8 && g.mblk == 0) {
-      splits = int(std::min<long>({slabs / 2, room, 32}));
+    } else if (slabs >= (small ? 4 : 8) && g.mblk == 0) {
+      splits = int(std::min<long>({small ? slabs : slabs / 2, room, 32}));
     }
     splits = std::max(1, splits);
   }
@@ -138,7 +149,6 @@ void emit_gemm(Seq& q, Planner& pl, GemmDesc<T>&& g) {
   L.beta = g.beta;
   L.splits = splits;
   L.partial = partial;
-  L.bf16 = std::is_same<T, float>::value && pl.bf16_factors && g.factor_product;
   L.ngroups = ng;
   L.mblk = g.mblk;
   L.astr = g.astr;

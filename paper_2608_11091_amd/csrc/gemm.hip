@@ -1,14 +1,18 @@
 // Grouped GEMM kernel on MFMA (v_mfma_f64_16x16x4f64 / v_mfma_f32_16x16x4f32).
 //
-// Tile: 64 x 64 outputs per workgroup of 256 threads (4 waves).  A wave owns a
-// strip of 16 rows or 16 columns of the tile and up to four MFMA 16 x 16
-// accumulators along it; the strips run along the shorter live side, so a
-// product with 15, 32 or 37 columns issues 1, 2 or 3 MFMAs a step in place of
-// 4 (FP64 16x16x4: 64 cycles each on its SIMD).  K is staged through LDS in
-// slabs of 32 (16 in the bf16 form) with global loads coalesced along the
-// contiguous dimension of each operand; rows and k steps beyond the operands
-// are neither loaded nor multiplied, and the alpha of a term is folded into
-// the A slab while it is staged.
+// Tile: 64 x 64 outputs per workgroup of 256 threads (4 waves), or 32 x 32 where
+// that leaves most of the chip idle.  In the large tile a wave owns a strip of
+// 16 rows or 16 columns and up to four MFMA 16 x 16 accumulators along it; the
+// strips run along the shorter live side, so a product with 15, 32 or 37
+// columns issues 1, 2 or 3 MFMAs a step in place of 4 (FP64 16x16x4: 64 cycles
+// each on its SIMD).  In the small tile a wave owns one accumulator.  K is
+// staged through LDS in slabs of 32 (large tile), 64 (small tile) or 16 (bf16
+// form), eight loads per operand and thread, coalesced along the contiguous
+// dimension of each operand; halves of a slab and k steps beyond the operands
+// are neither loaded nor multiplied, and the alpha of a term is folded into the
+// A slab while it is staged.  A small launch is bound by its chain of
+// latencies (table, operands, LDS, MFMAs, store): the small tile has a quarter
+// of the MFMAs of a wave and one slab where the large one has two.
 #include "gemm.hpp"
 
 #include <type_traits>
@@ -48,7 +52,7 @@ __device__ __forceinline__ f4 mfma_bf16(s4 a, s4 b, f4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, c, 0, 0, 0);
 }
 
-constexpr int BM = 64, BN = 64, NT = 256;
+constexpr int NT = 256;
 
 // Rows in slices (GemmLaunch::mblk); the quotient by a multiplication, exact
 // while rows * mblk < 2^32.
@@ -77,18 +81,19 @@ __device__ __forceinline__ bool uniform_zero(double x) {
 // second pass sums the partials in split order.  (Summing them in the last
 // workgroup to arrive at a tile needs device-scope fences, whose L2
 // write-back across the XCDs cost more than the second launch.)
-template <typename T, bool TA, bool TB, bool BF = false>
+template <typename T, bool TA, bool TB, int TS, bool BF = false>
 __global__ __launch_bounds__(NT) void gemm_kernel(int M, int N, int K, int lda, int ldb, int ldc,
                                                   const GemmTerm<T>* __restrict__ terms,
                                                   const GemmGroup<T>* __restrict__ groups, double beta,
                                                   int splits, T* __restrict__ partial, size_t pstride,
                                                   int max_terms, int uniform_terms, bool mixed, RowBlocks rb_) {
   static_assert(!BF || sizeof(T) == 4, "bf16 operands with FP32 storage only");
-  // K depth of a slab: 32 (8 loads per operand and thread in flight at once,
-  // half the slab iterations of a 16-deep slab on the path's short-K
-  // workgroups); 16 for the bf16 form, one 16-deep MFMA per output tile
-  constexpr int KB = BF ? 16 : 32;
+  static_assert(!BF || TS == 64, "bf16 operands with the large tile only");
+  // K depth of a slab: 8 loads per operand and thread in flight at once (16
+  // for the bf16 form, one 16-deep MFMA per output tile)
+  constexpr int BM = TS, BN = TS, KB = BF ? 16 : TS == 64 ? 32 : 64;
   constexpr int SA = (BM * KB) / NT, SB = (BN * KB) / NT;  // staged elements per thread
+  constexpr int NACC = TS == 64 ? 4 : 1;
   constexpr int BKP = 16 + 4;  // bf16 row: 16 k values + 4 pad (40 bytes: conflict-free 8-byte reads)
   static_assert(BM == BN, "one row length for both slabs");
   __shared__ T slabs[2][BF ? 1 : KB][BM + 1];  // [A, B][k][m or n]
@@ -120,9 +125,9 @@ __global__ __launch_bounds__(NT) void gemm_kernel(int M, int N, int K, int lda, 
   }
 
   typedef typename Acc<T>::type AT;
-  AT acc[4];
+  AT acc[NACC];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < NACC; ++i)
 #pragma unroll
     for (int v = 0; v < 4; ++v) acc[i][v] = T(0);
 
@@ -133,15 +138,19 @@ __global__ __launch_bounds__(NT) void gemm_kernel(int M, int N, int K, int lda, 
   const int sb = sp * per, se = min(total, sb + per);
   const int Ml = min(BM, M - m0), Nl = min(BN, N - n0);  // live rows and columns of the tile
   const int mt = (Ml + 15) >> 4, nt = (Nl + 15) >> 4;
-  const bool by_rows = nt < mt;  // a wave owns 16 rows (else 16 columns) of the tile
-  const int live = by_rows ? (wid < mt ? nt : 0) : (wid < nt ? mt : 0);  // its accumulators
+  // large tile: a wave owns 16 rows (or 16 columns) of it and `live`
+  // accumulators; small tile: one of its 2 x 2 accumulators
+  const bool by_rows = nt < mt;
+  const int wi = wid & 1, wj = wid >> 1;
+  const int live = TS == 32 ? (wi < mt && wj < nt ? 1 : 0) : by_rows ? (wid < mt ? nt : 0) : (wid < nt ? mt : 0);
 
   // staging coordinates of this thread (fixed over slabs): element i of A is
   // row am0 + i * amd, k ak0 + i * akd of the slab
-  const int am0 = TA ? tid / KB : lane, ak0 = TA ? tid % KB : wid;
-  constexpr int amd = TA ? NT / KB : 0, akd = TA ? 0 : 4;
-  const int bn0 = TB ? lane : tid / KB, bk0 = TB ? wid : tid % KB;
-  constexpr int bnd = TB ? 0 : NT / KB, bkd = TB ? 4 : 0;
+  const int tm0 = tid % TS, tk0 = TS == 64 ? wid : tid / TS;
+  const int am0 = TA ? tid / KB : tm0, ak0 = TA ? tid % KB : tk0;
+  constexpr int amd = TA ? NT / KB : 0, akd = TA ? 0 : NT / TS;
+  const int bn0 = TB ? tm0 : tid / KB, bk0 = TB ? tk0 : tid % KB;
+  constexpr int bnd = TB ? 0 : NT / KB, bkd = TB ? NT / TS : 0;
   // Slab s is fetched into registers one slab ahead of its use, so its global
   // loads are in flight while the matrix cores work on slab s - 1; the record
   // of the next term is fetched one term ahead, and a term's coefficients are
@@ -269,6 +278,22 @@ __global__ __launch_bounds__(NT) void gemm_kernel(int M, int N, int K, int lda, 
         for (int j = 0; j < 4; ++j)
           if (j < live) acc[j] = mfma_bf16(*reinterpret_cast<const s4*>(&Asb[j * 16 + c][kq]), b, acc[j]);
       }
+    } else if constexpr (TS == 32) {
+      if (live) {
+#pragma unroll
+        for (int k0 = 0; k0 < KB; k0 += 16) {
+          if (k0 >= kl) continue;
+          T x[4], y[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const int kr = k0 + 4 * u + (lane >> 4), c = lane & 15;
+            x[u] = As[kr][wi * 16 + c];
+            y[u] = Bs[kr][wj * 16 + c];
+          }
+#pragma unroll
+          for (int u = 0; u < 4; ++u) acc[0] = mfma(x[u], y[u], acc[0]);
+        }
+      }
     } else {
       // strip operand x (one 16-wide strip) against y (`live` strips)
       const auto& xs = slabs[by_rows ? 0 : 1];
@@ -307,9 +332,9 @@ __global__ __launch_bounds__(NT) void gemm_kernel(int M, int N, int K, int lda, 
   // sits in lane c + 16*(r/4), element r%4; for FP64 in lane c + 16*(r%4),
   // element r/4.
 #pragma unroll
-  for (int j = 0; j < 4; ++j)
+  for (int j = 0; j < NACC; ++j)
     if (j < live) {
-      const int ti = by_rows ? wid : j, tj = by_rows ? j : wid;
+      const int ti = TS == 32 ? wi : by_rows ? wid : j, tj = TS == 32 ? wj : by_rows ? j : wid;
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const int r16 = Acc<T>::f64 ? 4 * v + (lane >> 4) : 4 * (lane >> 4) + v;
@@ -358,8 +383,16 @@ __global__ void splitk_reduce(int M, int N, int ldc, const GemmGroup<T>* __restr
   }
   const unsigned MN = unsigned(M) * unsigned(N);
   for (unsigned e = blockIdx.x * blockDim.x + threadIdx.x; e < MN; e += gridDim.x * blockDim.x) {
+    // eight loads in flight; the additions keep their order
+    const GPtr<T> p = (GPtr<T>)(partial + (size_t)g * splits * pstride + e);
     T s = T(0);
-    for (int sp = 0; sp < splits; ++sp) s += partial[((size_t)g * splits + sp) * pstride + e];
+    for (int sp = 0; sp < splits; sp += 8) {
+      T v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = p[(size_t)min(sp + u, splits - 1) * pstride];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) s += sp + u < splits ? v[u] : T(0);
+    }
     const int row = int(e % unsigned(M)), col = int(e / unsigned(M));
     T* c = grp.C + row + (size_t)col * ldc;
     *c = (beta == 0.0) ? s : T(beta) * (*c) + s;
@@ -371,7 +404,8 @@ __global__ void splitk_reduce(int M, int N, int ldc, const GemmGroup<T>* __restr
 template <typename T>
 void gemm_run(const GemmLaunch<T>& g, hipStream_t st) {
   if (g.ngroups <= 0 || g.M <= 0 || g.N <= 0) return;
-  dim3 grid(ceil_div(g.M, BM), ceil_div(g.N, BN), g.ngroups * g.splits);
+  TK_CHECK(g.tile == 64 || (g.tile == 32 && !g.bf16), kErrInvalidArg, "internal: product tile");
+  dim3 grid(ceil_div(g.M, g.tile), ceil_div(g.N, g.tile), g.ngroups * g.splits);
   T* part = g.splits > 1 ? g.partial : nullptr;
   const size_t pstride = (size_t)g.M * g.N;
   RowBlocks rb{};
@@ -385,21 +419,22 @@ void gemm_run(const GemmLaunch<T>& g, hipStream_t st) {
   }
   timer_begin(kKcGemm, st, g.flops);
   TK_CHECK(!g.bf16 || sizeof(T) == 4, kErrUnsupported, "bf16 operands need FP32 storage");
-#define TK_GEMM_CASE(TA, TB, BF)                                                                          \
-  if (g.ta == TA && g.tb == TB && g.bf16 == BF)                                                            \
-    hipLaunchKernelGGL((gemm_kernel<T, TA, TB, BF && sizeof(T) == 4>), grid, dim3(NT), 0, st, g.M, g.N, g.K, \
-                       g.lda, g.ldb, g.ldc, g.terms, g.groups, g.beta, g.splits, part, pstride, g.max_terms,        \
+#define TK_GEMM_CASE(TA, TB, TS, BF)                                                                           \
+  if (g.ta == TA && g.tb == TB && g.tile == TS && g.bf16 == BF)                                                \
+    hipLaunchKernelGGL((gemm_kernel<T, TA, TB, TS, BF && sizeof(T) == 4>), grid, dim3(NT), 0, st, g.M, g.N, g.K, \
+                       g.lda, g.ldb, g.ldc, g.terms, g.groups, g.beta, g.splits, part, pstride, g.max_terms,   \
                        g.uniform_terms, g.mixed, rb);
-  TK_GEMM_CASE(false, false, false)
-  TK_GEMM_CASE(false, true, false)
-  TK_GEMM_CASE(true, false, false)
-  TK_GEMM_CASE(true, true, false)
+#define TK_GEMM_CASES(TS, BF)         \
+  TK_GEMM_CASE(false, false, TS, BF)  \
+  TK_GEMM_CASE(false, true, TS, BF)   \
+  TK_GEMM_CASE(true, false, TS, BF)   \
+  TK_GEMM_CASE(true, true, TS, BF)
+  TK_GEMM_CASES(32, false)
+  TK_GEMM_CASES(64, false)
   if constexpr (sizeof(T) == 4) {
-    TK_GEMM_CASE(false, false, true)
-    TK_GEMM_CASE(false, true, true)
-    TK_GEMM_CASE(true, false, true)
-    TK_GEMM_CASE(true, true, true)
+    TK_GEMM_CASES(64, true)
   }
+#undef TK_GEMM_CASES
 #undef TK_GEMM_CASE
   TK_LAUNCH_CHECK();
   if (g.folds > 0) {

@@ -40,6 +40,7 @@ struct GemmLaunch {
   const GemmGroup<T>* groups = nullptr; // device
   int ngroups = 0;
   double beta = 0.0;
+  int tile = 64;           // side of a workgroup's output tile: 64 or 32
   int splits = 1;          // split of the (term x K-slab) space (>1 uses `partial` + a reduction pass)
   T* partial = nullptr;    // ngroups * splits * M * N
   T* folded = nullptr;     // folds > 0: the deferred partials are first summed into folds of them here

@@ -36,6 +36,7 @@ struct GemmDesc {
   int mblk = 0;                        // rows in slices (see GemmLaunch)
   long astr = 0, cstr = 0;
   bool own_dims = false;               // every group has dims of its own (group_dims)
+  bool any_ops = false;                // and transposes of its own (group_ops); small launches only
   bool factor_product = false;         // a product with a Tucker factor (BF16 in the BF16-factor form)
   // optional: the only consumer of C sums the split-K partials itself, which
   // saves the reduction launch (C is then not written); needs beta = 0,
@@ -61,6 +62,10 @@ struct GemmDesc {
     g.ldc = lc;
     own_dims = true;
   }
+  void group_ops(bool a, bool b) {
+    groups.back().ops = (a ? 1 : 0) + (b ? 2 : 0);
+    any_ops = true;
+  }
   void group1(T* C, const T* A, const T* B, const double* c1 = nullptr, const double* c2 = nullptr,
               const double* c3 = nullptr, double scale = 1.0) {
     group(C, {GemmTerm<T>{A, B, c1, c2, c3, scale}});
@@ -74,6 +79,8 @@ GemmTerm<T> term(const T* A, const T* B, const double* c1 = nullptr, const doubl
 }
 
 constexpr long kSmallTiles = 256;  // 64 x 64 tiles below which a launch takes 32 x 32 ones (128 to 512: the same)
+
+constexpr long kLongSlabs = 256;   // slabs of 32 from which a product is split further than a consumer would sum
 
 template <typename T>
 void emit_gemm(Seq& q, Planner& pl, GemmDesc<T>&& g) {
@@ -104,11 +111,16 @@ void emit_gemm(Seq& q, Planner& pl, GemmDesc<T>&& g) {
   // the large tile, 210 with the small one); a very long reduction fills the
   // chip with its splits and keeps the large tile, which reads less.
   const long tiles64 = long(ceil_div(g.M, 64)) * ceil_div(g.N, 64) * ng;
-  const long slabs32 = long(maxt) * ceil_div(g.K, 32);
-  const bool small = !L.bf16 && tiles64 < kSmallTiles && slabs32 <= 256;
+  long slabs32 = 0, slabs64 = 0;  // of the longest group
+  for (auto& gr : g.groups) {
+    slabs32 = std::max(slabs32, long(gr.t1 - gr.t0) * ceil_div(gr.K, 32));
+    slabs64 = std::max(slabs64, long(gr.t1 - gr.t0) * ceil_div(gr.K, 64));
+  }
+  const bool small = !L.bf16 && ((tiles64 < kSmallTiles && slabs32 <= kLongSlabs) || g.any_ops);
   L.tile = small ? 32 : 64;
+  L.any_ops = g.any_ops;
   const long tiles = small ? long(ceil_div(g.M, 32)) * ceil_div(g.N, 32) * ng : tiles64;
-  const long slabs = small ? long(maxt) * ceil_div(g.K, 64) : slabs32;
+  const long slabs = small ? slabs64 : slabs32;
   // Split-K for the path's small, long-K products.  With a reduction launch of
   // its own (3 to 4 us) one slab per workgroup, from 4 slabs on (twenty
   // iterations at n = 256, four slabs of 64 a factor product: 14.4 ms split,
@@ -123,7 +135,7 @@ void emit_gemm(Seq& q, Planner& pl, GemmDesc<T>&& g) {
   if (tiles < 256) {
     const long room = std::max<long>(1, 512 / tiles);
     if (g.split_out) {
-      if (slabs > 256 && room >= 64) {
+      if (!small && slabs > kLongSlabs && room >= 64) {
         splits = int(std::min<long>({ceil_div(slabs, 4), room, 256}));
         folds = 16;
       } else if (slabs >= 2) {
@@ -270,6 +282,27 @@ void emit_ttm(Seq& q, Planner& pl, int d, const int* dims, int k, int newdim, co
   emit_gemm(q, pl, std::move(g));
 }
 
+// Adds the group G = X_(k) Y_(k)^T (ld ldg) of two tensors of dims `dims` to a
+// launch whose groups differ in layout (N = dims[k] is common).
+template <typename T>
+void add_unfold_gram(GemmDesc<T>& g, int d, const int* dims, int k, const T* X, const T* Y, T* G, int ldg) {
+  long pre = 1, post = 1;
+  for (int j = 0; j < k; ++j) pre *= dims[j];
+  for (int j = k + 1; j < d; ++j) post *= dims[j];
+  const int mid = dims[k];
+  if (post == 1) {
+    g.group1(G, X, Y);
+    g.group_dims(mid, int(pre), mid, mid, ldg);
+    g.group_ops(false, true);
+    return;
+  }
+  std::vector<GemmTerm<T>> ts;
+  for (long p = 0; p < pre; ++p) ts.push_back(term<T>(X + size_t(p) * post * mid, Y + size_t(p) * post * mid));
+  g.group(G, ts);
+  g.group_dims(mid, int(post), int(post), int(post), ldg);
+  g.group_ops(true, false);
+}
+
 // G = X_(k) Y_(k)^T (mid x mid, ld ldg) for two tensors of dims `dims`.
 template <typename T>
 void emit_unfold_gram(Seq& q, Planner& pl, int d, const int* dims, int k, const T* X, const T* Y, T* G, int ldg,
@@ -398,7 +431,9 @@ void plan_krp_range(Seq& q, Planner& pl, const Shape& sh, const Blocks<T>& in, c
   T* Zl = ar.alloc<T>(size_t(nb) * P * w);
   T* Zf = ar.alloc<T>(size_t(nb) * P * w);
   {
-    GemmDesc<T> g;  // Zlast_b = G_b x_d M_bd^T : (P x w)
+    // Zlast_b = G_b x_d M_bd^T and Zfirst_b = G_b x_1 M_b1^T (P x w): one launch
+    // while the two would not fill the chip
+    GemmDesc<T> g;
     g.ta = true;
     g.tb = false;
     g.M = int(P);
@@ -408,22 +443,27 @@ void plan_krp_range(Seq& q, Planner& pl, const Shape& sh, const Blocks<T>& in, c
     g.ldb = rc;
     g.ldc = int(P);
     g.nb = nb_active;
-    g.ngroups_of = [](int a) { return a; };
-    for (int b = 0; b < nb; ++b) g.group1(Zl + size_t(b) * P * w, in.core[b], Mp(b, d - 1));
-    emit_gemm(q, pl, std::move(g));
-    GemmDesc<T> h;  // Zfirst_b = G_b x_1 M_b1^T : (P x w)
+    const bool one = long(ceil_div(g.M, 64)) * ceil_div(w, 64) * 2 * nb < kSmallTiles;
+    const int per = one ? 2 : 1;
+    g.ngroups_of = [per](int a) { return per * a; };
+    GemmDesc<T> h = g;
     h.ta = false;
-    h.tb = false;
-    h.M = int(P);
-    h.N = w;
-    h.K = rc;
     h.lda = int(P);
-    h.ldb = rc;
-    h.ldc = int(P);
-    h.nb = nb_active;
-    h.ngroups_of = [](int a) { return a; };
-    for (int b = 0; b < nb; ++b) h.group1(Zf + size_t(b) * P * w, in.core[b], Mp(b, 0));
-    emit_gemm(q, pl, std::move(h));
+    for (int b = 0; b < nb; ++b) {
+      g.group1(Zl + size_t(b) * P * w, in.core[b], Mp(b, d - 1));
+      if (one) {
+        g.group_dims(int(P), rc, rc, rc, int(P));
+        g.group_ops(true, false);
+      }
+      GemmDesc<T>& f = one ? g : h;
+      f.group1(Zf + size_t(b) * P * w, in.core[b], Mp(b, 0));
+      if (one) {
+        g.group_dims(int(P), rc, int(P), rc, int(P));
+        g.group_ops(false, false);
+      }
+    }
+    emit_gemm(q, pl, std::move(g));
+    if (!one) emit_gemm(q, pl, std::move(h));
   }
   T* Tb = ar.alloc<T>(size_t(nb) * d * rc * w);
   auto Tp = [&](int b, int k) { return Tb + (size_t(b) * d + k) * rc * w; };
@@ -474,33 +514,44 @@ void plan_krp_range(Seq& q, Planner& pl, const Shape& sh, const Blocks<T>& in, c
   emit_gemm(q, pl, std::move(g));
 }
 
+// Products W_bk = P_k^T U_bk (w x rc, block-major) of per-mode matrices P_k (n_k
+// x >= w, column-major) with the factors of a block sum, one launch; groups
+// ordered by block, so the active ones are a prefix.
+template <typename T>
+void emit_factor_products(Seq& q, Planner& pl, const Shape& sh, const Blocks<T>& in,
+                          const std::array<const T*, kMaxD>& Pm, int w, T* Wb, const int* nb_active) {
+  const int d = sh.d, rc = sh.rc, nb = in.size();
+  GemmDesc<T> g;
+  g.ta = true;
+  g.tb = false;
+  g.N = rc;
+  g.nb = nb_active;
+  g.ngroups_of = [d](int a) { return a * d; };
+  for (int b = 0; b < nb; ++b)
+    for (int k = 0; k < d; ++k) {
+      g.group1(Wb + (size_t(b) * d + k) * w * rc, Pm[k], in.U[b][k]);
+      g.group_dims(w, sh.n[k], sh.n[k], sh.n[k], w);
+    }
+  g.factor_product = true;
+  emit_gemm(q, pl, std::move(g));
+}
+
 // Core projection of a block sum onto per-mode matrices P_k (n_k x >= w,
 // column-major): C = sum_b coef_b G_b x_1 (P_1^T U_b1) ... x_d (P_d^T U_bd),
 // a w^d row-major core (the RoundSum core of Sec. 3.1 with P_k = the range
 // basis; the sketched core of the multilinear Nystrom method with P_k = Psi_k).
 template <typename T>
 void plan_core_projection(Seq& q, Planner& pl, const Shape& sh, const Blocks<T>& in, const double* coef,
-                          const std::array<const T*, kMaxD>& Pm, int w, T* C, const int* nb_active) {
+                          const std::array<const T*, kMaxD>& Pm, int w, T* C, const int* nb_active, const T* W) {
   const int d = sh.d, rc = sh.rc, nb = in.size();
   TK_CHECK(d >= 2, kErrUnsupported, "d = 1");
   Arena& ar = pl.ar;
-  T* Wb = ar.alloc<T>(size_t(nb) * d * w * rc);
-  auto Wp = [&](int b, int k) { return Wb + (size_t(b) * d + k) * w * rc; };
-  {
-    GemmDesc<T> g;
-    g.ta = true;
-    g.tb = false;
-    g.N = rc;
-    g.nb = nb_active;
-    g.ngroups_of = [d](int a) { return a * d; };
-    for (int b = 0; b < nb; ++b)
-      for (int k = 0; k < d; ++k) {
-        g.group1(Wp(b, k), Pm[k], in.U[b][k]);
-        g.group_dims(w, sh.n[k], sh.n[k], sh.n[k], w);
-      }
-    g.factor_product = true;
-    emit_gemm(q, pl, std::move(g));
+  if (W == nullptr) {
+    T* Wb = ar.alloc<T>(size_t(nb) * d * w * rc);
+    emit_factor_products<T>(q, pl, sh, in, Pm, w, Wb, nb_active);
+    W = Wb;
   }
+  auto Wp = [&](int b, int k) { return W + (size_t(b) * d + k) * w * rc; };
   // after the TTM of mode k (k = d-1 .. 1) the block tensor has dims
   // (rc^k, w^(d-k)); size the two ping-pong buffers for the largest
   size_t tmplen = 0;
@@ -734,10 +785,7 @@ RoundSumOut<T> plan_roundsum(Seq& q, Planner& pl, const Shape& sh, const Blocks<
       T* Gc = ar.alloc<T>(size_t(ldc) * NM * d);
       T* lam = ar.alloc<T>(size_t(std::max(NM, n)) * d);
       q.steps.push_back([=](hipStream_t st) {
-        // the flags against the register order first, then enable / nact
-        // against the compacted capacity (the second call overwrites them)
-        gram_prep(bl->at<const int*>(off_ranks), nbA(), d, kEigRegMax, enable, nact, st, skip_reg, skip_gm);
-        gram_prep(bl->at<const int*>(off_ranks), nbA(), d, NM, enable, nact, st);
+        gram_prep(bl->at<const int*>(off_ranks), nbA(), d, NM, kEigRegMax, enable, nact, skip_reg, skip_gm, st);
       });
       {
         GemmDesc<T> g;
@@ -909,50 +957,51 @@ RoundSumOut<T> plan_roundsum(Seq& q, Planner& pl, const Shape& sh, const Blocks<
       });
     }
   }
+  T* Wbas = nullptr;  // Q_k^T U_bk, where the certificate has formed them
   if (use_cert) {
     // Rank certificate (Courant-Fischer): for Q_k' = the first cap columns of
     // the orthonormal range basis, lambda_cap(G_k) >= lambda_min(Q_k'^T G_k Q_k')
     // for the rule's Gram G_k = sum_b w_b^2 U_bk U_bk^T, so a Cholesky
     // factorisation of Q_k'^T G_k Q_k' - theta I settles r~_k >= cap without the
     // spectrum (rank_certificate).  theta covers the rounding of
-    // P_bk = w_b Q_k'^T U_bk (inner dimension n) and of sum_b P_bk P_bk^T
+    // P_bk = Q_k'^T U_bk (inner dimension n) and of sum_b w_b^2 P_bk P_bk^T
     // (inner dimension at most nb rc): 4 (n sqrt(cap) + nb rc) u tr(G_k).
+    // The core projection's products W_bk = Q_k^T U_bk hold Q_k'^T U_bk in their
+    // first cap rows, so they are formed here, at the full width, and their rows
+    // beyond s zeroed with the bases' columns below (the BF16-factor form rounds
+    // W's operands and forms the certificate's products apart).
     const int cp_ = sh.cap;
-    T* Pm = ar.alloc<T>(size_t(nb) * d * cp_ * rc);
+    const bool share = !pl.bf16_factors;
+    const int ldw = share ? sc : cp_;
+    T* Wc = ar.alloc<T>(size_t(nb) * d * ldw * rc);
     T* Hc = ar.alloc<T>(size_t(d) * cp_ * cp_);
     {
-      // P_bk (cap x rc); groups ordered by block, so the active ones are a prefix
-      GemmDesc<T> g;
-      g.ta = true;
-      g.tb = false;
-      g.N = rc;
-      g.nb = nb_active;
-      g.ngroups_of = [d](int a) { return a * d; };
-      for (int b = 0; b < nb; ++b)
-        for (int k = 0; k < d; ++k) {
-          g.group1(Pm + (size_t(k) * nb + b) * cp_ * rc, Uh[k], in.U[b][k], w + b);
-          g.group_dims(cp_, sh.n[k], sh.n[k], sh.n[k], cp_);
-        }
-      emit_gemm(q, pl, std::move(g));
+      std::array<const T*, kMaxD> Uc{};
+      for (int k = 0; k < d; ++k) Uc[k] = Uh[k];
+      const bool bf = pl.bf16_factors;
+      pl.bf16_factors = false;
+      emit_factor_products<T>(q, pl, sh, in, Uc, ldw, Wc, nb_active);
+      pl.bf16_factors = bf;
     }
+    if (share) Wbas = Wc;
     {
-      // H_k = sum_b P_bk P_bk^T (cap x cap)
+      // H_k = sum_b w_b^2 P_bk P_bk^T (cap x cap) with P_bk = Q_k'^T U_bk
       GemmDesc<T> g;
       g.ta = false;
       g.tb = true;
       g.M = cp_;
       g.N = cp_;
       g.K = rc;
-      g.lda = cp_;
-      g.ldb = cp_;
+      g.lda = ldw;
+      g.ldb = ldw;
       g.ldc = cp_;
       g.nb = nb_active;
       g.terms_are_blocks = nb_active != nullptr;
       for (int k = 0; k < d; ++k) {
         std::vector<GemmTerm<T>> ts;
         for (int b = 0; b < nb; ++b) {
-          const T* P = Pm + (size_t(k) * nb + b) * cp_ * rc;
-          ts.push_back(term<T>(P, P));
+          const T* P = Wc + (size_t(b) * d + k) * ldw * rc;
+          ts.push_back(term<T>(P, P, w + b, w + b));
         }
         g.group(Hc + size_t(k) * cp_ * cp_, ts);
       }
@@ -979,6 +1028,10 @@ RoundSumOut<T> plan_roundsum(Seq& q, Planner& pl, const Shape& sh, const Blocks<
       wz.U[k] = Uh[k];
       wz.n[k] = sh.n[k];
     }
+    if (Wbas) {
+      wz.W = Wbas;
+      wz.wcols = nb * d * rc;
+    }
     q.steps.push_back([=](hipStream_t st) { width_and_zero<T>(wz, d, sc, rt_, p_, cap_, fs_, s_dev, st); });
   }
   // --- 4. core projection C^ = sum_b c_b G_b x_k (U^_k^T U_bk)
@@ -987,7 +1040,7 @@ RoundSumOut<T> plan_roundsum(Seq& q, Planner& pl, const Shape& sh, const Blocks<
   {
     std::array<const T*, kMaxD> Uc{};
     for (int k = 0; k < d; ++k) Uc[k] = Uh[k];
-    plan_core_projection<T>(q, pl, sh, in, coef, Uc, sc, Cb[0], nb_active);
+    plan_core_projection<T>(q, pl, sh, in, coef, Uc, sc, Cb[0], nb_active, Wbas);
   }
   if (!use_cert && overlap) {
     // The rule's eigensolves ran beside steps 2-4: join them, then keep the
@@ -1033,13 +1086,26 @@ RoundSumOut<T> plan_roundsum(Seq& q, Planner& pl, const Shape& sh, const Blocks<
   {
     std::vector<EigTask<T>> et(d);
     int in_splits = 1;
+    // the eigensolver sums the Grams' split-K partials itself; one launch for
+    // all modes while their reductions are short (a middle mode's terms end
+    // inside a slab: up to twice the slabs of the others; 25 -> 13 us at
+    // s = 53)
+    const bool one = 2 * long(ceil_div(int(sclen / size_t(sc)), 32)) <= kLongSlabs;
+    SplitOut<T> all;
+    if (one) {
+      GemmDesc<T> g;
+      g.N = sc;
+      for (int k = 0; k < d; ++k) add_unfold_gram<T>(g, d, dims, k, Cb[0], Cb[0], G1 + size_t(k) * sc * sc, sc);
+      g.split_out = &all;
+      emit_gemm(q, pl, std::move(g));
+    }
     for (int k = 0; k < d; ++k) {
       V1[k] = ar.alloc<T>(size_t(sc) * sc);
       V2[k] = ar.alloc<T>(size_t(sc) * sc);
       U12[k] = ar.alloc<T>(size_t(sc) * sc);
-      // the eigensolver sums the Gram's split-K partials itself
-      SplitOut<T> so;
-      emit_unfold_gram<T>(q, pl, d, dims, k, Cb[0], Cb[0], G1 + size_t(k) * sc * sc, sc, 1.0, &so);
+      SplitOut<T> so = all;
+      if (one && all.part) so.part = all.part + k * size_t(all.splits) * all.stride;
+      if (!one) emit_unfold_gram<T>(q, pl, d, dims, k, Cb[0], Cb[0], G1 + size_t(k) * sc * sc, sc, 1.0, &so);
       et[k] = EigTask<T>{};
       et[k].A = G1 + size_t(k) * sc * sc;
       et[k].lda = sc;
@@ -1048,7 +1114,7 @@ RoundSumOut<T> plan_roundsum(Seq& q, Planner& pl, const Shape& sh, const Blocks<
       et[k].part = so.part;
       et[k].splits = so.splits;
       et[k].pstride = so.stride;
-      in_splits = std::max(in_splits, so.splits);  // equal for every mode (same K)
+      in_splits = std::max(in_splits, so.splits);
     }
     const size_t off = blob.add(et);
     q.steps.push_back([=](hipStream_t st) { jacobi_eig<T>(bl->at<EigTask<T>>(off), d, sc, true, st, in_splits); });
@@ -1699,7 +1765,7 @@ void plan_precond(Seq& q, Planner& pl, const Shape& sh, const PrecondT<T>& pc, c
                                   const std::array<const T*, kMaxD>&, int, const std::array<T*, kMaxD>&,     \
                                   const int*);                                                                 \
   template void plan_core_projection<T>(Seq&, Planner&, const Shape&, const Blocks<T>&, const double*,        \
-                                        const std::array<const T*, kMaxD>&, int, T*, const int*);         \
+                                        const std::array<const T*, kMaxD>&, int, T*, const int*, const T*);         \
   template void plan_precond<T>(Seq&, Planner&, const Shape&, const PrecondT<T>&, const TT<T>&, const TT<T>&,  \
                                 const RoundCfg&, const std::array<const T*, kMaxD>&);                         \
   template Blocks<T> plan_precond_terms<T>(Seq&, Planner&, const Shape&, const PrecondT<T>&, const TT<T>&);

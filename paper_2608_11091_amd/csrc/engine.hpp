@@ -191,10 +191,12 @@ void plan_krp_range(Seq& q, Planner& pl, const Shape& sh, const Blocks<T>& in, c
                     const std::array<const T*, kMaxD>& L, int w, const std::array<T*, kMaxD>& Y,
                     const int* nb_active);
 // Core projection C = sum_b coef_b G_b x_1 (P_1^T U_b1) ... x_d (P_d^T U_bd)
-// (w^d row-major; P_k column-major n_k x >= w).
+// (w^d row-major; P_k column-major n_k x >= w).  W: the products P_k^T U_bk
+// where they are there already (w x rc each, block-major).
 template <typename T>
 void plan_core_projection(Seq& q, Planner& pl, const Shape& sh, const Blocks<T>& in, const double* coef,
-                          const std::array<const T*, kMaxD>& Pm, int w, T* C, const int* nb_active);
+                          const std::array<const T*, kMaxD>& Pm, int w, T* C, const int* nb_active,
+                          const T* W = nullptr);
 
 // Exact squared Frobenius norm of a block sum (QR of concatenated factors).
 void plan_exact_norm2(Seq& q, Planner& pl, const Shape& sh, const Blocks<double>& in, double* out_norm2);

@@ -81,7 +81,9 @@ __device__ __forceinline__ bool uniform_zero(double x) {
 // second pass sums the partials in split order.  (Summing them in the last
 // workgroup to arrive at a tile needs device-scope fences, whose L2
 // write-back across the XCDs cost more than the second launch.)
-template <typename T, bool TA, bool TB, int TS, bool BF = false>
+// OPS: bit 0 op(A) = A^T, bit 1 op(B) = B^T; kAnyOps: as each group says.
+constexpr int kAnyOps = 4;
+template <typename T, int OPS, int TS, bool BF = false>
 __global__ __launch_bounds__(NT) void gemm_kernel(int M, int N, int K, int lda, int ldb, int ldc,
                                                   const GemmTerm<T>* __restrict__ terms,
                                                   const GemmGroup<T>* __restrict__ groups, double beta,
@@ -89,6 +91,7 @@ __global__ __launch_bounds__(NT) void gemm_kernel(int M, int N, int K, int lda, 
                                                   int max_terms, int uniform_terms, bool mixed, RowBlocks rb_) {
   static_assert(!BF || sizeof(T) == 4, "bf16 operands with FP32 storage only");
   static_assert(!BF || TS == 64, "bf16 operands with the large tile only");
+  static_assert(OPS != kAnyOps || TS == 32, "operations per group with the small tile only");
   // K depth of a slab: 8 loads per operand and thread in flight at once (16
   // for the bf16 form, one 16-deep MFMA per output tile)
   constexpr int BM = TS, BN = TS, KB = BF ? 16 : TS == 64 ? 32 : 64;
@@ -123,6 +126,8 @@ __global__ __launch_bounds__(NT) void gemm_kernel(int M, int N, int K, int lda, 
     ldc = grp.ldc;
     if (m0 >= M) return;
   }
+  const int ops = OPS == kAnyOps ? grp.ops : OPS;
+  const bool TA = ops & 1, TB = ops & 2;
 
   typedef typename Acc<T>::type AT;
   AT acc[NACC];
@@ -148,9 +153,9 @@ __global__ __launch_bounds__(NT) void gemm_kernel(int M, int N, int K, int lda, 
   // row am0 + i * amd, k ak0 + i * akd of the slab
   const int tm0 = tid % TS, tk0 = TS == 64 ? wid : tid / TS;
   const int am0 = TA ? tid / KB : tm0, ak0 = TA ? tid % KB : tk0;
-  constexpr int amd = TA ? NT / KB : 0, akd = TA ? 0 : NT / TS;
+  const int amd = TA ? NT / KB : 0, akd = TA ? 0 : NT / TS;
   const int bn0 = TB ? tm0 : tid / KB, bk0 = TB ? tk0 : tid % KB;
-  constexpr int bnd = TB ? 0 : NT / KB, bkd = TB ? NT / TS : 0;
+  const int bnd = TB ? 0 : NT / KB, bkd = TB ? NT / TS : 0;
   // Slab s is fetched into registers one slab ahead of its use, so its global
   // loads are in flight while the matrix cores work on slab s - 1; the record
   // of the next term is fetched one term ahead, and a term's coefficients are
@@ -404,13 +409,14 @@ __global__ void splitk_reduce(int M, int N, int ldc, const GemmGroup<T>* __restr
 template <typename T>
 void gemm_run(const GemmLaunch<T>& g, hipStream_t st) {
   if (g.ngroups <= 0 || g.M <= 0 || g.N <= 0) return;
-  TK_CHECK(g.tile == 64 || (g.tile == 32 && !g.bf16), kErrInvalidArg, "internal: product tile");
+  TK_CHECK(g.bf16 || g.any_ops ? g.tile == (g.bf16 ? 64 : 32) : g.tile == 64 || g.tile == 32, kErrInvalidArg,
+           "internal: product tile");
   dim3 grid(ceil_div(g.M, g.tile), ceil_div(g.N, g.tile), g.ngroups * g.splits);
   T* part = g.splits > 1 ? g.partial : nullptr;
   const size_t pstride = (size_t)g.M * g.N;
   RowBlocks rb{};
   if (g.mblk > 0) {
-    TK_CHECK(!g.ta && g.splits == 1 && !g.mixed && long(g.M) * g.mblk < (1L << 32), kErrInvalidArg,
+    TK_CHECK(!g.ta && !g.any_ops && g.splits == 1 && !g.mixed && long(g.M) * g.mblk < (1L << 32), kErrInvalidArg,
              "internal: rows in slices");
     rb.mblk = unsigned(g.mblk);
     rb.magic = unsigned(((1ull << 32) + rb.mblk - 1) / rb.mblk);
@@ -419,17 +425,19 @@ void gemm_run(const GemmLaunch<T>& g, hipStream_t st) {
   }
   timer_begin(kKcGemm, st, g.flops);
   TK_CHECK(!g.bf16 || sizeof(T) == 4, kErrUnsupported, "bf16 operands need FP32 storage");
-#define TK_GEMM_CASE(TA, TB, TS, BF)                                                                           \
-  if (g.ta == TA && g.tb == TB && g.tile == TS && g.bf16 == BF)                                                \
-    hipLaunchKernelGGL((gemm_kernel<T, TA, TB, TS, BF && sizeof(T) == 4>), grid, dim3(NT), 0, st, g.M, g.N, g.K, \
+  const int ops = g.any_ops ? kAnyOps : (g.ta ? 1 : 0) + (g.tb ? 2 : 0);
+#define TK_GEMM_CASE(OPS, TS, BF)                                                                              \
+  if (ops == OPS && g.tile == TS && g.bf16 == BF)                                                              \
+    hipLaunchKernelGGL((gemm_kernel<T, OPS, TS, BF && sizeof(T) == 4>), grid, dim3(NT), 0, st, g.M, g.N, g.K,  \
                        g.lda, g.ldb, g.ldc, g.terms, g.groups, g.beta, g.splits, part, pstride, g.max_terms,   \
                        g.uniform_terms, g.mixed, rb);
 #define TK_GEMM_CASES(TS, BF)         \
-  TK_GEMM_CASE(false, false, TS, BF)  \
-  TK_GEMM_CASE(false, true, TS, BF)   \
-  TK_GEMM_CASE(true, false, TS, BF)   \
-  TK_GEMM_CASE(true, true, TS, BF)
+  TK_GEMM_CASE(0, TS, BF)             \
+  TK_GEMM_CASE(1, TS, BF)             \
+  TK_GEMM_CASE(2, TS, BF)             \
+  TK_GEMM_CASE(3, TS, BF)
   TK_GEMM_CASES(32, false)
+  TK_GEMM_CASE(kAnyOps, 32, false)
   TK_GEMM_CASES(64, false)
   if constexpr (sizeof(T) == 4) {
     TK_GEMM_CASES(64, true)

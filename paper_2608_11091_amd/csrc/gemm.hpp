@@ -29,12 +29,14 @@ struct GemmGroup {
   T* C;
   int t0, t1;  // term range [t0, t1)
   int M, K, lda, ldb, ldc;  // read when the launch is mixed
+  int ops;                  // transposes, read when the launch has any_ops: op(A) = A^T (1), op(B) = B^T (2)
 };
 
 // Launch descriptor: uniform transposes and N, device tables.
 template <typename T>
 struct GemmLaunch {
   bool ta = false, tb = false;
+  bool any_ops = false;    // transposes per group (tile 32)
   int M = 0, N = 0, K = 0, lda = 0, ldb = 0, ldc = 0;
   const GemmTerm<T>* terms = nullptr;   // device
   const GemmGroup<T>* groups = nullptr; // device

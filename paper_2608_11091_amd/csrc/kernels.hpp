@@ -130,19 +130,19 @@ void core_recap(const T* src, const int* sd, const int* sv, T* dst, const int* d
 // Zero columns [*from_dev, cols) of a column-major rows x cols matrix.
 template <typename T>
 void zero_cols_from(T* A, int ld, int rows, int cols, const int* from_dev, hipStream_t st);
-// One launch: columns >= s of the d factors U[k] (n[k] x sc, ld n[k]) and,
-// unless core is null, every entry of the dense sc^d core (row-major) with an
-// index >= s.
+// RoundSum's width s = min(max_k rank + p, cap + p) from the kept ranks (as
+// sketch_width computes it), written to *s_out, and the zeroing that follows:
+// columns of the bases U_k (n_k x sc) at or beyond s, optionally every core
+// entry with an index there, and optionally the rows there of `wcols` columns
+// of length sc (products of the bases with other factors).
 template <typename T>
 struct WidthZero {
   T* U[kMaxD];
   int n[kMaxD];
   T* core;
+  T* W;
+  int wcols;
 };
-template <typename T>
-void zero_beyond_width(const WidthZero<T>& a, int d, int sc, const int* s_dev, hipStream_t st);
-// The same zeroing with the width computed in the kernel from the kept ranks,
-// as sketch_width does it, and written to *s_out.
 template <typename T>
 void width_and_zero(const WidthZero<T>& a, int d, int sc, const int* rt, int p, int cap, int force, int* s_out,
                     hipStream_t st);
@@ -280,12 +280,12 @@ template <typename T>
 void rank_certificate(const T* H, const double* w, const double* fro, int nb_active, const double* tau,
                       const CertParams& cp, int* cert, int* rt, hipStream_t st);
 
-// Per mode k: R_k = sum_b rank_b[k]; enable[k] = (R_k <= rmax); nact[k] = R_k or -1.
+// Per mode k: R_k = sum_b rank_b[k]; enable[k] = (R_k <= rmax); nact[k] = R_k or -1;
+// skip_small[k] = (R_k > rreg), skip_big[k] = (R_k <= rreg).
 // Then the padded Gram (blocks of rc rows/cols) is compacted to its R_k x R_k
 // active part (ld = ldc) for every mode with enable[k] = 1.
-// skip_small[k] = (R_k > rmax), skip_big[k] = (R_k <= rmax) when non-null.
-void gram_prep(const int* const* ranks, int nb, int d, int rmax, double* enable, int* nact, hipStream_t st,
-               int* skip_small = nullptr, int* skip_big = nullptr);
+void gram_prep(const int* const* ranks, int nb, int d, int rmax, int rreg, double* enable, int* nact, int* skip_small,
+               int* skip_big, hipStream_t st);
 template <typename T>
 void gram_compact(const T* padded, int ldp, const int* const* ranks, int nb, int d, int rc, const int* nact,
                   T* compact, int ldc, size_t mode_stride_p, size_t mode_stride_c, hipStream_t st);

@@ -97,19 +97,15 @@ __device__ inline int width_from_ranks(const int* rt, int d, int p, int cap, int
   return est < cap + p ? est : cap + p;
 }
 
-// Zeroes basis columns (part < d) and core indices (part == d) at or beyond
-// the width s; s comes from *s_dev, or from the ranks rt when rt is given (and
-// is then written to *s_out by one thread).
+// Zeroes basis columns (part < d), core indices (part == d, when there is a
+// core) and rows of the basis products (the last part, when there are any) at
+// or beyond the width s, which comes from the ranks rt and is written to *s_out
+// by one thread.
 template <typename T>
-__global__ void zero_beyond_width_kernel(WidthZero<T> a, int d, int sc, const int* s_dev, const int* rt, int p,
-                                         int cap, int force, int* s_out) {
-  int s;
-  if (rt) {
-    s = width_from_ranks(rt, d, p, cap, force);
-    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *s_out = s;
-  } else {
-    s = *s_dev;
-  }
+__global__ void zero_beyond_width_kernel(WidthZero<T> a, int d, int sc, const int* rt, int p, int cap, int force,
+                                         int* s_out) {
+  int s = width_from_ranks(rt, d, p, cap, force);
+  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *s_out = s;
   s = max(s, 0);
   const int part = blockIdx.y;
   const size_t stride = size_t(gridDim.x) * blockDim.x;
@@ -126,6 +122,10 @@ __global__ void zero_beyond_width_kernel(WidthZero<T> a, int d, int sc, const in
     const size_t len = size_t(n) * sc;
     for (size_t e = e0; e < len; e += stride)
       if (int(e / n) >= s) U[e] = T(0);
+  } else if (part > d || a.core == nullptr) {
+    const size_t len = size_t(a.wcols) * sc;
+    for (size_t e = e0; e < len; e += stride)
+      if (int(e % sc) >= s) a.W[e] = T(0);
   } else {
     size_t len = 1;
     for (int k = 0; k < d; ++k) len *= size_t(sc);
@@ -299,26 +299,17 @@ void zero_cols_from(T* A, int ld, int rows, int cols, const int* from_dev, hipSt
 }
 
 template <typename T>
-void zero_beyond_width(const WidthZero<T>& a, int d, int sc, const int* s_dev, hipStream_t st) {
-  size_t mx = 1;
-  for (int k = 0; k < d; ++k) mx *= size_t(sc);
-  for (int k = 0; k < d; ++k) mx = std::max(mx, size_t(a.n[k]) * sc);
-  const unsigned gx = unsigned(std::min<size_t>((mx + 255) / 256, 1024));
-  const unsigned parts = a.core ? d + 1 : d;
-  hipLaunchKernelGGL((zero_beyond_width_kernel<T>), dim3(gx, parts), dim3(256), 0, st, a, d, sc, s_dev, nullptr, 0,
-                     0, 0, nullptr);
-  TK_LAUNCH_CHECK();
-}
-
-template <typename T>
 void width_and_zero(const WidthZero<T>& a, int d, int sc, const int* rt, int p, int cap, int force, int* s_out,
                     hipStream_t st) {
-  size_t mx = 1;
-  for (int k = 0; k < d; ++k) mx *= size_t(sc);
-  for (int k = 0; k < d; ++k) mx = std::max(mx, size_t(a.n[k]) * sc);
+  size_t mx = size_t(a.W ? a.wcols : 0) * sc, core = 1;
+  for (int k = 0; k < d; ++k) {
+    core *= size_t(sc);
+    mx = std::max(mx, size_t(a.n[k]) * sc);
+  }
+  if (a.core) mx = std::max(mx, core);
   const unsigned gx = unsigned(std::min<size_t>((mx + 255) / 256, 1024));
-  const unsigned parts = a.core ? d + 1 : d;
-  hipLaunchKernelGGL((zero_beyond_width_kernel<T>), dim3(gx, parts), dim3(256), 0, st, a, d, sc, nullptr, rt, p, cap,
+  const unsigned parts = d + (a.core ? 1 : 0) + (a.W ? 1 : 0);
+  hipLaunchKernelGGL((zero_beyond_width_kernel<T>), dim3(gx, parts), dim3(256), 0, st, a, d, sc, rt, p, cap,
                      force, s_out);
   TK_LAUNCH_CHECK();
 }
@@ -499,8 +490,6 @@ template void zero_sum_fixup<double>(const double*, const double*, int, const in
 template void zero_sum_fixup<float>(const double*, const double*, int, const int*, int, float* const*, float*, size_t,
                                     int*, hipStream_t);
 template void zero_cols_from<double>(double*, int, int, int, const int*, hipStream_t);
-template void zero_beyond_width<double>(const WidthZero<double>&, int, int, const int*, hipStream_t);
-template void zero_beyond_width<float>(const WidthZero<float>&, int, int, const int*, hipStream_t);
 template void width_and_zero<double>(const WidthZero<double>&, int, int, const int*, int, int, int, int*, hipStream_t);
 template void width_and_zero<float>(const WidthZero<float>&, int, int, const int*, int, int, int, int*, hipStream_t);
 template void zero_cols_from<float>(float*, int, int, int, const int*, hipStream_t);

@@ -1,84 +1,110 @@
-// Right-looking Cholesky steps of a symmetric matrix of order m <= 64 held in
-// the registers of eight waves.
+// Right-looking Cholesky steps of a symmetric matrix of order m <= 64: eight
+// waves hold the rows in registers, a ninth reduces the panels.
 #pragma once
 
 #include "common.hpp"
 
 namespace tk {
 
-constexpr int kCholWaves = 8;
-constexpr int kCholRows = kWave / kCholWaves;  // rows of a wave
+constexpr int kCholPanel = 8;               // rows of a panel, and waves that hold rows
+constexpr int kCholWaves = kCholPanel + 1;  // waves that call chol_rows
+constexpr int kCholRows = kWave / kCholPanel;
 
-// Wave w holds the rows w, w + W, .. (W waves; a[r] = entry (w + W r, lane));
-// entries left of the diagonal are not used.  Step k reads row k and updates
-// every later row i:
+template <typename T>
+struct CholShared {
+  T in[kCholPanel][kWave];      // the rows of the next panel
+  T row[2][kCholPanel][kWave];  // a reduced panel and its rows / pivot
+  T f[2][kCholPanel][kWave];
+  int stop;
+};
+
+// Wave w < 8 holds the rows w, w + 8, .. (a[r] = entry (w + 8 r, lane)); entries
+// left of the diagonal are not used.  Step k reads row k and updates every
+// later row i:
 //   A[i][j] -= A[k][i] (A[k][j] / pivot).
-// pivot(k, A[k][k]) says what to do: > 0 update, 0 skip the update (a dead
-// column), < 0 stop (the same in every thread; chol_rows then returns false).
-// retire(k, a) gets row k in its wave.  row_s: LDS for two panels.  All W waves
-// call it; other waves must have left the kernel.
+// scale(k, A[k][k], A[k][j], f), called by the ninth wave, sets f to A[k][j] /
+// pivot (0: a dead column, nothing is updated) and returns whether to go on;
+// chol_rows returns false in every thread when it was told not to.  retire(k, a)
+// gets row k in wave k % 8.  All nine waves call it; other waves
+// must have left the kernel.
 //
-// A serial chain of m divisions.  The W rows of a panel are published at once
-// and every wave reduces them for itself, so there is one LDS exchange and one
-// barrier a panel; each wave then applies the panel's steps to its own rows.
-// Every entry sees the same operations in the same order as one step at a
-// time.  The multipliers A[k][i] come from the row's lanes through scalar
-// registers, read ahead of their uses.  At order 48 a step takes
-// 0.31 us (0.35 us with an exchange a step, 0.66 us with the matrix in
-// LDS and 4 waves, whose update read two operands and wrote one there for
-// every multiply-add).
-template <typename Pivot, typename Retire>
-__device__ __forceinline__ bool chol_rows(double (&a)[kCholRows], int m, int lane, int w,
-                                          double (*row_s)[kCholWaves][kWave], Pivot&& pivot, Retire&& retire) {
-  constexpr int W = kCholWaves;
+// A serial chain of m divisions, so what counts is what else is on it.  The
+// ninth wave reduces a panel of eight rows by itself (0.1 us a step: pivot
+// through a scalar register, division, multiply-add) and leaves it in LDS; the
+// others apply its eight steps to the row of theirs that the next panel needs,
+// hand that over, and update the rest beside the next panel.  Every entry sees
+// the same operations in the same order as one step at a time.  At order 53, FP64:
+// 9.2 us (17.5 us with the panel reduced by every wave for itself and one
+// barrier a panel, whose eight copies share the SIMDs).
+template <typename T, typename Scale, typename Retire>
+__device__ __forceinline__ bool chol_rows(T (&a)[kCholRows], int m, int lane, int w, CholShared<T>& sh,
+                                          Scale&& scale, Retire&& retire) {
+  constexpr int W = kCholPanel;
+  if (w < W) sh.in[w][lane] = a[0];
+  if (w == W && lane == 0) sh.stop = 0;
+  __syncthreads();
   for (int k0 = 0, buf = 0; k0 < m; k0 += W, buf ^= 1) {
-    row_s[buf][w][lane] = a[0];
-    __syncthreads();
-    double r[W], f[W];
+    if (w == W) {
+      T r[W];
 #pragma unroll
-    for (int p = 0; p < W; ++p) r[p] = row_s[buf][p][lane];
-    int acts = 0;  // steps that update
+      for (int p = 0; p < W; ++p) r[p] = sh.in[p][lane];
+      bool stop = false;
 #pragma unroll
-    for (int q = 0; q < W; ++q) {
-      const int k = k0 + q;
-      if (k < m) {
-        const double pv = rdlane(r[q], k);
-        const int act = pivot(k, pv);
-        if (act < 0) return false;
-        if (w == q) retire(k, r[q]);
-        if (act) {
-          acts |= 1 << q;
-          double s[W];
+      for (int q = 0; q < W; ++q) {
+        const int k = k0 + q;
+        if (k < m) {
+          const T pv = rdlane(r[q], k);
+          T s[W];
 #pragma unroll
           for (int p = 0; p < W; ++p)
             if (p > q) s[p] = rdlane(r[q], k0 + p);
-          f[q] = r[q] / pv;
+          T f;
+          stop |= !scale(k, pv, r[q], f);
           __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
           for (int p = 0; p < W; ++p)
-            if (p > q) r[p] = fma(-s[p], f[q], r[p]);
+            if (p > q) r[p] = fma(-s[p], f, r[p]);
+          sh.row[buf][q][lane] = r[q];
+          sh.f[buf][q][lane] = f;
         }
       }
+      if (stop && lane == 0) sh.stop = 1;
     }
-    const int live = (m - k0 - w + W - 1) / W;  // rows k0 + w + W i below m
+    __syncthreads();
+    if (sh.stop != 0) return false;
+    if (w < W) {
+      const int np = min(W, m - k0);
+      if (w < np) retire(k0 + w, sh.row[buf][w][lane]);
 #pragma unroll
-    for (int q = 0; q < W; ++q) {
-      if (!(acts >> q & 1)) continue;
+      for (int i = 0; i + 1 < kCholRows; ++i) a[i] = a[i + 1];
+    }
+    if (k0 + W >= m) break;
+    // a whole panel is behind (only the last can be short)
+    T f[W];
+    if (w < W) {
+      T s[W];
 #pragma unroll
-      for (int g = 1; g < kCholRows; g += 4) {
-        if (g >= live) continue;
-        double s[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-          if (g + u < kCholRows) s[u] = rdlane(r[q], k0 + w + W * (g + u));
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-          if (g + u < kCholRows) a[g + u] = fma(-s[u], f[q], a[g + u]);
+      for (int q = 0; q < W; ++q) {
+        f[q] = sh.f[buf][q][lane];
+        s[q] = sh.row[buf][q][k0 + W + w];
       }
-    }
 #pragma unroll
-    for (int i = 0; i + 1 < kCholRows; ++i) a[i] = a[i + 1];
+      for (int q = 0; q < W; ++q) a[0] = fma(-s[q], f[q], a[0]);
+      sh.in[w][lane] = a[0];
+    }
+    __syncthreads();
+    if (w < W) {
+      const int live = (m - k0 - W - w + W - 1) / W;  // rows k0 + 8 + w + 8 i below m
+#pragma unroll
+      for (int i = 1; i < kCholRows; ++i)
+        if (i < live) {
+          T s[W];
+#pragma unroll
+          for (int q = 0; q < W; ++q) s[q] = sh.row[buf][q][k0 + W + w + W * i];
+#pragma unroll
+          for (int q = 0; q < W; ++q) a[i] = fma(-s[q], f[q], a[i]);
+        }
+    }
   }
   return true;
 }

@@ -737,11 +737,12 @@ __device__ __forceinline__ bool above_tol(float d, float nx, float ny, float tol
 // Bound: the dependent chain of one wave per SIMD (about 6 cycles an
 // instruction): a rotation step (dot and DPP reduction, the angle's
 // reciprocals and square roots, the rotation, LDS hand-over and barrier) takes
-// 920 cycles in FP64 and 730 in FP32, a Cholesky step 990 and 730.  Measured at
-// order 53 (two-sided form in brackets): three Grams of 32 partials each 158 us
-// (419) in FP64, 105 us (270) in FP32; a nearly diagonal Gram, the second pass,
-// 47 us (66) and 37 us (48); three Grams of order 15 30 us (71) and 22 us (43).
-template <typename T, int RPL>
+// 900 cycles in FP64 and 750 in FP32, a pivoted Cholesky step 1000 and 800, one
+// on panels 500 and 400.  Measured at order 53 (two-sided form in brackets):
+// three Grams of 32 partials each 160 us (419) in FP64, 112 us (270) in FP32; a
+// nearly diagonal Gram, the second pass, 36 us (66; 47 pivotless but a step at
+// a time) and 31 us (48); three Grams of order 15 30 us (71) and 23 us (43).
+template <typename T, int RPL, bool PIV>
 __global__ __launch_bounds__(1024) void jacobi_osj_kernel(const EigTask<T>* __restrict__ tasks, int N) {
   constexpr int NT = 1024;
   constexpr int JW = 4;                               // waves of the factorisation and the rotations
@@ -791,7 +792,7 @@ __global__ __launch_bounds__(1024) void jacobi_osj_kernel(const EigTask<T>* __re
   for (int e = tid; e < NP * LDX; e += NT) X0[e] = T(0);
   if (tid < 3) bigflag[tid] = 0;
   __syncthreads();
-  if (wave >= JW) return;  // a barrier waits for the waves that are left
+  if (wave >= (PIV ? JW : kCholWaves)) return;  // a barrier waits for the waves that are left
 
   // ---- scale by a power of two so that the trace is in [1, 2)
   T tr = T(0);
@@ -803,20 +804,46 @@ __global__ __launch_bounds__(1024) void jacobi_osj_kernel(const EigTask<T>* __re
   if (tr > T(0) && tr < T(INFINITY)) (void)frexp(tr, &ex);
   const T down = ldexp(T(1), -ex), up = ldexp(T(1), ex);
 
-  // ---- Cholesky: lane = row, wave w holds the columns w NB .. w NB + NB - 1 of
-  // the remaining symmetric matrix in registers and every wave the remaining
+  // ---- Cholesky.  A matrix of any rank in any order takes the largest remaining
+  // diagonal as pivot (PIV), without which a rank-deficient one amplifies
+  // rounding; one whose rows are sorted (the second pass of ST-HOSVD, sorted by
+  // the first) keeps their order and runs on panels (chol_rows).  A remaining
+  // diagonal at or below the rounding of its own start (N eps a_kk) is cut:
+  // that pivot is the floor and the rest of its column zero.
+  if constexpr (!PIV) {
+    __shared__ CholShared<T> chs;
+    T a[kCholRows];
+#pragma unroll
+    for (int r = 0; r < kCholRows; ++r) {
+      const int i = wave + kCholPanel * r;
+      a[r] = i < N && lane >= i && lane < N ? G[i * LDG + lane] * down : T(0);
+    }
+    const T floor_l = lane < N ? G[lane * LDG + lane] * down * (T(N) * Lim<T>::eps()) : T(0);
+    chol_rows(
+        a, N, lane, wave, chs,
+        [&](int k, T pv, T row, T& f) {
+          f = pv <= rdlane(floor_l, k) ? T(0) : row / pv;  // (a NaN pivot stays)
+          return true;
+        },
+        [&](int k, T row) {
+          const T pv = rdlane(row, k), fl = rdlane(floor_l, k);
+          const bool dead = pv <= fl;
+          const T d = dead ? (fl > T(0) ? fl : Lim<T>::pivot_tiny()) : pv;
+          const T r = rsq_full(d);
+          const T x = dead ? T(0) : row * r;
+          if (lane < NM) X0[k * LDX + lane] = lane == k ? d * r : lane > k && lane < N ? x : T(0);
+        });
+    if (wave >= JW) return;
+  }
+  // Pivoted (PIV): lane = row, wave w holds the columns w NB .. w NB + NB - 1 of the
+  // remaining symmetric matrix in registers and every wave the remaining
   // diagonal.  The pivot column goes through LDS, one barrier a step; its
   // entries for a wave's columns are read across lanes (as LDS broadcasts
-  // they took longer than the whole update).  The first pass of ST-HOSVD meets
-  // matrices of any rank in any order and takes the largest remaining diagonal
-  // (to 17 bits, ties to the lowest row; all waves derive the same p), without
-  // which a rank-deficient matrix amplifies rounding; the second pass (the one
-  // with the truncation rule) has its rows sorted by the first and keeps
-  // their order, which saves the search.
-  {
+  // they took longer than the whole update).  Pivots are compared to 17 bits,
+  // ties to the lowest row; all waves derive the same p.
+  if constexpr (PIV) {
     typedef T Cols __attribute__((ext_vector_type(16)));
     static_assert(NB <= 16, "a wave's columns fit the vector");
-    const bool piv = tk_.rule.kind != 2;
     Cols a;
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
@@ -841,11 +868,8 @@ __global__ __launch_bounds__(1024) void jacobi_osj_kernel(const EigTask<T>* __re
     };
     int p = 0;
     auto choose = [&](int k) {  // the pivot of step k, its column published to the step's buffer
-      p = k;
-      if (piv) {
-        const unsigned bits = __float_as_uint(fmaxf(float(dg), 0.0f));
-        p = 63 - int(wave_umax(alive ? 0x80000000u | (bits & ~63u) | unsigned(63 - lane) : 0u) & 63u);
-      }
+      const unsigned bits = __float_as_uint(fmaxf(float(dg), 0.0f));
+      p = 63 - int(wave_umax(alive ? 0x80000000u | (bits & ~63u) | unsigned(63 - lane) : 0u) & 63u);
       const int b = p - wave * NB;
       if (b >= 0 && b < NB) colk[k & 1][lane] = a[b];
     };
@@ -1032,7 +1056,7 @@ __global__ __launch_bounds__(CERT_NT) void rank_cert_kernel(const T* __restrict_
                                                             const double* __restrict__ fro, int nb_act,
                                                             const double* __restrict__ tau_dev, CertParams cp,
                                                             int* __restrict__ cert, int* __restrict__ rt) {
-  __shared__ double row_s[2][kCholWaves][kWave];
+  __shared__ CholShared<double> chs;
   __shared__ double red[kCholWaves];
   const int k = blockIdx.x;
   const int tid = threadIdx.x;
@@ -1050,13 +1074,18 @@ __global__ __launch_bounds__(CERT_NT) void rank_cert_kernel(const T* __restrict_
   double a[kCholRows];
 #pragma unroll
   for (int r = 0; r < kCholRows; ++r) {
-    const int i = wave + kCholWaves * r;
+    const int i = wave + kCholPanel * r;
     a[r] = double(((GPtr<T>)Hk)[min(lane, m - 1) + (size_t)min(i, m - 1) * m]) - (i == lane ? theta : 0.0);
   }
   bool ok = tr > 0.0 && tr < INFINITY;  // the same in every thread
   if (ok)
     ok = chol_rows(
-        a, m, lane, wave, row_s, [](int, double pv) { return pv > 0.0 && pv < INFINITY ? 1 : -1; }, [](int, double) {});
+        a, m, lane, wave, chs,
+        [](int, double pv, double row, double& f) {
+          f = row / pv;
+          return pv > 0.0 && pv < INFINITY;
+        },
+        [](int, double) {});
   if (tid == 0) {
     cert[k] = ok ? 1 : 0;
     if (ok)
@@ -1069,7 +1098,8 @@ __global__ __launch_bounds__(CERT_NT) void rank_cert_kernel(const T* __restrict_
 }  // namespace
 
 template <typename T>
-void jacobi_eig(const EigTask<T>* tasks_d, int ntasks, int N, bool want_v, hipStream_t st, int in_splits) {
+void jacobi_eig(const EigTask<T>* tasks_d, int ntasks, int N, bool want_v, hipStream_t st, int in_splits,
+                bool sorted) {
   if (ntasks <= 0 || N <= 0) return;
   // algorithmic work of a symmetric eigendecomposition of order N: 9 N^3 with
   // eigenvectors (symmetric QR algorithm count), (4/3) N^3 for the tridiagonal
@@ -1087,7 +1117,10 @@ void jacobi_eig(const EigTask<T>* tasks_d, int ntasks, int N, bool want_v, hipSt
     switch (ceil_div(N, 8)) {
 #define TK_OSJ_CASE(R)                                                                                      \
   case R:                                                                                                   \
-    hipLaunchKernelGGL((jacobi_osj_kernel<T, R>), dim3(ntasks), dim3(1024), 0, st, tasks_d, N);             \
+    if (sorted)                                                                                             \
+      hipLaunchKernelGGL((jacobi_osj_kernel<T, R, false>), dim3(ntasks), dim3(1024), 0, st, tasks_d, N);    \
+    else                                                                                                    \
+      hipLaunchKernelGGL((jacobi_osj_kernel<T, R, true>), dim3(ntasks), dim3(1024), 0, st, tasks_d, N);     \
     break;
       TK_OSJ_CASE(1)
       TK_OSJ_CASE(2)
@@ -1136,7 +1169,7 @@ template void rank_certificate<double>(const double*, const double*, const doubl
 template void rank_certificate<float>(const float*, const double*, const double*, int, const double*,
                                       const CertParams&, int*, int*, hipStream_t);
 
-template void jacobi_eig<double>(const EigTask<double>*, int, int, bool, hipStream_t, int);
-template void jacobi_eig<float>(const EigTask<float>*, int, int, bool, hipStream_t, int);
+template void jacobi_eig<double>(const EigTask<double>*, int, int, bool, hipStream_t, int, bool);
+template void jacobi_eig<float>(const EigTask<float>*, int, int, bool, hipStream_t, int, bool);
 
 }  // namespace tk

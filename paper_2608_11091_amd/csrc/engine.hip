@@ -1144,7 +1144,7 @@ RoundSumOut<T> plan_roundsum(Seq& q, Planner& pl, const Shape& sh, const Blocks<
       et[0].rule.rank_out = out.rank + k;
       const size_t off = blob.add(et);
       const int in_splits = std::max(1, so.splits);
-      q.steps.push_back([=](hipStream_t st) { jacobi_eig<T>(bl->at<EigTask<T>>(off), 1, sc, true, st, in_splits); });
+      q.steps.push_back([=](hipStream_t st) { jacobi_eig<T>(bl->at<EigTask<T>>(off), 1, sc, true, st, in_splits, true); });
     }
     emit_ttm<T>(q, pl, d, dims, k, sc, {Bt}, {V2[k]}, sc, true, {Cb[1 - cb]});
     cb = 1 - cb;

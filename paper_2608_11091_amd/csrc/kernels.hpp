@@ -252,10 +252,13 @@ struct EigTask {
 // Eigenvalues only: N <= 512; above kEigRegMax the matrix is reduced in place
 // (A must then be writable scratch).  With vectors: N <= 64.  in_splits is the
 // number of split-K partials the tasks' loads sum (1 when they read A); it
-// only enters the kernel timer's byte count.
+// only enters the kernel timer's byte count.  `sorted` (with vectors): the
+// matrices are close to diagonal with rows in descending order, so that their
+// Cholesky factorisation needs no pivoting.
 constexpr int kEigRegMax = 160;
 template <typename T>
-void jacobi_eig(const EigTask<T>* tasks_d, int ntasks, int N, bool want_v, hipStream_t st, int in_splits = 1);
+void jacobi_eig(const EigTask<T>* tasks_d, int ntasks, int N, bool want_v, hipStream_t st, int in_splits = 1,
+                bool sorted = false);
 
 // Certificate for the effective-rank rule of RoundSum (Sec. 3.1), one task
 // per mode k.  H_k = Q_k^T G_k Q_k (cap x cap, ld cap, T) is the compression of

@@ -369,14 +369,14 @@ constexpr int CH_MAX = 64;
 // factorisation by its serial chain (chol_rows); row k of R is row k of the
 // reduced matrix / sqrt(pivot).  A pivot that is not above max(dead_rel tr,
 // dead_abs) marks a dead column: its row of R is zero and it updates nothing.
-// Three Grams of order 53 from 16 partials each: 27.5 us (28.4 us from 8
-// partials with the matrix in LDS).
+// Three Grams of order 53 from 8 partials each: 18.5 us (28.4 us with the matrix
+// in LDS, 16 waves updating it and a barrier a step).
 __global__ __launch_bounds__(CH_NT) void chol_kernel(const CholTask* __restrict__ tasks, int cap,
                                                      const int* __restrict__ m_dev, double dead_rel,
                                                      double dead_abs) {
   constexpr int NW = CH_NT / kWave;
   __shared__ double G[CH_MAX][CH_MAX + 1];
-  __shared__ double row_s[2][kCholWaves][kWave];
+  __shared__ CholShared<double> chs;
   __shared__ double rk_s[CH_MAX];
   const CholTask tk_ = tasks[blockIdx.x];
   const int tid = threadIdx.x;
@@ -385,27 +385,38 @@ __global__ __launch_bounds__(CH_NT) void chol_kernel(const CholTask* __restrict_
   int m = m_dev ? *m_dev : cap;
   m = __builtin_amdgcn_readfirstlane(min(m, cap));
   // row i from column i of the symmetric Gram: contiguous over the lanes
+  constexpr int RW = CH_MAX / NW;  // rows of a wave
+  double g[RW];
+  if (tk_.part) {  // the Gram's split-K partials, summed in split order (32 loads in flight)
+    GPtr<double> pp[RW];
 #pragma unroll
-  for (int u = 0; u < CH_MAX / NW; ++u) {
-    const int i = wave + u * NW;
-    if (i >= m) continue;
-    double g = 0.0;
-    if (lane >= i && lane < m) {
-      const size_t at = lane + (size_t)i * cap;
-      if (tk_.part) {  // the Gram's split-K partials, summed in split order
-        const GPtr<double> pp = (GPtr<double>)(tk_.part + at);
-        for (int sp = 0; sp < tk_.splits; sp += 16) {
-          double v[16];
-#pragma unroll
-          for (int x = 0; x < 16; ++x) v[x] = pp[min(sp + x, tk_.splits - 1) * tk_.pstride];
-#pragma unroll
-          for (int x = 0; x < 16; ++x) g += sp + x < tk_.splits ? v[x] : 0.0;
-        }
-      } else {
-        g = ((GPtr<double>)tk_.G)[at];
-      }
+    for (int u = 0; u < RW; ++u) {
+      const int i = min(wave + u * NW, m - 1);
+      pp[u] = (GPtr<double>)(tk_.part + min(max(lane, i), m - 1) + (size_t)i * cap);
+      g[u] = 0.0;
     }
-    G[i][lane] = g;
+    for (int sp = 0; sp < tk_.splits; sp += 8) {
+      double v[RW][8];
+#pragma unroll
+      for (int u = 0; u < RW; ++u)
+#pragma unroll
+        for (int x = 0; x < 8; ++x) v[u][x] = pp[u][min(sp + x, tk_.splits - 1) * tk_.pstride];
+#pragma unroll
+      for (int u = 0; u < RW; ++u)
+#pragma unroll
+        for (int x = 0; x < 8; ++x) g[u] += sp + x < tk_.splits ? v[u][x] : 0.0;
+    }
+  } else {
+#pragma unroll
+    for (int u = 0; u < RW; ++u) {
+      const int i = min(wave + u * NW, m - 1);
+      g[u] = ((GPtr<double>)tk_.G)[min(max(lane, i), m - 1) + (size_t)i * cap];
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < RW; ++u) {
+    const int i = wave + u * NW;
+    if (i < m) G[i][lane] = lane >= i && lane < m ? g[u] : 0.0;
   }
   __syncthreads();
   if (wave >= kCholWaves) return;  // a barrier waits for the waves that are left
@@ -415,16 +426,17 @@ __global__ __launch_bounds__(CH_NT) void chol_kernel(const CholTask* __restrict_
   double a[kCholRows];
 #pragma unroll
   for (int r = 0; r < kCholRows; ++r) {
-    const int i = wave + kCholWaves * r;
+    const int i = wave + kCholPanel * r;
     a[r] = i < m ? G[i][lane] : 0.0;
     if (lane == i) a[r] += s;
   }
   chol_rows(
-      a, m, lane, wave, row_s,
-      [&](int k, double pv) {
+      a, m, lane, wave, chs,
+      [&](int k, double pv, double row, double& f) {
         const bool dead = !(pv > dtol);
-        if (wave == 0 && lane == 0) rk_s[k] = dead ? 0.0 : pv;
-        return dead ? 0 : 1;
+        if (lane == 0) rk_s[k] = dead ? 0.0 : pv;
+        f = dead ? 0.0 : row / pv;
+        return true;
       },
       [&](int i, double v) { G[i][lane] = v; });
   __syncthreads();

@@ -659,33 +659,37 @@ RoundSumOut<T> plan_roundsum(Seq& q, Planner& pl, const Shape& sh, const Blocks<
   const bool rule = cfg.force_s < 0;
   const bool overlap = rule && !cfg.householder;
   const size_t rule_from = q.steps.size();
-  // Where the spectrum is expensive (every FP64 Gram; in FP32 the Grams that
-  // can exceed the register eigensolver's order) the overlap becomes: Grams
-  // on the side stream, and the eigensolves wait on the main stream for the
-  // rank certificate after step 3; when it shows r~_k >= cap for some mode
-  // the width is cap + p and every eigensolve returns at once.  Elsewhere the
-  // eigensolves run on the side stream beside steps 2-3.
-  bool big_gram = false;
-  for (auto& modes : modes_by_n<T>(sh)) {
-    const int n = sh.n[modes[0]];
-    big_gram |= n > kEigRegMax && nb * rc > kEigRegMax;
+  // n-side up to order 64 (where the eigensolve is short either way), and
+  // up to 160 unless the concatenation is the narrower side: at n = 128 and
+  // three blocks of rank 12 the order drops from 128 to 36.  The FP32 form
+  // stays on the n-side there (its count of the zero eigenvalues' noise
+  // depends on the side).
+  const int Rp = nb * rc;
+  auto on_nside = [=](int n) {
+    return n <= 64 || (n <= kEigRegMax && (Rp > n || !std::is_same<T, double>::value));
+  };
+  // Where the spectrum is expensive (FP64 Grams above order 64; in FP32 the
+  // Grams that can exceed the register eigensolver's order) the overlap
+  // becomes: Grams on the side stream, and the eigensolves wait on the main
+  // stream for the rank certificate after step 3; when it shows r~_k >= cap for
+  // some mode the width is cap + p and every eigensolve returns at once.
+  // Elsewhere the eigensolves run on the side stream beside steps 2-3, where
+  // they fit (order 62, FP64: 775 us with the certificate, 735 beside; order 32:
+  // 546 and 498), which they do not at order 96 and more (1035 and 1900 us for
+  // three rank-48 blocks at n = 512).
+  bool big_gram = false, wide = false;
+  for (int k = 0; k < d; ++k) {
+    const int n = sh.n[k];
+    big_gram |= n > kEigRegMax && Rp > kEigRegMax;
+    wide |= (on_nside(n) ? n : std::min(Rp, n)) > 64;
   }
-  const bool use_cert = overlap && (std::is_same<T, double>::value || big_gram);
+  const bool use_cert = overlap && ((std::is_same<T, double>::value && wide) || big_gram);
   int* cert_dev = use_cert ? ar.alloc<int>(kMaxD) : nullptr;
   double* fro = use_cert ? ar.alloc<double>(size_t(nb) * d) : nullptr;
   std::vector<std::function<void(hipStream_t)>> eig_steps;
   if (rule) {
     // Modes that share launches: those whose Gram goes on the R-side of order
     // Rp <= n together, whatever their sizes; the others by size.
-    const int Rp = nb * rc;
-    // n-side up to order 64 (where the eigensolve is short either way), and
-    // up to 160 unless the concatenation is the narrower side: at n = 128 and
-    // three blocks of rank 12 the order drops from 128 to 36.  The FP32 form
-    // stays on the n-side there (its count of the zero eigenvalues' noise
-    // depends on the side).
-    auto on_nside = [=](int n) {
-      return n <= 64 || (n <= kEigRegMax && (Rp > n || !std::is_same<T, double>::value));
-    };
     std::map<int, std::vector<int>> sets;
     for (int k = 0; k < d; ++k) sets[!on_nside(sh.n[k]) && Rp <= sh.n[k] ? 0 : sh.n[k]].push_back(k);
     if (use_cert) {

@@ -59,16 +59,18 @@ NOTE = {
 
 
 # HBM traffic of the dominant kernel per launch, from rocprofv3 FETCH_SIZE and
-# WRITE_SIZE passes over this benchmark (each scaled by what the counter reads
-# for a plain copy of known size), valid only for the kernel sources it was
-# measured on: reported as null once any of them changes.
+# WRITE_SIZE passes over RoundSums of this workload in the FP32 form (each scaled
+# by what the counter reads for a plain copy of known size), valid only for the
+# kernel sources it was measured on: reported as null once any of them changes.
 TRAFFIC = {
-    "jacobi": dict(bytes_per_launch=549908.0,
+    "jacobi": dict(bytes_per_launch=436974.0,
                    sources={"paper_2608_11091_amd/csrc/eig.hip":
-                            "9dc9777fee3f276e3378feeb5eac3de9f492afe7a909eecc99a0a9fe449a0af1",
+                            "1b70a6194b983cf6c0e58bb739d201557c5b9b8ae40630c0401cc59ade9b08d7",
+                            "paper_2608_11091_amd/csrc/chol.hpp":
+                            "14f8360877accdc0609287583c04de139bdd4c39bfde8f67c1fc97fd5370d1e4",
                             "paper_2608_11091_amd/csrc/common.hpp":
-                            "a72a951f0c6374c30ec565058a937f7bb8014779678f6d341fc5b73470946bd8"},
-                   profile="profiles/jacobi_blk_traffic_deblur3d_n512.md"),
+                            "3283029788d10a6301ce5d9ea808f355ff416a945d660ef303ea0e48717daff3"},
+                   profile="profiles/jacobi_osj_traffic_roundsum_n512.md"),
 }
 
 

@@ -71,13 +71,22 @@ bool in_layout(const Shape& sh, const tk_tucker& u, int k) {
   return true;
 }
 
+// Arrays a call writes before its last read of the inputs.
+using Writes = std::vector<std::pair<const double*, size_t>>;
+bool overlaps(const Writes& w, const double* p, size_t len) {
+  for (auto& x : w)
+    if (x.first != nullptr && x.first < p + len && p < x.first + x.second) return true;
+  return false;
+}
+
 // The moves that bring a caller tensor into the capacity layout: core,
-// factors and ranks.  With `in_place` the parts that have the layout are used
-// where they are (the plan only reads them): t then points at them, and the
-// move of such a core only stores the ranks.
+// factors and ranks.  With `in_place` the parts that have the layout, and that
+// none of those writes touches, are used where they are (the plan only reads
+// them): t then points at them, and the move of such a part is empty (it keeps
+// its place in the table, so that the workspace depends on capacities alone).
 template <typename D>
 void import_tasks(const Shape& sh, const tk_tucker& u, TT<D>& t, std::vector<MoveTask<double, D>>& out,
-                  bool in_place = false) {
+                  const Writes* in_place = nullptr) {
   const int d = sh.d;
   MoveTask<double, D> c{};
   c.src = u.core;
@@ -102,22 +111,22 @@ void import_tasks(const Shape& sh, const tk_tucker& u, TT<D>& t, std::vector<Mov
     c.valid = slice * size_t(u.r[0]);
   }
   if constexpr (std::is_same<D, double>::value)
-    if (in_place && in_layout(sh, u, -1)) {
+    if (in_place && in_layout(sh, u, -1) && !overlaps(*in_place, u.core, sh.core_len())) {
       t.core = const_cast<double*>(u.core);
       c.total = c.valid = 0;
     }
   out.push_back(c);
   for (int k = 0; k < d; ++k) {
-    if constexpr (std::is_same<D, double>::value)
-      if (in_place && in_layout(sh, u, k)) {
-        t.U[k] = const_cast<double*>(u.U[k]);
-        continue;
-      }
     MoveTask<double, D> f{};
     f.src = u.U[k];
     f.dst = t.U[k];
     f.total = size_t(sh.n[k]) * sh.rc;
     f.valid = size_t(sh.n[k]) * size_t(u.r[k]);
+    if constexpr (std::is_same<D, double>::value)
+      if (in_place && in_layout(sh, u, k) && !overlaps(*in_place, u.U[k], f.total)) {
+        t.U[k] = const_cast<double*>(u.U[k]);
+        f.total = f.valid = 0;
+      }
     out.push_back(f);
   }
 }
@@ -233,18 +242,18 @@ int do_apply(const tk_kron_op* op, const tk_tucker* x, int transpose, int form, 
       shapes[{int(x->n[k]), int(x->rcap[k])}].push_back(Product{A, AU[j * d + k], k});
     }
   // FP32 storage: operands rounded by one launch, results widened by one
-  std::map<std::pair<const double*, size_t>, const float*> narrow;
+  // (every product converts its own operand: the workspace does not depend on
+  // which pointers coincide)
   std::vector<MoveTask<double, float>> down;
   std::vector<MoveTask<float, double>> up;
   auto f32_of = [&](const double* src, size_t len) {
-    auto& p = narrow[{src, len}];
-    if (!p) {
-      float* dst = ar.alloc<float>(len);
-      down.push_back(convert_task<double, float>(src, dst, len));
-      p = dst;
-    }
-    return p;
+    float* dst = ar.alloc<float>(len);
+    down.push_back(convert_task<double, float>(src, dst, len));
+    return static_cast<const float*>(dst);
   };
+  std::array<const float*, kMaxD> U32{};
+  if (f32)
+    for (int k = 0; k < d; ++k) U32[k] = f32_of(x->U[k], size_t(x->n[k]) * x->rcap[k]);
   Seq prod;
   for (auto& sh : shapes) {
     const int n = sh.first.first, rcap = sh.first.second;
@@ -254,7 +263,7 @@ int do_apply(const tk_kron_op* op, const tk_tucker* x, int transpose, int form, 
       std::vector<float*> c;
       for (auto& p : sh.second) {
         a.push_back(f32_of(p.A, size_t(n) * n));
-        b.push_back(f32_of(x->U[p.k], len));
+        b.push_back(U32[p.k]);
         c.push_back(ar.alloc<float>(len));
         up.push_back(convert_task<float, double>(c.back(), p.out, len));
       }
@@ -359,15 +368,16 @@ Shape shape_of_blocks(const tk_block_sum* in, int cap, int p) {
 
 // The blocks in the capacity layout, rounded to T; the moves are added to
 // `tasks` (launched by the caller together with its own).  FP64 parts that
-// have the layout are read where they are; their space stays reserved, so the
+// have the layout are read where they are (`writes`: see import_tasks); their space stays reserved, so the
 // workspace depends on the capacities alone.
 template <typename T>
-Imported<T> import_blocks(Arena& ar, const tk_block_sum* in, const Shape& sh, std::vector<MoveTask<double, T>>& tasks) {
+Imported<T> import_blocks(Arena& ar, const tk_block_sum* in, const Shape& sh, std::vector<MoveTask<double, T>>& tasks,
+                          const Writes& writes = {}) {
   Imported<T> im;
   im.sh = sh;
   for (int b = 0; b < in->nblocks; ++b) {
     TT<T> t = alloc_tt<T>(ar, sh);
-    import_tasks<T>(sh, in->blocks[b], t, tasks, true);
+    import_tasks<T>(sh, in->blocks[b], t, tasks, &writes);
     im.blocks.add(t, nullptr, in->coef[b]);
   }
   return im;
@@ -757,11 +767,14 @@ int do_mln_sketch(const tk_block_sum* x, const double* const* Psi, int r, int p,
   Planner pl(ar, blob);
   Seq q;
   std::vector<MoveTask<double, double>> mv;
-  const auto im = import_blocks<double>(ar, x, shape_of_blocks(x, 1, 0), mv);
+  TK_CHECK(F != nullptr, kErrInvalidArg, "factor sketch outputs missing");
+  const Shape shape = shape_of_blocks(x, 1, 0);
+  Writes writes = {{core, size_t(ipow(r + p, shape.d))}, {diag, size_t(r + p)}};
+  for (int k = 0; k < shape.d; ++k) writes.push_back({F[k], size_t(shape.n[k]) * r});
+  const auto im = import_blocks<double>(ar, x, shape, mv, writes);
   emit_moves(q, pl, mv);
   const int d = im.sh.d;
   const auto ps = psi_of(Psi, d);
-  TK_CHECK(F != nullptr, kErrInvalidArg, "factor sketch outputs missing");
   MlnSk out;
   out.core = core;
   for (int k = 0; k < d; ++k) out.F[k] = F[k];

@@ -384,6 +384,7 @@ __global__ __launch_bounds__(CH_NT) void chol_kernel(const CholTask* __restrict_
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
   int m = m_dev ? *m_dev : cap;
   m = __builtin_amdgcn_readfirstlane(min(m, cap));
+  const int last = max(m - 1, 0);
   // row i from column i of the symmetric Gram: contiguous over the lanes
   constexpr int RW = CH_MAX / NW;  // rows of a wave
   double g[RW];
@@ -391,8 +392,8 @@ __global__ __launch_bounds__(CH_NT) void chol_kernel(const CholTask* __restrict_
     GPtr<double> pp[RW];
 #pragma unroll
     for (int u = 0; u < RW; ++u) {
-      const int i = min(wave + u * NW, m - 1);
-      pp[u] = (GPtr<double>)(tk_.part + min(max(lane, i), m - 1) + (size_t)i * cap);
+      const int i = min(wave + u * NW, last);
+      pp[u] = (GPtr<double>)(tk_.part + min(max(lane, i), last) + (size_t)i * cap);
       g[u] = 0.0;
     }
     for (int sp = 0; sp < tk_.splits; sp += 8) {
@@ -409,8 +410,8 @@ __global__ __launch_bounds__(CH_NT) void chol_kernel(const CholTask* __restrict_
   } else {
 #pragma unroll
     for (int u = 0; u < RW; ++u) {
-      const int i = min(wave + u * NW, m - 1);
-      g[u] = ((GPtr<double>)tk_.G)[min(max(lane, i), m - 1) + (size_t)i * cap];
+      const int i = min(wave + u * NW, last);
+      g[u] = ((GPtr<double>)tk_.G)[min(max(lane, i), last) + (size_t)i * cap];
     }
   }
 #pragma unroll

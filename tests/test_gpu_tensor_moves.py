@@ -129,3 +129,42 @@ def test_grouped_products(tk, ns, r, rcap, form, tol, transpose):
             assert got.shape == ref.shape
             if A is not None:
                 assert np.linalg.norm(got - ref) <= tol * np.linalg.norm(ref)
+
+
+def test_sketch_into_its_inputs(tk):
+    """Outputs that lie in the inputs' own storage: the inputs are then copied
+    before anything is written, so the result is that of separate outputs."""
+    import ctypes as C
+
+    from paper_2608_11091_amd import _abi, api
+    rng = np.random.default_rng(9)
+    n, r, p = 24, 6, 2
+    x = tk.Tucker.from_numpy(rng.standard_normal((r,) * 3), [rng.standard_normal((n, r)) for _ in range(3)])
+    Psi = [_cm(rng.standard_normal((n, r + p))) for _ in range(3)]
+    core, F, diag = tk.mln_sketch([(1.5, x)], Psi, r)
+    bs, keep = api._blocks_struct([(1.5, x)])
+    lib = _abi.load()
+    out = torch.zeros_like(core)
+    nb = C.c_size_t()
+    api.check(lib.tucker_mln_sketch_workspace(C.byref(bs), r, p, C.byref(nb)))
+    ws = api._workspace(nb.value, core.device)
+    api.check(lib.tucker_mln_sketch(C.byref(bs), api._ptr_array(Psi), r, p, C.c_void_p(out.data_ptr()),
+                                    api._ptr_array(x.U), None, C.c_void_p(ws.data_ptr()), nb.value, api._stream()))
+    assert torch.equal(out, core) and all(torch.equal(u, f) for u, f in zip(x.U, F))
+
+
+def test_workspace_does_not_depend_on_ranks(tk):
+    """Blocks with and without the capacity layout need the same workspace."""
+    import ctypes as C
+
+    from paper_2608_11091_amd import _abi, api
+    rng = np.random.default_rng(4)
+    lib = _abi.load()
+    sizes = set()
+    for r in ((6, 6, 6), (6, 5, 6), (1, 6, 2)):
+        x = tk.Tucker.from_numpy(rng.standard_normal(r), [rng.standard_normal((20, k)) for k in r], rcap=(6, 6, 6))
+        bs, keep = api._blocks_struct([(1.0, x), (2.0, x)])
+        nb = C.c_size_t()
+        api.check(lib.tucker_sketch_workspace(C.byref(bs), 12, 0, C.byref(nb)))
+        sizes.add(nb.value)
+    assert len(sizes) == 1

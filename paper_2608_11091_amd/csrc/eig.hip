@@ -794,7 +794,7 @@ __global__ __launch_bounds__(1024) void jacobi_osj_kernel(const EigTask<T>* __re
   __syncthreads();
   if (wave >= (PIV ? JW : kCholWaves)) return;  // a barrier waits for the waves that are left
 
-  // ---- scale by a power of two so that the trace is in [1, 2)
+  // ---- scale by a power of two so that the trace is in [1/2, 1)
   T tr = T(0);
   {
     const T dg = lane < N ? G[lane * LDG + lane] : T(0);
@@ -802,7 +802,9 @@ __global__ __launch_bounds__(1024) void jacobi_osj_kernel(const EigTask<T>* __re
   }
   int ex = 0;
   if (tr > T(0) && tr < T(INFINITY)) (void)frexp(tr, &ex);
-  const T down = ldexp(T(1), -ex), up = ldexp(T(1), ex);
+  // (applied to an entry as an exponent: the factor itself would overflow for a
+  // trace below 2^-128 in FP32, 2^-1024 in FP64, or in the last binade)
+  auto down = [&](T x) { return ldexp(x, -ex); };
 
   // ---- Cholesky.  A matrix of any rank in any order takes the largest remaining
   // diagonal as pivot (PIV), without which a rank-deficient one amplifies
@@ -816,9 +818,9 @@ __global__ __launch_bounds__(1024) void jacobi_osj_kernel(const EigTask<T>* __re
 #pragma unroll
     for (int r = 0; r < kCholRows; ++r) {
       const int i = wave + kCholPanel * r;
-      a[r] = i < N && lane >= i && lane < N ? G[i * LDG + lane] * down : T(0);
+      a[r] = i < N && lane >= i && lane < N ? down(G[i * LDG + lane]) : T(0);
     }
-    const T floor_l = lane < N ? G[lane * LDG + lane] * down * (T(N) * Lim<T>::eps()) : T(0);
+    const T floor_l = lane < N ? down(G[lane * LDG + lane]) * (T(N) * Lim<T>::eps()) : T(0);
     chol_rows(
         a, N, lane, wave, chs,
         [&](int k, T pv, T row, T& f) {
@@ -851,9 +853,9 @@ __global__ __launch_bounds__(1024) void jacobi_osj_kernel(const EigTask<T>* __re
       const bool in = lane < N && j < N;
       const int hi = in ? (j > lane ? j : lane) : 0, lo = in ? (j > lane ? lane : j) : 0;
       const T v = G[lo * LDG + hi];
-      a[b] = in ? v * down : T(0);
+      a[b] = in ? down(v) : T(0);
     }
-    T dg = lane < N ? G[lane * LDG + lane] * down : T(0);
+    T dg = lane < N ? down(G[lane * LDG + lane]) : T(0);
     const T floor_l = dg * (T(N) * Lim<T>::eps());
     bool alive = lane < N;
     // every lane prepares its own row as the next pivot: l_pp in dl, 1 / l_pp in
@@ -1014,8 +1016,8 @@ __global__ __launch_bounds__(1024) void jacobi_osj_kernel(const EigTask<T>* __re
       posB += __shfl_xor(posB, m, 8);
     }
     if (l == 0) {
-      lam_d[posA] = nA * up;
-      lam_d[posB] = nB * up;
+      lam_d[posA] = ldexp(nA, ex);
+      lam_d[posB] = ldexp(nB, ex);
     }
   }
   __syncthreads();

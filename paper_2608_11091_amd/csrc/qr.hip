@@ -72,15 +72,17 @@ __device__ __forceinline__ double wave_partials_sum(const double (*part)[kWave],
   return s0 + s1;
 }
 
-// Householder vector of a column with leading entry alpha and squared norm xx
-// (over the rows from the diagonal down): beta = -sign(alpha) ||x||,
-// tau = (beta - alpha) / beta, v = (1, scal * x_below); tau = scal = 0 where
-// nothing stands below the diagonal (to rounding).
+// Householder vector of a column with leading entry alpha, squared norm xx
+// (over the rows from the diagonal down) and squared norm `below` of the part
+// below the diagonal: beta = -sign(alpha) ||x||, tau = (beta - alpha) / beta,
+// v = (1, scal * x_below); tau = scal = 0 where nothing stands below the
+// diagonal.  (Whether xx exceeds alpha^2 does not tell: a part of up to 1e-8
+// of the diagonal is lost in the sum.)
 struct Reflector {
   double beta, tau, scal;
 };
-__device__ __forceinline__ Reflector reflector(double alpha, double xx) {
-  const bool some = xx > alpha * alpha;
+__device__ __forceinline__ Reflector reflector(double alpha, double xx, double below) {
+  const bool some = below > 0.0;
   const double aa = fabs(alpha);
   const double nrm = sqrt(some ? xx : 1.0);
   Reflector r;
@@ -234,7 +236,8 @@ __global__ __launch_bounds__(NW* kWave) void qr_cols_kernel(const Task* __restri
   int nret = 1;        // retired rows
   for (int j = 0; j < kmax; ++j) {
     const double rj = rows[j][c];
-    const double n1 = fma(rj, rj, wave_partials_sum<NW>(pn1, c));
+    const double below = wave_partials_sum<NW>(pn1, c);
+    const double n1 = fma(rj, rj, below);
     int p = j;
     if (PIV) {
       const double rel = n1 * iref;
@@ -246,7 +249,7 @@ __global__ __launch_bounds__(NW* kWave) void qr_cols_kernel(const Task* __restri
       if (key == 0u || !(rdlane(rel, p) > drop_tol * drop_tol)) break;
     }
     pw[0][w][c] = column_dot(p);
-    const Reflector rf = reflector(rdlane(rj, p), rdlane(n1, p));
+    const Reflector rf = reflector(rdlane(rj, p), rdlane(n1, p), rdlane(below, p));
     if (tid == 0) {
       tau_s[j] = rf.tau;
       scal_s[j] = rf.scal;

@@ -36,7 +36,7 @@ template <> struct Lim<double> {
   static __device__ constexpr double eps() { return DBL_EPSILON; }
   static __device__ constexpr double stop() { return 1e-9; }  // 2^-21 of it is about eps
   static __device__ constexpr double tiny() { return 1e-300; }
-  static __device__ constexpr double pivot_tiny() { return 1e-300; }  // stands for a zero pivot
+  static __device__ constexpr double pivot_tiny() { return 1e-300; }  // the least pivot
 };
 template <> struct Lim<float> {
   static __device__ constexpr float eps() { return FLT_EPSILON; }
@@ -811,7 +811,10 @@ __global__ __launch_bounds__(1024) void jacobi_osj_kernel(const EigTask<T>* __re
   // rounding; one whose rows are sorted (the second pass of ST-HOSVD, sorted by
   // the first) keeps their order and runs on panels (chol_rows).  A remaining
   // diagonal at or below the rounding of its own start (N eps a_kk) is cut:
-  // that pivot is the floor and the rest of its column zero.
+  // that pivot is the floor and the rest of its column zero.  So is one below
+  // the least pivot, whose root the hardware does not form in FP32 (a denormal
+  // gives infinity, and NaN after the correction).  A NaN pivot stays.
+  auto cut = [](T pv, T fl) { return pv <= fl || pv < Lim<T>::pivot_tiny(); };
   if constexpr (!PIV) {
     __shared__ CholShared<T> chs;
     T a[kCholRows];
@@ -824,13 +827,13 @@ __global__ __launch_bounds__(1024) void jacobi_osj_kernel(const EigTask<T>* __re
     chol_rows(
         a, N, lane, wave, chs,
         [&](int k, T pv, T row, T& f) {
-          f = pv <= rdlane(floor_l, k) ? T(0) : row / pv;  // (a NaN pivot stays)
+          f = cut(pv, rdlane(floor_l, k)) ? T(0) : row / pv;
           return true;
         },
         [&](int k, T row) {
           const T pv = rdlane(row, k), fl = rdlane(floor_l, k);
-          const bool dead = pv <= fl;
-          const T d = dead ? (fl > T(0) ? fl : Lim<T>::pivot_tiny()) : pv;
+          const bool dead = cut(pv, fl);
+          const T d = dead ? fmax(fl, Lim<T>::pivot_tiny()) : pv;
           const T r = rsq_full(d);
           const T x = dead ? T(0) : row * r;
           if (lane < NM) X0[k * LDX + lane] = lane == k ? d * r : lane > k && lane < N ? x : T(0);
@@ -862,8 +865,8 @@ __global__ __launch_bounds__(1024) void jacobi_osj_kernel(const EigTask<T>* __re
     // ri (zero where the rest of the column is cut)
     T dl = T(0), ri = T(0);
     auto prepare = [&]() {
-      const bool dead = dg <= floor_l;  // false for NaN, which stays
-      const T pv = dead ? (floor_l > T(0) ? floor_l : Lim<T>::pivot_tiny()) : dg;
+      const bool dead = cut(dg, floor_l);
+      const T pv = dead ? fmax(floor_l, Lim<T>::pivot_tiny()) : dg;
       const T r = rsq_full(pv);
       dl = pv * r;
       ri = dead ? T(0) : r;

@@ -290,6 +290,7 @@ __device__ __forceinline__ void tridiag_reg(const EigTask<T>& tk_, TrgShared<T>&
       if (r < N && c < N) v = (r >= c) ? tk_.A[r + (size_t)c * tk_.lda] : tk_.A[c + (size_t)r * tk_.lda];
       a[i][k] = v;
     }
+  __syncthreads();  // the first vector goes into what other waves clear
   // Householder vector of column jj from this wave's registers (called by the
   // wave holding column jj only; jj + 2 < N)
   auto householder = [&](int jj) {

@@ -486,18 +486,49 @@ int do_rhosvd(const tk_block_sum* in, const tk_round_params* prm, const double* 
   return 0;
 }
 
-int do_norm(const tk_block_sum* x, double* out, Arena& ar, hipStream_t st) {
-  Blob blob;
+// Plans the exact norm of a block sum; returns where it leaves the square.
+double* plan_norm(const tk_block_sum* x, const Shape& sh, bool share, Seq& q, Blob& blob, Arena& ar, hipStream_t st) {
   Planner pl(ar, blob);
-  Seq q;
-  const Shape sh = shape_of_blocks(x, 1, 0);
-  TK_CHECK(sh.rc <= 64, kErrUnsupported, "exact norm: ranks above 64");
   std::vector<MoveTask<double, double>> mv;
   const auto im = import_blocks<double>(ar, x, sh, mv);
   emit_moves(q, pl, mv);
   double* n2 = ar.alloc<double>(1);
-  plan_exact_norm2(q, pl, im.sh, im.blocks, n2);
+  plan_exact_norm2(q, pl, im.sh, im.blocks, n2, share);
   finish_blob(ar, blob, st);
+  return n2;
+}
+
+// The workspace is that of distinct factors: it must not depend on which
+// pointers coincide, as the query may be asked with other ones.  Blocks that
+// do share a factor are planned with it taken once where that plan fits in
+// (it needs less but for its splits, which follow its own sizes).
+int do_norm(const tk_block_sum* x, double* out, Arena& ar, hipStream_t st) {
+  const Shape sh = shape_of_blocks(x, 1, 0);
+  TK_CHECK(sh.rc <= 64, kErrUnsupported, "exact norm: ranks above 64");
+  bool share = false;
+  for (int k = 0; k < sh.d; ++k) {
+    std::vector<const double*> u;
+    for (int b = 0; b < x->nblocks; ++b) u.push_back(x->blocks[b].U[k]);
+    std::sort(u.begin(), u.end());
+    share |= std::adjacent_find(u.begin(), u.end()) != u.end();
+  }
+  Blob blob;
+  Seq q;
+  double* n2 = nullptr;
+  if (share && !ar.measuring()) {
+    size_t need[2] = {0, 0};  // of distinct, of shared factors
+    for (int i = 0; i < 2; ++i) {
+      Arena probe(nullptr, 0);
+      Blob b;
+      Seq s;
+      plan_norm(x, sh, i == 1, s, b, probe, st);
+      need[i] = probe.used();
+    }
+    TK_CHECK(ar.capacity() >= need[0], kErrWorkspace,
+             "workspace too small: need at least " + std::to_string(need[0]) + " bytes");
+    share = need[1] <= need[0];
+  }
+  n2 = plan_norm(x, sh, share && !ar.measuring(), q, blob, ar, st);
   if (ar.measuring()) return 0;
   TK_CHECK(out != nullptr, kErrInvalidArg, "output pointer is NULL");
   q.run(st);

@@ -86,6 +86,7 @@ class Arena {
   // Bytes the workspace must hold (the high-water mark).
   size_t used() const { return peak_; }
   bool measuring() const { return base_ == nullptr; }
+  size_t capacity() const { return cap_; }
   // Scratch scopes: buffers allocated after mark() are handed out again after
   // rewind(); valid only for plans whose steps never run concurrently.  An
   // allocation that must outlive every scope (read by steps of several

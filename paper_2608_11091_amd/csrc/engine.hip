@@ -1386,7 +1386,8 @@ void plan_inner(Seq& q, Planner& pl, const Shape& sh, const std::vector<TT<T>>& 
 }
 
 // ====================================================================== exact norm
-void plan_exact_norm2(Seq& q, Planner& pl, const Shape& sh, const Blocks<double>& in, double* out_norm2) {
+void plan_exact_norm2(Seq& q, Planner& pl, const Shape& sh, const Blocks<double>& in, double* out_norm2,
+                      bool share) {
   constexpr double kCutTol = 64.0 * 0x1p-53;
   const int d = sh.d, rc = sh.rc, nb = in.size();
   Arena& ar = pl.ar;
@@ -1401,7 +1402,7 @@ void plan_exact_norm2(Seq& q, Planner& pl, const Shape& sh, const Blocks<double>
   int m = 1;
   for (int k = 0; k < d; ++k) {
     for (int b = 0; b < nb; ++b) {
-      auto it = std::find(fac[k].begin(), fac[k].end(), in.U[b][k]);
+      auto it = share ? std::find(fac[k].begin(), fac[k].end(), in.U[b][k]) : fac[k].end();
       if (it == fac[k].end()) {
         fac[k].push_back(in.U[b][k]);
         facr[k].push_back(in.rank[b] + k);

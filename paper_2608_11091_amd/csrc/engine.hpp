@@ -199,7 +199,10 @@ void plan_core_projection(Seq& q, Planner& pl, const Shape& sh, const Blocks<T>&
                           const T* W = nullptr);
 
 // Exact squared Frobenius norm of a block sum (QR of concatenated factors).
-void plan_exact_norm2(Seq& q, Planner& pl, const Shape& sh, const Blocks<double>& in, double* out_norm2);
+// `share`: factors at one address are orthogonalised once (buffers follow the
+// number of distinct ones); otherwise every block's count as its own.
+void plan_exact_norm2(Seq& q, Planner& pl, const Shape& sh, const Blocks<double>& in, double* out_norm2,
+                      bool share = true);
 
 // ------------------------------------------------------------------ multilinear Nystrom
 // Sketched form of a Tucker tensor X (Sec. 3.3): the projected core

@@ -184,8 +184,10 @@ int tucker_sketch_workspace(const tk_block_sum* x, int64_t s, int32_t form, size
  * that forbid hipMalloc).  Same arguments, result and errors as tucker_sketch,
  * without the workspace: its temporaries live in a static device array of
  * 64 MiB that the library holds on every GPU it runs on until the process
- * ends.  A call whose workspace query (tucker_sketch_workspace) exceeds
- * 64 MiB launches nothing and returns TK_ERR_WORKSPACE.  The call allocates
+ * ends.  A call that cannot be planned in 64 MiB launches nothing and returns
+ * TK_ERR_WORKSPACE; one whose workspace query (tucker_sketch_workspace) exceeds
+ * 64 MiB is planned without the buffers that the query reserves for splitting
+ * products over the chip.  The call allocates
  * no device memory (no hipMalloc / hipFree).  All calls on one GPU share that
  * array: calls that overlap in time on the same GPU (different streams or
  * host threads) race and must be serialised by the caller. */

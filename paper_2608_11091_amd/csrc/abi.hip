@@ -396,7 +396,7 @@ std::array<const float*, kMaxD> sketch_f32(Arena& ar, const Shape& sh, const dou
 }
 
 int do_sketch(const tk_block_sum* x, const double* const* S, int64_t s, int form, double* out, Arena& ar,
-              hipStream_t st) {
+              hipStream_t st, bool lean = false) {
   TK_CHECK(S != nullptr && out != nullptr, kErrInvalidArg, "sketch factors or output missing");
   TK_CHECK(s >= 1 && s <= 65535, kErrInvalidArg, "sketch size out of range");
   check_form(form);
@@ -410,12 +410,23 @@ int do_sketch(const tk_block_sum* x, const double* const* S, int64_t s, int form
     Sk[k] = S[k];
   }
   pl.bf16_factors = form == TK_FORM_BF16;
+  pl.lean = lean;
   if (form != TK_FORM_FP64) {
     std::vector<MoveTask<double, float>> mv;
     const auto S32 = sketch_f32(ar, sh, Sk.data(), size_t(s), mv);
     const auto im = import_blocks<float>(ar, x, sh, mv);
     emit_moves(q, pl, mv);
     plan_sketch<float>(q, pl, sh, im.blocks, S32, int(s), out);
+  } else if (lean) {  // one import launch per block, without a table
+    Blocks<double> blocks;
+    for (int b = 0; b < x->nblocks; ++b) {
+      TT<double> t;  // (a sketch reads no ranks)
+      t.core = ar.alloc<double>(sh.core_len());
+      for (int k = 0; k < sh.d; ++k) t.U[k] = ar.alloc<double>(size_t(sh.n[k]) * sh.rc);
+      emit_import(q, sh, x->blocks[b], t);
+      blocks.add(t, nullptr, x->coef[b]);
+    }
+    plan_sketch<double>(q, pl, sh, blocks, Sk, int(s), out);
   } else {
     std::vector<MoveTask<double, double>> mv;
     const auto im = import_blocks<double>(ar, x, sh, mv);
@@ -1033,16 +1044,25 @@ int tucker_sketch(const tk_block_sum* x, const double* const* S, int64_t s, int3
 int tucker_sketch_noalloc(const tk_block_sum* x, const double* const* S, int64_t s, int32_t form, double* out,
                           void* stream) {
   return guarded([&] {
+    bool lean = false;
     {
-      // size check first, so that an oversized call launches nothing
+      // size check first, so that an oversized call launches nothing; a plan
+      // that is too large is tried again without the buffers of split products
       Arena probe(nullptr, 0);
       do_sketch(x, S, s, form, out, probe, nullptr);
-      TK_CHECK(probe.used() <= kNoAllocScratchBytes, kErrWorkspace,
-               "tucker_sketch_noalloc: needs " + std::to_string(probe.used()) +
+      size_t need = probe.used();
+      lean = need > kNoAllocScratchBytes;
+      if (lean) {
+        Arena small(nullptr, 0);
+        do_sketch(x, S, s, form, out, small, nullptr, true);
+        need = small.used();
+      }
+      TK_CHECK(need <= kNoAllocScratchBytes, kErrWorkspace,
+               "tucker_sketch_noalloc: needs " + std::to_string(need) +
                    " bytes of scratch, above its static maximum of " + std::to_string(kNoAllocScratchBytes));
     }
     Arena ar(noalloc_scratch(), kNoAllocScratchBytes);
-    return do_sketch(x, S, s, form, out, ar, as_stream(stream));
+    return do_sketch(x, S, s, form, out, ar, as_stream(stream), lean);
   });
 }
 int tucker_sketch_workspace(const tk_block_sum* x, int64_t s, int32_t form, size_t* bytes) {

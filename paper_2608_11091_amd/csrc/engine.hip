@@ -132,7 +132,7 @@ void emit_gemm(Seq& q, Planner& pl, GemmDesc<T>&& g) {
   // 256 of them and a launch that folds the partials to 16.  Products that
   // already fill the chip or have little K run whole.
   int splits = 1, folds = 0;
-  if (tiles < 256) {
+  if (tiles < 256 && !pl.lean) {
     const long room = std::max<long>(1, 512 / tiles);
     if (g.split_out) {
       if (!small && slabs > kLongSlabs && room >= 64) {

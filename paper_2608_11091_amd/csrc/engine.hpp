@@ -117,6 +117,7 @@ struct Planner {
   // matrix cores with FP32 accumulation; cores, Grams, QRs and eigensolves
   // keep FP32 / FP64.
   bool bf16_factors = false;
+  bool lean = false;  // no buffers that only buy speed (products are not split)
   Planner(Arena& a, Blob& b) : ar(a), blob(b) {}
 };
 

@@ -37,6 +37,7 @@ struct GemmDesc {
   long astr = 0, cstr = 0;
   bool own_dims = false;               // every group has dims of its own (group_dims)
   bool any_ops = false;                // and transposes of its own (group_ops); small launches only
+  bool gated = false;                  // every group has one term with a gate (group1)
   bool factor_product = false;         // a product with a Tucker factor (BF16 in the BF16-factor form)
   // optional: the only consumer of C sums the split-K partials itself, which
   // saves the reduction launch (C is then not written); needs beta = 0,
@@ -67,15 +68,16 @@ struct GemmDesc {
     any_ops = true;
   }
   void group1(T* C, const T* A, const T* B, const double* c1 = nullptr, const double* c2 = nullptr,
-              const double* c3 = nullptr, double scale = 1.0) {
-    group(C, {GemmTerm<T>{A, B, c1, c2, c3, scale}});
+              double scale = 1.0, const double* gate = nullptr) {
+    group(C, {GemmTerm<T>{A, B, c1, c2, gate, scale}});
+    gated = gate != nullptr;
   }
 };
 
 template <typename T>
 GemmTerm<T> term(const T* A, const T* B, const double* c1 = nullptr, const double* c2 = nullptr,
-                 const double* c3 = nullptr, double scale = 1.0) {
-  return GemmTerm<T>{A, B, c1, c2, c3, scale};
+                 double scale = 1.0) {
+  return GemmTerm<T>{A, B, c1, c2, nullptr, scale};
 }
 
 constexpr long kSmallTiles = 256;  // 64 x 64 tiles below which a launch takes 32 x 32 ones (128 to 512: the same)
@@ -119,6 +121,7 @@ void emit_gemm(Seq& q, Planner& pl, GemmDesc<T>&& g) {
   const bool small = !L.bf16 && ((tiles64 < kSmallTiles && slabs32 <= kLongSlabs) || g.any_ops);
   L.tile = small ? 32 : 64;
   L.any_ops = g.any_ops;
+  L.gated = g.gated;
   const long tiles = small ? long(ceil_div(g.M, 32)) * ceil_div(g.N, 32) * ng : tiles64;
   const long slabs = small ? slabs64 : slabs32;
   // Split-K for the path's small, long-K products.  With a reduction launch of
@@ -239,7 +242,7 @@ void emit_ttm(Seq& q, Planner& pl, int d, const int* dims, int k, int newdim, co
     g.ldc = newdim;
     if (sum_into) {
       std::vector<GemmTerm<T>> ts;
-      for (int b = 0; b < nbat; ++b) ts.push_back(term<T>(W[b], X[b], c1 ? (*c1)[b] : nullptr, nullptr, nullptr, cscale));
+      for (int b = 0; b < nbat; ++b) ts.push_back(term<T>(W[b], X[b], c1 ? (*c1)[b] : nullptr, nullptr, cscale));
       g.group(sum_into, ts);
       g.terms_are_blocks = nb != nullptr;
     } else {
@@ -259,7 +262,7 @@ void emit_ttm(Seq& q, Planner& pl, int d, const int* dims, int k, int newdim, co
     if (sum_into) {
       TK_CHECK(pre == 1, kErrInvalidArg, "internal: summed TTM needs a leading mode");
       std::vector<GemmTerm<T>> ts;
-      for (int b = 0; b < nbat; ++b) ts.push_back(term<T>(X[b], W[b], c1 ? (*c1)[b] : nullptr, nullptr, nullptr, cscale));
+      for (int b = 0; b < nbat; ++b) ts.push_back(term<T>(X[b], W[b], c1 ? (*c1)[b] : nullptr, nullptr, cscale));
       g.group(sum_into, ts);
       g.terms_are_blocks = nb != nullptr;
     } else {
@@ -321,7 +324,7 @@ void emit_unfold_gram(Seq& q, Planner& pl, int d, const int* dims, int k, const 
     g.K = int(pre);
     g.lda = mid;
     g.ldb = mid;
-    g.group1(G, X, Y, nullptr, nullptr, nullptr, scale);
+    g.group1(G, X, Y, nullptr, nullptr, scale);
   } else {
     g.ta = true;
     g.tb = false;
@@ -330,7 +333,7 @@ void emit_unfold_gram(Seq& q, Planner& pl, int d, const int* dims, int k, const 
     g.ldb = int(post);
     std::vector<GemmTerm<T>> ts;
     for (long p = 0; p < pre; ++p)
-      ts.push_back(term<T>(X + size_t(p) * post * mid, Y + size_t(p) * post * mid, nullptr, nullptr, nullptr, scale));
+      ts.push_back(term<T>(X + size_t(p) * post * mid, Y + size_t(p) * post * mid, nullptr, nullptr, scale));
     g.group(G, ts);
   }
   g.split_out = split_out;
@@ -777,8 +780,8 @@ RoundSumOut<T> plan_roundsum(Seq& q, Planner& pl, const Shape& sh, const Blocks<
         continue;
       }
       // R-side Gram of the padded concatenation, compacted to the active ranks
-      // (only while they fit the compacted capacity NM; blocks of a disabled
-      // mode cost nothing in the GEMM)
+      // (only while they fit the compacted capacity NM; the gate leaves the
+      // blocks of a mode whose ranks do not unread)
       const int NM = std::min(Rp, Rp > n ? kEigRegMax : n);
       const int ldc = NM > kEigRegMax ? (NM + 3) / 4 * 4 : NM;
       double* enable = ar.alloc<double>(kMaxD);
@@ -803,7 +806,7 @@ RoundSumOut<T> plan_roundsum(Seq& q, Planner& pl, const Shape& sh, const Blocks<
           for (int b2 = 0; b2 <= b; ++b2)
             for (int k : modes) {
               g.group1(Gp + size_t(k) * Rp * Rp + size_t(b) * rc + size_t(b2) * rc * Rp, in.U[b][k], in.U[b2][k],
-                       w + b, w + b2, enable + k);
+                       w + b, w + b2, 1.0, enable + k);
               g.group_dims(rc, sh.n[k], sh.n[k], sh.n[k], Rp);
             }
         emit_gemm(q, pl, std::move(g));
@@ -1459,7 +1462,7 @@ void plan_exact_norm2(Seq& q, Planner& pl, const Shape& sh, const Blocks<double>
         g.ldb = ldb;
         g.ldc = ldc;
         g.beta = beta;
-        for (int k : act) g.group1(Cf(k), Af(k), Bf(k), nullptr, nullptr, nullptr, alpha);
+        for (int k : act) g.group1(Cf(k), Af(k), Bf(k), nullptr, nullptr, alpha);
         emit_gemm(q, pl, std::move(g));
       };
       std::vector<double*> xs;
@@ -1645,7 +1648,7 @@ void plan_gemm(Seq& q, Planner& pl, bool ta, bool tb, int M, int N, int K, const
   g.ldb = ldb;
   g.ldc = ldc;
   g.beta = beta;
-  g.group1(C, A, B, nullptr, nullptr, nullptr, alpha);
+  g.group1(C, A, B, nullptr, nullptr, alpha);
   emit_gemm(q, pl, std::move(g));
 }
 
@@ -1664,7 +1667,7 @@ void plan_gemm_batched(Seq& q, Planner& pl, bool ta, bool tb, int M, int N, int 
   g.lda = lda;
   g.ldb = ldb;
   g.ldc = ldc;
-  for (size_t i = 0; i < C.size(); ++i) g.group1(C[i], A[i], B[i], nullptr, nullptr, nullptr, alpha);
+  for (size_t i = 0; i < C.size(); ++i) g.group1(C[i], A[i], B[i], nullptr, nullptr, alpha);
   emit_gemm(q, pl, std::move(g));
 }
 

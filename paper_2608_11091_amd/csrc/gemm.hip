@@ -88,7 +88,8 @@ __global__ __launch_bounds__(NT) void gemm_kernel(int M, int N, int K, int lda, 
                                                   const GemmTerm<T>* __restrict__ terms,
                                                   const GemmGroup<T>* __restrict__ groups, double beta,
                                                   int splits, T* __restrict__ partial, size_t pstride,
-                                                  int max_terms, int uniform_terms, bool mixed, RowBlocks rb_) {
+                                                  int max_terms, int uniform_terms, bool mixed, bool gated,
+                                                  RowBlocks rb_) {
   static_assert(!BF || sizeof(T) == 4, "bf16 operands with FP32 storage only");
   static_assert(!BF || TS == 64, "bf16 operands with the large tile only");
   static_assert(OPS != kAnyOps || TS == 32, "operations per group with the small tile only");
@@ -140,7 +141,11 @@ __global__ __launch_bounds__(NT) void gemm_kernel(int M, int N, int K, int lda, 
   const int nks = (K + KB - 1) / KB;
   const int total = nterm * nks;
   const int per = (total + splits - 1) / splits;
-  const int sb = sp * per, se = min(total, sb + per);
+  const int sb = sp * per;
+  int se = min(total, sb + per);
+  // a term that is left out is not read (its alpha is known only after its
+  // operands are on their way)
+  if (gated && nterm > 0 && uniform_zero(*terms[t0].gate)) se = sb;
   const int Ml = min(BM, M - m0), Nl = min(BN, N - n0);  // live rows and columns of the tile
   const int mt = (Ml + 15) >> 4, nt = (Nl + 15) >> 4;
   // large tile: a wave owns 16 rows (or 16 columns) of it and `live`
@@ -171,13 +176,12 @@ __global__ __launch_bounds__(NT) void gemm_kernel(int M, int N, int K, int lda, 
   // multiplied, whatever its operands hold.
   int t = t0, kf = 0;  // term and k of the slab to fetch
   GemmTerm<T> tm = {}, tn = {};
-  double c1 = 1.0, c2 = 1.0, c3 = 1.0, sc = 0.0;  // coefficients of the fetched slab's term
+  double c1 = 1.0, c2 = 1.0, sc = 0.0;  // coefficients of the fetched slab's term
   T ra[SA], rb[SB];
   auto coefs = [&]() {
     sc = tm.scale;
     c1 = tm.c1 ? *tm.c1 : 1.0;
     c2 = tm.c2 ? *tm.c2 : 1.0;
-    c3 = tm.c3 ? *tm.c3 : 1.0;
   };
   const size_t arow = TA ? 0 : rb_.at(min(m0 + am0, M - 1), rb_.astr);  // (one row per thread when A is not transposed)
   auto load = [&]() {
@@ -220,7 +224,6 @@ __global__ __launch_bounds__(NT) void gemm_kernel(int M, int N, int K, int lda, 
       double al = sc;
       al *= c1;
       al *= c2;
-      al *= c3;
       alpha = T(al);
     }
     auto next = [&]() {  // fetch the following slab
@@ -237,8 +240,8 @@ __global__ __launch_bounds__(NT) void gemm_kernel(int M, int N, int K, int lda, 
       load();
       if (fresh) coefs();
     };
-    // a slab of a zero-coefficient term (e.g. a disabled Gram block) adds
-    // nothing: it is neither staged nor multiplied
+    // a slab of a zero-coefficient term adds nothing: it is neither staged nor
+    // multiplied
     if (uniform_zero(alpha)) {
       next();
       continue;
@@ -430,7 +433,7 @@ void gemm_run(const GemmLaunch<T>& g, hipStream_t st) {
   if (ops == OPS && g.tile == TS && g.bf16 == BF)                                                              \
     hipLaunchKernelGGL((gemm_kernel<T, OPS, TS, BF && sizeof(T) == 4>), grid, dim3(NT), 0, st, g.M, g.N, g.K,  \
                        g.lda, g.ldb, g.ldc, g.terms, g.groups, g.beta, g.splits, part, pstride, g.max_terms,   \
-                       g.uniform_terms, g.mixed, rb);
+                       g.uniform_terms, g.mixed, g.gated, rb);
 #define TK_GEMM_CASES(TS, BF)         \
   TK_GEMM_CASE(0, TS, BF)             \
   TK_GEMM_CASE(1, TS, BF)             \

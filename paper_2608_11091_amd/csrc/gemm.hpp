@@ -4,7 +4,7 @@
 //     C_g = beta * C_g + sum_{t in terms(g)} alpha_t * op(A_t) * op(B_t)
 // with column-major operands, of uniform shape M x N x K unless the launch is
 // mixed.  alpha_t is
-// scale_t * (*c1_t) * (*c2_t) * (*c3_t) with optional device scalars, so
+// scale_t * (*c1_t) * (*c2_t) with optional device scalars, so
 // device-resident coefficients (inner products, least-squares solutions,
 // block weights) scale terms without a host round trip.  Term and group
 // tables live in device memory and are built once per plan.
@@ -20,7 +20,7 @@ struct GemmTerm {
   const T* B;
   const double* c1;  // optional device scalar (nullptr = 1)
   const double* c2;  // optional device scalar (nullptr = 1)
-  const double* c3;  // optional device scalar (nullptr = 1)
+  const double* gate;  // read when the launch is gated: 0 leaves the term out
   double scale;
 };
 
@@ -55,6 +55,7 @@ struct GemmLaunch {
   int mblk = 0;
   long astr = 0, cstr = 0;
   int max_terms = 1 << 30; // clamp every group to its first max_terms terms
+  bool gated = false;      // groups of one term, left out (C = 0) where its gate is 0
   bool bf16 = false;       // FP32 storage: round the operands to bfloat16, BF16 matrix cores, FP32 accumulation
   bool defer_reduce = false;  // splits > 1: leave the partials for the consumer to sum (C is not written)
   double flops = 0.0;      // algorithmic flops of this launch (for the kernel timer)

@@ -18,6 +18,7 @@
 
 #include "chol.hpp"
 #include "kernels.hpp"
+#include "rotation.hpp"
 
 namespace tk {
 
@@ -34,7 +35,7 @@ template <> struct Vec4<double> { using type = double __attribute__((ext_vector_
 template <typename T> struct Lim;
 template <> struct Lim<double> {
   static __device__ constexpr double eps() { return DBL_EPSILON; }
-  static __device__ constexpr double stop() { return 1e-9; }  // 2^-21 of it is about eps
+  static __device__ constexpr double stop() { return 1.490116119384766e-08; }  // sqrt(eps)
   static __device__ constexpr double tiny() { return 1e-300; }
   static __device__ constexpr double pivot_tiny() { return 1e-300; }  // the least pivot
 };
@@ -644,45 +645,6 @@ __global__ __launch_bounds__(1024) void tridiag_gm_kernel(const EigTask<T>* __re
 
 // ------------------------------------------------------------ eigenvalues + vectors
 
-
-// 1 / sqrt(x) to working accuracy: the hardware approximation (1 ulp in FP32,
-// about 23 bits in FP64) and one step, of third order in FP64.  The FP32 step
-// matters: an error of the root is common to a whole column and reaches the
-// result once a mode (200 RoundSums of ranks 3 to 12: mean error against 64
-// bits 3-8% below the rotated vectors of a two-sided sweep with it, above
-// without).
-__device__ __forceinline__ float rsq_full(float x) {
-  const float y = __builtin_amdgcn_rsqf(x), h = x * y;
-  const float e = fmaf(-fmaf(x, y, -h), y, fmaf(-h, y, 1.0f));
-  return fmaf(0.5f * y, e, y);
-}
-__device__ __forceinline__ double rsq_full(double x) {
-  const double y = __builtin_amdgcn_rsq(x);
-  const double e = fma(-x * y, y, 1.0);
-  return fma(y * e, fma(0.375, e, 0.5), y);
-}
-
-// t = tan of the rotation that makes columns with dot product d and squared
-// norms nx, ny orthogonal: sign(z) / (|z| + sqrt(1 + z^2)), z = (ny - nx) / 2d.
-// FP64 forms z with the hardware reciprocal and the rest in FP32: an angle
-// with a relative error of 2^-21 leaves that share of the product it
-// annihilates, which the stopping rule allows for; the cosine belongs to the
-// t that is used and has working accuracy, so the rotation is orthogonal.
-// The root is taken of a z bounded against overflow: it is |z| itself long
-// before the bound.
-__device__ __forceinline__ float jac_tan_of(float z) {
-  const float az = fabsf(z);
-  const float q = fminf(az, 1e18f);
-  const float w = fmaf(q, q, 1.0f);
-  return copysignf(__builtin_amdgcn_rcpf(az + fmaxf(w * __builtin_amdgcn_rsqf(w), az)), z);
-}
-__device__ __forceinline__ float jac_tan(float d, float nx, float ny) {
-  return jac_tan_of((ny - nx) * __builtin_amdgcn_rcpf(d + d));
-}
-__device__ __forceinline__ double jac_tan(double d, double nx, double ny) {
-  return double(jac_tan_of(float((ny - nx) * __builtin_amdgcn_rcp(d + d))));
-}
-
 // Sum over the 8 lanes of a column group; every lane gets the same value.
 template <typename T>
 __device__ __forceinline__ T group8_sum(T v) {
@@ -919,8 +881,8 @@ __global__ __launch_bounds__(1024) void jacobi_osj_kernel(const EigTask<T>* __re
   T nA = T(0), nB = T(0);
 #pragma unroll
   for (int i = 0; i < RPL; ++i) {
-    A[i] = act ? X0[(2 * g) * LDX + l + 8 * i] : T(0);
-    B[i] = act ? X0[(2 * g + 1) * LDX + l + 8 * i] : T(0);
+    A[i] = act ? ldexp(X0[(2 * g) * LDX + l + 8 * i], kJacExp<T> / 2) : T(0);
+    B[i] = act ? ldexp(X0[(2 * g + 1) * LDX + l + 8 * i], kJacExp<T> / 2) : T(0);
   }
   bool big = false;
   // rotates (x, y) to orthogonal columns; where nothing is to be done applies
@@ -992,9 +954,8 @@ __global__ __launch_bounds__(1024) void jacobi_osj_kernel(const EigTask<T>* __re
     }
     // Read after the sweep's last barrier: the same values in every thread.
     // Stop after a sweep whose rotations all had scaled products
-    // |x_p . x_q| / (||x_p|| ||x_q||) at or below a bound whose square, and whose share that an inexact angle leaves, are O(eps):
-    // cyclic Jacobi converges quadratically, so another sweep would only
-    // confirm.
+    // |x_p . x_q| / (||x_p|| ||x_q||) at or below sqrt(eps): cyclic Jacobi
+    // converges quadratically, so another sweep would only confirm.
     if (bigflag[sweep % 3] == 0) break;
   }
 
@@ -1020,8 +981,8 @@ __global__ __launch_bounds__(1024) void jacobi_osj_kernel(const EigTask<T>* __re
       posB += __shfl_xor(posB, m, 8);
     }
     if (l == 0) {
-      lam_d[posA] = ldexp(nA, ex);
-      lam_d[posB] = ldexp(nB, ex);
+      lam_d[posA] = ldexp(nA, ex - kJacExp<T>);
+      lam_d[posB] = ldexp(nB, ex - kJacExp<T>);
     }
   }
   __syncthreads();

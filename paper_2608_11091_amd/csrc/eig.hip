@@ -178,8 +178,9 @@ __device__ void tridiag_spectrum(const EigTask<T>& tk_, T* dd, T* ee, T* lam, T*
   // FP64, and a tail threshold below the zero clamp whatever the spectrum
   // (tau^2 N < delta: the total is at most N lambda_1, so every eigenvalue
   // above delta lambda_1 exceeds tau^2 total by itself): r~ is the number of
-  // eigenvalues above delta lambda_1, so only the largest one is located, to
-  // 1e-7 of itself (256 points a round), and one more count gives the rank.
+  // eigenvalues above delta lambda_1, so only the largest one is located (256
+  // points a round), as far as it takes the counts at delta times both ends of
+  // its interval to agree: four rounds, but for an eigenvalue that lies between.
   // (Not in FP32, where the clamp lies below the Gram's rounding and the
   // count follows the noise of the eigenvalues as computed.)
   if constexpr (sizeof(T) == 8) {
@@ -187,7 +188,17 @@ __device__ void tridiag_spectrum(const EigTask<T>& tk_, T* dd, T* ee, T* lam, T*
     if (tk_.rule.kind == 1 && tk_.rule.cap1 > 0 && tau * tau * N * 2.0 < tk_.rule.delta) {
       T lo = gl - tolx, hi = gu + tolx;
       int* const first = reinterpret_cast<int*>(lam);  // scratch: first point above lambda_1, by wave
-      for (int it = 0; it < 4; ++it) {
+      for (int it = 0; it < 16; ++it) {
+        if (it >= 4) {
+          if (tid < kWave) {  // lane 0: the lower end, the others: the upper one
+            const int c = sturm_count(dd, ee, N, T(tk_.rule.delta) * (tid == 0 ? lo : hi), pivmin);
+            if (tid < 2) first[tid] = c;
+          }
+          __syncthreads();
+          const bool done = first[0] == first[1] || !(hi - lo > tolx);
+          __syncthreads();
+          if (done) break;  // uniform
+        }
         if (tid < 256) {
           const T mid = lo + (hi - lo) * (T(tid + 1) / T(257));
           const unsigned long long up = __ballot(sturm_count(dd, ee, N, mid, pivmin) == N);
@@ -200,7 +211,12 @@ __device__ void tridiag_spectrum(const EigTask<T>& tk_, T* dd, T* ee, T* lam, T*
         lo = f > 0 ? lo + span * (T(f) / T(257)) : lo;
         __syncthreads();
       }
-      if (tid == 0) *tk_.rule.rank_out = hi > T(0) ? N - sturm_count(dd, ee, N, T(tk_.rule.delta) * hi, pivmin) : 0;
+      if (tid == 0) {
+        const int below = first[0] == first[1]
+                              ? first[1]
+                              : sturm_count(dd, ee, N, T(tk_.rule.delta) * (T(0.5) * (lo + hi)), pivmin);
+        *tk_.rule.rank_out = hi > T(0) ? N - below : 0;
+      }
       return;  // uniform
     }
   }

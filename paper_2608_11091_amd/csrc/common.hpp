@@ -38,7 +38,6 @@ enum Status : int {
   kErrUnsupported = -7,
 };
 
-void set_error(const std::string& msg);
 const char* last_error();
 
 struct Error {

@@ -208,11 +208,6 @@ void emit_gemm(Seq& q, Planner& pl, GemmDesc<T>&& g) {
   });
 }
 
-template <typename X>
-size_t blob_ptrs(Blob& b, const std::vector<X>& v) {
-  return b.add(v);
-}
-
 // Y_b = X_b x_k W_b (mode-k TTM) for a batch.  X dims `dims` (row-major);
 // W_b is (newdim x dims[k]) col-major with leading dimension ldw, or, when
 // w_transposed, W_b^T is given as (dims[k] x newdim) with leading dim ldw.

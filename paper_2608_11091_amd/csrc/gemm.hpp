@@ -64,11 +64,4 @@ struct GemmLaunch {
 template <typename T>
 void gemm_run(const GemmLaunch<T>& g, hipStream_t st);
 
-// Host-side builder: collects the tables of many launches, uploads once.
-template <typename T>
-struct GemmTables {
-  std::vector<GemmTerm<T>> terms;
-  std::vector<GemmGroup<T>> groups;
-};
-
 }  // namespace tk

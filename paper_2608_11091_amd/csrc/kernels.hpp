@@ -36,11 +36,6 @@ template <typename T>
 void krp_reduce(const KrpTask<T>* tasks_d, int ntasks, int m, const int* z, int P, int S, hipStream_t st);
 
 // ---- reductions over flat vectors --------------------------------------------
-// out[i] = sum_e x_i[e]^2 for i < n (x_i = base + i * stride), deterministic order.
-template <typename T>
-void sumsq_batched(const T* base, size_t stride, size_t len, int n, double* out, hipStream_t st);
-// out[i] = |coef[i]| * sqrt(sumsq[i]) (RoundSum energy weights).
-void block_weights(const double* coef, const double* sumsq, int n, double* w, hipStream_t st);
 // out[i] = scale_i * sum_e x_i[e] * y_i[e]; x_i = xs[i], y_i = ys[i] (device pointer tables).
 template <typename T>
 void dot_batched(const T* const* xs, const T* const* ys, size_t len, int n, double scale, double* out, double* part,
@@ -127,9 +122,6 @@ void cast_multi(const CastSet<A, B>& set, hipStream_t st);
 // outside the valid region are zero.
 template <typename T>
 void core_recap(const T* src, const int* sd, const int* sv, T* dst, const int* dd, int d, hipStream_t st);
-// Zero columns [*from_dev, cols) of a column-major rows x cols matrix.
-template <typename T>
-void zero_cols_from(T* A, int ld, int rows, int cols, const int* from_dev, hipStream_t st);
 // RoundSum's width s = min(max_k rank + p, cap + p) from the kept ranks (as
 // sketch_width computes it), written to *s_out, and the zeroing that follows:
 // columns of the bases U_k (n_k x sc) at or beyond s, optionally every core
@@ -299,17 +291,13 @@ void sketch_width(const int* rt, int d, int p, int cap, int force, int* s_out, h
 // ---- small bookkeeping kernels ------------------------------------------------
 // coef[b] = cscale[b] * (cptr[b] ? *cptr[b] : 1) for b < *nb (or nb_static).
 void gather_coef(const double* const* cptr, const double* cscale, int nb, double* coef, hipStream_t st);
-// If *total <= *zthr: ranks = 1, factor columns = e_1, core zero (capacity rc layout).
-template <typename T>
-void zero_sum_fixup(const double* total, const double* zthr, int d, const int* n, int rc, T* const* U, T* core,
-                    size_t core_len, int* rank, hipStream_t st);
-// zthr = (tol * sum_{b < nb} w[b])^2.
-void zero_threshold(const double* w, int nb, double tol, double* zthr, hipStream_t st);
-// gather_coef, block_weights and zero_threshold in one launch (one
-// workgroup): coef[b], w[b] = |coef[b]| sqrt(sumsq[b]) and zthr.
+// RoundSum's block coefficients, energy weights and zero-sum threshold in one
+// launch (one workgroup): coef[b] as gather_coef, w[b] = |coef[b]| sqrt(sumsq[b])
+// and zthr = (tol sum_b w[b])^2.
 void coef_weights_threshold(const double* const* cptr, const double* cscale, const double* sumsq, int nb, double tol,
                             double* coef, double* w, double* zthr, hipStream_t st);
-// core_recap (no view limit) followed by zero_sum_fixup, in one launch.
+// core_recap (no view limit); if *total <= *zthr the core is zero instead, every
+// factor e_1 in its first column and every rank 1.
 template <typename T>
 void core_recap_fixup(const T* src, const int* sd, T* dst, const int* dd, int d, const double* total,
                       const double* zthr, const int* n, int rc, T* const* U, int* rank, hipStream_t st);

@@ -17,14 +17,6 @@ __global__ void gather_coef_kernel(const double* const* cptr, const double* csca
   if (b < nb) coef[b] = cscale[b] * (cptr[b] ? *cptr[b] : 1.0);
 }
 
-__global__ void zero_threshold_kernel(const double* w, int nb, double tol, double* zthr) {
-  if (threadIdx.x != 0) return;
-  double s = 0.0;
-  for (int b = 0; b < nb; ++b) s += w[b];
-  s *= tol;
-  *zthr = s * s;
-}
-
 __global__ __launch_bounds__(256) void coef_weights_threshold_kernel(const double* const* cptr, const double* cscale,
                                                                      const double* sumsq, int nb, double tol,
                                                                      double* coef, double* w, double* zthr) {
@@ -39,22 +31,6 @@ __global__ __launch_bounds__(256) void coef_weights_threshold_kernel(const doubl
   for (int b = 0; b < nb; ++b) s += w[b];
   s *= tol;
   *zthr = s * s;
-}
-
-template <typename T>
-__global__ void zero_sum_fixup_kernel(const double* total, const double* zthr, int d, int n0, int n1, int n2, int n3, int rc, T* U0, T* U1,
-                                      T* U2, T* U3, T* core, size_t core_len, int* rank) {
-  if (*total > *zthr) return;
-  const int ns[4] = {n0, n1, n2, n3};
-  T* Us[4] = {U0, U1, U2, U3};
-  const size_t tid = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
-  const size_t nth = (size_t)gridDim.x * blockDim.x;
-  for (int k = 0; k < d; ++k) {
-    const size_t len = size_t(ns[k]) * rc;
-    for (size_t e = tid; e < len; e += nth) Us[k][e] = (e == 0) ? T(1) : T(0);
-  }
-  for (size_t e = tid; e < core_len; e += nth) core[e] = T(0);
-  if (tid < size_t(d)) rank[tid] = 1;
 }
 
 template <typename T>
@@ -73,16 +49,6 @@ __global__ void sum_vectors_kernel(const T* base, size_t stride, int nb, int len
   double s = 0.0;
   for (int b = 0; b < nb; ++b) s += double(base[b * stride + l]);
   out[l] = s;
-}
-
-template <typename T>
-__global__ void zero_cols_from_kernel(T* A, int ld, int rows, int cols, const int* from_dev) {
-  const int from = max(*from_dev, 0);
-  const size_t e = size_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  const size_t len = size_t(rows) * cols;
-  if (e >= len) return;
-  const int c = int(e / rows), r = int(e % rows);
-  if (c >= from) A[r + size_t(c) * ld] = T(0);
 }
 
 // The sketch width s = min(max_k (rt_k + p), cap + p), or force when force >= 0
@@ -259,25 +225,6 @@ void gather_coef(const double* const* cptr, const double* cscale, int nb, double
   TK_LAUNCH_CHECK();
 }
 
-void zero_threshold(const double* w, int nb, double tol, double* zthr, hipStream_t st) {
-  hipLaunchKernelGGL(zero_threshold_kernel, dim3(1), dim3(64), 0, st, w, nb, tol, zthr);
-  TK_LAUNCH_CHECK();
-}
-
-template <typename T>
-void zero_sum_fixup(const double* total, const double* zthr, int d, const int* n, int rc, T* const* U, T* core,
-                    size_t core_len, int* rank, hipStream_t st) {
-  int nn[4] = {0, 0, 0, 0};
-  T* uu[4] = {nullptr, nullptr, nullptr, nullptr};
-  for (int k = 0; k < d; ++k) {
-    nn[k] = n[k];
-    uu[k] = U[k];
-  }
-  hipLaunchKernelGGL((zero_sum_fixup_kernel<T>), dim3(gsz(core_len)), dim3(256), 0, st, total, zthr, d, nn[0], nn[1], nn[2],
-                     nn[3], rc, uu[0], uu[1], uu[2], uu[3], core, core_len, rank);
-  TK_LAUNCH_CHECK();
-}
-
 template <typename T>
 void mat_axpy(const T* X, int ldx, T* Y, int ldy, int rows, int cols, hipStream_t st) {
   hipLaunchKernelGGL((mat_axpy_kernel<T>), dim3(gsz(size_t(rows) * cols)), dim3(256), 0, st, X, ldx, Y, ldy, rows, cols);
@@ -287,14 +234,6 @@ void mat_axpy(const T* X, int ldx, T* Y, int ldy, int rows, int cols, hipStream_
 template <typename T>
 void sum_vectors(const T* base, size_t stride, int nb, int len, double* out, hipStream_t st) {
   hipLaunchKernelGGL((sum_vectors_kernel<T>), dim3(ceil_div(len, 256)), dim3(256), 0, st, base, stride, nb, len, out);
-  TK_LAUNCH_CHECK();
-}
-
-template <typename T>
-void zero_cols_from(T* A, int ld, int rows, int cols, const int* from_dev, hipStream_t st) {
-  if (rows <= 0 || cols <= 0) return;
-  hipLaunchKernelGGL((zero_cols_from_kernel<T>), dim3(gsz(size_t(rows) * cols)), dim3(256), 0, st, A, ld, rows, cols,
-                     from_dev);
   TK_LAUNCH_CHECK();
 }
 
@@ -485,14 +424,8 @@ void timer_read(int kind, int64_t* launches, double* total_ms, double* total_flo
   *total_bytes = t.bytes;
 }
 
-template void zero_sum_fixup<double>(const double*, const double*, int, const int*, int, double* const*, double*,
-                                     size_t, int*, hipStream_t);
-template void zero_sum_fixup<float>(const double*, const double*, int, const int*, int, float* const*, float*, size_t,
-                                    int*, hipStream_t);
-template void zero_cols_from<double>(double*, int, int, int, const int*, hipStream_t);
 template void width_and_zero<double>(const WidthZero<double>&, int, int, const int*, int, int, int, int*, hipStream_t);
 template void width_and_zero<float>(const WidthZero<float>&, int, int, const int*, int, int, int, int*, hipStream_t);
-template void zero_cols_from<float>(float*, int, int, int, const int*, hipStream_t);
 template void mat_axpy<double>(const double*, int, double*, int, int, int, hipStream_t);
 template void mat_axpy<float>(const float*, int, float*, int, int, int, hipStream_t);
 template void sum_vectors<double>(const double*, size_t, int, int, double*, hipStream_t);

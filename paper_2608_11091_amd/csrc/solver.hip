@@ -723,7 +723,6 @@ void solver_run(Solver& s, TT<double>& x_out, SolveInfo& info, hipStream_t st) {
   info.seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
 }
 
-TT<double> solver_solution(Solver& s) { return s.x[s.xc]; }
 TT<double> solver_slot(Solver& s, int i) { return s.x[i]; }  // i in [0, 3)
 int solver_slot_index(Solver& s) { return s.xc; }
 

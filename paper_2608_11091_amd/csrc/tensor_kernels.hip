@@ -116,24 +116,6 @@ __global__ __launch_bounds__(KRP_NT) void krp_kernel(const KrpTask<T>* __restric
   }
 }
 
-template <typename T>
-__global__ void sumsq_kernel(const T* __restrict__ base, size_t stride, size_t len, double* __restrict__ out) {
-  __shared__ double red[4];
-  const T* x = base + blockIdx.x * stride;
-  double acc = 0.0;
-  for (size_t e = threadIdx.x; e < len; e += blockDim.x) {
-    const double v = double(x[e]);
-    acc += v * v;
-  }
-  const double s = block_sum(acc, red);
-  if (threadIdx.x == 0) out[blockIdx.x] = s;
-}
-
-__global__ void weights_kernel(const double* coef, const double* sumsq, int n, double* w) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) w[i] = fabs(coef ? coef[i] : 1.0) * sqrt(sumsq[i]);
-}
-
 // Dot products, `parts` workgroups each; 16-byte loads, eight in flight per
 // thread.  One CU reads about 50 GB/s, so a long product is spread: workgroup c
 // of a product takes the elements [c, c + 1) * chunk and leaves a partial sum
@@ -489,18 +471,6 @@ void krp_reduce(const KrpTask<T>* tasks_d, int ntasks, int m, const int* z, int 
   timer_end(kKcKrp, st);
 }
 
-template <typename T>
-void sumsq_batched(const T* base, size_t stride, size_t len, int n, double* out, hipStream_t st) {
-  if (n <= 0) return;
-  hipLaunchKernelGGL((sumsq_kernel<T>), dim3(n), dim3(256), 0, st, base, stride, len, out);
-  TK_LAUNCH_CHECK();
-}
-
-void block_weights(const double* coef, const double* sumsq, int n, double* w, hipStream_t st) {
-  hipLaunchKernelGGL(weights_kernel, dim3(ceil_div(n, 64)), dim3(64), 0, st, coef, sumsq, n, w);
-  TK_LAUNCH_CHECK();
-}
-
 // A second launch costs 4 us and more, a single workgroup 1 us per 8 K
 // elements (FP64): spread from 64 K elements on (three squared norms of 110 K
 // elements 16.6 us in one workgroup each, FP64; one of 1.9 M elements 216 us).
@@ -660,7 +630,6 @@ void sketch_width(const int* rt, int d, int p, int cap, int force, int* s_out, h
 
 #define TK_INST(T)                                                                                         \
   template void krp_reduce<T>(const KrpTask<T>*, int, int, const int*, int, int, hipStream_t);             \
-  template void sumsq_batched<T>(const T*, size_t, size_t, int, double*, hipStream_t);                     \
   template void dot_batched<T>(const T* const*, const T* const*, size_t, int, double, double*, double*, hipStream_t); \
   template void scale_copy<T>(const T*, T*, size_t, double, const double*, const double*, hipStream_t);    \
   template void fill<T>(T*, size_t, T, hipStream_t);                                                       \

@@ -1024,9 +1024,10 @@ int tucker_apply_op(const tk_kron_op* op, const tk_tucker* x, int32_t transpose,
 int tucker_apply_op_workspace(const tk_kron_op* op, const tk_tucker* x, int32_t form, size_t* bytes) {
   return guarded([&] {
     Arena ar(nullptr, 0);
-    double* dummy[TK_MAX_D * 64] = {};
-    for (auto& p : dummy) p = reinterpret_cast<double*>(uintptr_t(0x1000));
-    const int r = do_apply(op, x, 0, form, dummy, ar, nullptr);
+    // one stand-in output per product (the sizes are checked by the plan)
+    const size_t np = op && op->nterms > 0 && op->d > 0 ? size_t(op->nterms) * size_t(op->d) : 0;
+    std::vector<double*> dummy(np, reinterpret_cast<double*>(uintptr_t(0x1000)));
+    const int r = do_apply(op, x, 0, form, dummy.data(), ar, nullptr);
     if (bytes) *bytes = ar.used();
     return r;
   });

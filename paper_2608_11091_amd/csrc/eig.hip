@@ -266,9 +266,9 @@ __device__ void tridiag_spectrum(const EigTask<T>& tk_, T* dd, T* ee, T* lam, T*
 // columns a thread holds; the order is a device value), as the registers of
 // order 160 for every matrix made the FP64 form spill at each of them.  With
 // the count in place of the spectrum (below) and the narrower Gram side, the
-// FP64 launches of a preconditioned training step at n = 128 went from 1124 to
-// 224 us on average, those of twelve solver iterations at n = 512 from 295 to
-// 109 us.
+// FP64 launches of a preconditioned training step at n = 128 went from 1122 to
+// 218 us on average, those of twelve solver iterations at n = 512 from 295 to
+// 106 us.
 constexpr int TRG_NT = 1024;            // 16 waves
 constexpr int TRG_NW = TRG_NT / kWave;
 
@@ -683,8 +683,9 @@ __device__ __forceinline__ bool above_tol(float d, float nx, float ny, float tol
 
 // Symmetric positive semidefinite eigensolver with vectors, one workgroup per
 // matrix of order N <= 64: pivoted Cholesky factor A = L L^T (rows in place),
-// then one-sided Jacobi on the columns of L.  Rotations from the right make the columns orthogonal,
-// L W = X with X^T X diagonal, so A = X X^T: the eigenvalues are the squared
+// then one-sided Jacobi on the columns of L (scaled by a power of two, see
+// jac_tan).  Rotations from the right make the columns orthogonal, L W = X with
+// X^T X diagonal, so A = X X^T: the eigenvalues are the squared
 // column norms and the eigenvectors the normalised columns; no eigenvector
 // block is carried along.  Both steps keep the small eigenvalues of a graded
 // matrix D H D to the relative accuracy that the conditioning of H allows, as
@@ -716,11 +717,13 @@ __device__ __forceinline__ bool above_tol(float d, float nx, float ny, float tol
 // Bound: the dependent chain of one wave per SIMD (about 6 cycles an
 // instruction): a rotation step (dot and DPP reduction, the angle's
 // reciprocals and square roots, the rotation, LDS hand-over and barrier) takes
-// 900 cycles in FP64 and 750 in FP32, a pivoted Cholesky step 1000 and 800, one
-// on panels 500 and 400.  Measured at order 53 (two-sided form in brackets):
-// three Grams of 32 partials each 160 us (419) in FP64, 112 us (270) in FP32; a
-// nearly diagonal Gram, the second pass, 36 us (66; 47 pivotless but a step at
-// a time) and 31 us (48); three Grams of order 15 30 us (71) and 23 us (43).
+// 930 cycles in FP64 and 750 in FP32, a pivoted Cholesky step 1000 and 800, one
+// on panels 500 and 400.  Measured in RoundSums (the two-sided form's average
+// over both passes in brackets): three rank-48 blocks at n = 512, order 53, first
+// pass (three Grams a launch) 189 us, second (one Gram) 74.5 us in FP64 (243);
+// two such blocks in FP32 134 and 47 us (128); twelve solver iterations of that
+// size 152 and 55 us (181); three rank-10 blocks, order 15, 33 and 20 us (54).
+// A second-pass Gram that is diagonal to rounding takes 36 us at order 53.
 template <typename T, int RPL, bool PIV>
 __global__ __launch_bounds__(1024) void jacobi_osj_kernel(const EigTask<T>* __restrict__ tasks, int N) {
   constexpr int NT = 1024;

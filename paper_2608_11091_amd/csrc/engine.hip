@@ -263,8 +263,11 @@ void emit_ttm(Seq& q, Planner& pl, int d, const int* dims, int k, int newdim, co
     } else {
       if (pre > 1 && mid <= 128 && pre * post * post < (1L << 32)) {
         // the slices stacked into one product (while its row arithmetic fits 32
-        // bits): full row tiles whatever post is, and one group per tensor (1369 slices of 37 x 37 x 37: 26 -> 18 us,
-        // and no table of 1369 groups to build and upload)
+        // bits): full row tiles whatever post is, and one group per tensor (1369
+        // slices of 37 x 37 x 37: 26 -> 18 us, and no table of 1369 groups to build
+        // and upload).  Beyond 128 (a recovery with r + p > 128, 8 to 64 slices) the
+        // two take the same time (r = 64, r + p = 256: 131 us either way); there the
+        // slices stay, whose long reductions are split.
         g.M = int(pre * post);
         g.mblk = int(post);
         g.astr = post * mid;

@@ -3,9 +3,10 @@
 // Every operation is *planned* once: buffers are carved from the caller's
 // workspace, GEMM / reduction task tables are collected on the host and
 // uploaded in one copy, and the resulting sequence of launches is replayed
-// as often as needed (every sGMRES iteration replays the plan built for its
-// index).  All sizes in a plan are capacities; actual ranks, sketch widths
-// and coefficients are device values read by the kernels.
+// as often as needed.  A solver plans its iterations up to the first full
+// window ahead, each later one when it is first enqueued, and replays an
+// iteration's plan in every cycle.  All sizes in a plan are capacities; actual
+// ranks, sketch widths and coefficients are device values read by the kernels.
 #pragma once
 
 #include <array>

@@ -33,8 +33,9 @@ namespace {
 // over four waves first (16 or 32 rows each) and over eight above 128 rows.
 // Measured, three matrices a launch (in brackets the form that handed the
 // reflector over through LDS and tested every row against the diagonal):
-// pivoted 96 x 48 with Q 123 us (205), plain 48 x 48 with Q 76 (176), R only
-// 256 x 32 72 (98) and 512 x 48 176 (240), pivoted 512 x 48 with Q 339 (940).
+// pivoted 96 x 48 with Q 123 us (205), plain 48 x 48 with Q 78 (176); averages
+// over solves, whose first iterations have lower ranks: R only 256 x 32 58 (79),
+// R only 512 x 48 140 (172), pivoted 512 x 48 with Q 290 (771).
 constexpr int QC_MAXROWS = 512;
 constexpr int QC_V = 16;  // rows per register vector (indexed at run time by the retired row)
 typedef double QcVec __attribute__((ext_vector_type(QC_V)));

@@ -63,13 +63,15 @@ NOTE = {
 # by what the counter reads for a plain copy of known size), valid only for the
 # kernel sources it was measured on: reported as null once any of them changes.
 TRAFFIC = {
-    "jacobi": dict(bytes_per_launch=436974.0,
+    "jacobi": dict(bytes_per_launch=437590.0,
                    sources={"paper_2608_11091_amd/csrc/eig.hip":
-                            "1b70a6194b983cf6c0e58bb739d201557c5b9b8ae40630c0401cc59ade9b08d7",
+                            "7e53702e208481626564c3bed0e3aaac15233f7b43167f39bef267e57e0c9854",
+                            "paper_2608_11091_amd/csrc/rotation.hpp":
+                            "27f5fb3db545495ca25cd479a7bbec0c458c2c24fdbdd218a839688d3f6d0ef3",
                             "paper_2608_11091_amd/csrc/chol.hpp":
                             "14f8360877accdc0609287583c04de139bdd4c39bfde8f67c1fc97fd5370d1e4",
                             "paper_2608_11091_amd/csrc/common.hpp":
-                            "3283029788d10a6301ce5d9ea808f355ff416a945d660ef303ea0e48717daff3"},
+                            "62fe003584502ecaaf1658f1d5cf4aa4d3a462649b528e866ea3755e80cfe965"},
                    profile="profiles/jacobi_osj_traffic_roundsum_n512.md"),
 }
 

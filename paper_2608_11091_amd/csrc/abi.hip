@@ -298,7 +298,9 @@ struct FiniteCheck {
   const double** dptr = nullptr;
   size_t* dlen = nullptr;
   int* count = nullptr;
+  size_t room = 0;  // entries of the tables: null pointers count, as a query has no others
   void add(const double* p, size_t n) {
+    ++room;
     if (p != nullptr && n > 0) {
       ptr.push_back(p);
       len.push_back(n);
@@ -323,8 +325,8 @@ struct FiniteCheck {
     }
   }
   void alloc(Arena& ar) {
-    dptr = ar.alloc<const double*>(std::max<size_t>(ptr.size(), 1));
-    dlen = ar.alloc<size_t>(std::max<size_t>(len.size(), 1));
+    dptr = ar.alloc<const double*>(std::max<size_t>(room, 1));
+    dlen = ar.alloc<size_t>(std::max<size_t>(room, 1));
     count = ar.alloc<int>(1);
   }
   void run(hipStream_t st) const {

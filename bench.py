@@ -65,7 +65,7 @@ NOTE = {
 TRAFFIC = {
     "jacobi": dict(bytes_per_launch=437590.0,
                    sources={"paper_2608_11091_amd/csrc/eig.hip":
-                            "7e53702e208481626564c3bed0e3aaac15233f7b43167f39bef267e57e0c9854",
+                            "54bbfc421d1de46cbae3d1f4d56061ea5e4e205d97b0127aeaea6cc3bef56a3c",
                             "paper_2608_11091_amd/csrc/rotation.hpp":
                             "27f5fb3db545495ca25cd479a7bbec0c458c2c24fdbdd218a839688d3f6d0ef3",
                             "paper_2608_11091_amd/csrc/chol.hpp":

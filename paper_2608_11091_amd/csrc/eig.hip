@@ -188,14 +188,14 @@ __device__ void tridiag_spectrum(const EigTask<T>& tk_, T* dd, T* ee, T* lam, T*
     if (tk_.rule.kind == 1 && tk_.rule.cap1 > 0 && tau * tau * N * 2.0 < tk_.rule.delta) {
       T lo = gl - tolx, hi = gu + tolx;
       int* const first = reinterpret_cast<int*>(lam);  // scratch: first point above lambda_1, by wave
-      for (int it = 0; it < 16; ++it) {
+      for (int it = 0;; ++it) {
         if (it >= 4) {
           if (tid < kWave) {  // lane 0: the lower end, the others: the upper one
             const int c = sturm_count(dd, ee, N, T(tk_.rule.delta) * (tid == 0 ? lo : hi), pivmin);
             if (tid < 2) first[tid] = c;
           }
           __syncthreads();
-          const bool done = first[0] == first[1] || !(hi - lo > tolx);
+          const bool done = first[0] == first[1] || !(hi - lo > tolx) || it == 16;
           __syncthreads();
           if (done) break;  // uniform
         }
